@@ -374,8 +374,15 @@ typedef struct opm_problem {
    * set, the dead-oil assembly with fixed-source wells runs on lattice
    * tiles whose cell properties and face fluxes are staged in LDS; NULL
    * (or live oil, or standard wells) selects the row-per-lane assembly.
-   * Both give the same residual and Jacobian up to rounding. */
-  int32_t nx, ny, nz, pad_l;
+   * Both give the same residual and Jacobian up to rounding.
+   * ilu_box (optional, 0: not given): the box of a block-ILU0 topology,
+   * bx | by << 10 | bz << 20 (each axis at most 1023 cells, the bx, by, bz
+   * given to opm_topology_build_blocks, at most the lattice's).  With it, or
+   * without a block topology, the ILU(0) is factored and swept by lattice
+   * columns, one workgroup per subdomain or per tile of the whole system;
+   * otherwise by the position lists below.  Both give the same factors and
+   * solutions. */
+  int32_t nx, ny, nz, ilu_box;
   const int32_t* box_cell;
   /* cell_box [n_cells] (device): the box index of each active cell (the
    * inverse of box_cell).  With both maps, the ILU(0) sweeps of a system

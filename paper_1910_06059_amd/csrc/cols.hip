@@ -1,0 +1,754 @@
+// ILU(0) preconditioner by columns: the factorisation and the triangular
+// solves of the boxes of a lattice, one workgroup per box (cols_dev.h has the
+// shape of the sweeps and the storage).  Two uses:
+//  - the block ILU0 (paper sec. 2.5), a box per subdomain, and the ILU(0) of
+//    a whole system of few columns, one box: both sweeps in one launch, the
+//    forward results in LDS;
+//  - the ILU(0) of a whole lattice (sec. 2.3.1) cut into tiles that exchange
+//    the values of their boundary columns while they run (HALO): one launch
+//    per sweep.  The chain of dependent levels is the whole system's, but all
+//    tiles walk it at once, a few levels behind each other.
+#include <algorithm>
+
+#include "cols_dev.h"
+
+namespace opm {
+
+extern int g_plane_spin;
+
+namespace {
+
+using namespace ilu;
+
+constexpr size_t kMaxColLds = 150 * 1024;
+
+inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
+
+// ---------------------------------------------------------- factorisation
+// Three launches (and the exchange arrays' reset for tiles):
+//  - k_cols_slots finds where the blocks of every slot's row lie, all slots at
+//    once, so that the recursion loads one 32-byte index record per slot
+//    instead of following a chain of three loads;
+//  - k_cols_pivots walks the levels: D_i = A_ii - sum_k A_ik (D_k^{-1} A_ki)
+//    takes the scaled upper blocks that the three lower neighbours have just
+//    formed (its own column's from the quad's registers, the others' from
+//    LDS), inverts, scales the row's upper blocks and passes them on.  Only
+//    what the next level waits for is in this chain.  Lane eq of a quad holds
+//    row eq of the lower blocks and of D, and column eq of the upper blocks, so
+//    that each product needs either only its own values or the whole D^{-1},
+//    which every lane forms;
+//  - k_cols_records scales the blocks and writes the sweeps' records, all
+//    slots at once (it reads the matrix a second time: cheaper than its stores
+//    and its products in the chain).
+// Factorisation with its records, by HIP events, against the recursion by
+// position and a packing pass: 9000 cells 40.2 -> 25.7 us, 500k cells
+// (4x4x50 boxes) 304 -> 201 us FP64.
+struct FacIn {
+  const double* J;
+  const int32_t* row_ptr;
+  const int32_t* box_cell;
+  const int32_t* iperm;
+  int32_t* status;
+  double* dinv64;
+  void* dinv;   // in the sweeps' precision (FP32: an array of its own)
+  int ns, nnzb;
+};
+
+// In a slot's index record: no such block (past the end of the matrix, with
+// room for the offsets added to it).
+constexpr unsigned kNoBlock = 0xffffff00u;
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_cols_slots(ColView<T> v, FacIn f) {
+  const ColGrid& g = v.g;
+  const size_t slot = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0)   // the padding of the inverse pivots
+    for (int e = threadIdx.x; e < 9 * (f.ns - g.n); e += 256) {
+      const size_t at = (size_t)(e / (f.ns - g.n)) * f.ns + g.n + e % (f.ns - g.n);
+      f.dinv64[at] = 0.0;
+      if (sizeof(T) != sizeof(double)) ((T*)f.dinv)[at] = (T)0;
+    }
+  if (slot >= g.slots()) return;
+  const int c = (int)(slot % g.C), s = (int)(slot / g.C % g.L), box = (int)(slot / g.C / g.L);
+  const int cj = c / g.bx, ci = c - cj * g.bx, kk = s - ci - cj;
+  const int gi = box % g.nbx * g.bx + ci, gj = box / g.nbx % g.nby * g.by + cj;
+  const int k = box / (g.nbx * g.nby) * g.bz + kk;
+  FacSlot rec{{kNoBlock, kNoBlock, kNoBlock}, kNoBlock, {kNoBlock, kNoBlock, kNoBlock}, 0};
+  int cell = -1;
+  if (c < g.bx * g.by && gi < g.nx && gj < g.ny && kk >= 0 && kk < g.bz && k < g.nz) {
+    const int sxy = g.nx * g.ny;
+    const int32_t* b = f.box_cell + gi + g.nx * gj + (size_t)sxy * k;
+    cell = b[0];
+    if (cell >= 0) {
+      const bool in[6] = {k > 0, gj > 0, gi > 0, gi + 1 < g.nx, gj + 1 < g.ny, k + 1 < g.nz};
+      const int step[6] = {-sxy, -g.nx, -1, 1, g.nx, sxy};
+      const bool h = g.halo != 0;
+      const bool own[6] = {kk > 0, h || cj > 0, h || ci > 0, h || ci + 1 < g.bx,
+                           h || cj + 1 < g.by, kk + 1 < g.bz};
+      unsigned at = (unsigned)f.row_ptr[cell] * 72u;   // the row's blocks in column order
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        if (q == 3) {
+          rec.diag = at;
+          at += 72u;
+        }
+        const bool act = in[q] && b[in[q] ? step[q] : 0] >= 0;
+        if (act && own[q]) (q < 3 ? rec.lo[q] : rec.up[q - 3]) = at;
+        at += act ? 72u : 0u;
+      }
+      rec.pos = f.iperm[cell];
+    }
+  }
+  v.fac[slot] = rec;
+  v.idx[slot] = cell + 1;
+}
+
+// three consecutive doubles
+__device__ __forceinline__ void load3(__amdgpu_buffer_rsrc_t r, unsigned off, double* x) {
+  typedef double v2 __attribute__((ext_vector_type(2)));
+  const v2 w = __builtin_bit_cast(v2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+  x[0] = w[0];
+  x[1] = w[1];
+  x[2] = col_load<double>(r, (int)off + 16);
+}
+
+struct FacRow {
+  double lo[3][3], D[3];   // row a of the lower blocks (k-, j-, i-) and of the diagonal
+  double up[3][3];         // column a of the upper blocks (i+, j+, k+)
+  double hx[3], hy[3];     // HALO: column a of the neighbouring tiles' scaled upper blocks
+};
+template <typename T, int NT, bool HALO>
+__global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
+  typedef ColRows<NT, HALO> R;
+  constexpr int kB = 10;   // doubles of a block's place in LDS
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // scaled upper blocks towards i + 1 and j + 1 of every column, column by
+  // column: two levels
+  Lds<double>* ui = (Lds<double>*)reinterpret_cast<double*>(smem);
+  Lds<double>* uj = ui + 2 * kB * R::kRows;
+  const ColGrid& g = v.g;
+  const int box = (int)blockIdx.x, L = g.L, C = g.C;
+  const ColLane ln(g);
+  const int a = min(ln.eq, 2);
+  const int I = box % g.nbx, Jt = (box / g.nbx) % g.nby;
+  for (int e = threadIdx.x; e < 4 * kB * R::kRows; e += NT) ui[e] = 0.0;
+  __syncthreads();
+  constexpr int kOut = (int)0x80000000;
+  const __amdgpu_buffer_rsrc_t rslot = col_rsrc(v.fac + (size_t)box * L * C, (size_t)L * C * 32);
+  const __amdgpu_buffer_rsrc_t rj = col_rsrc(f.J, (size_t)f.nnzb * 72);
+  const int vslot = ln.c < C ? ln.c * 32 : kOut;
+  auto slot_at = [&](int s) {
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    const int so = min(s, L - 1) * C * 32;
+    const u4 p = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vslot, so, 0));
+    const u4 q = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vslot, so + 16, 0));
+    return FacSlot{{p[0], p[1], p[2]}, p[3], {q[0], q[1], q[2]}, (int)q[3]};
+  };
+  // HALO exchange: the scaled upper blocks of the boundary columns
+  const bool edge_i = HALO && ln.in_box && ln.ci == 0, edge_j = HALO && ln.in_box && ln.cj == 0;
+  const bool from_x = edge_i && I > 0, from_y = edge_j && Jt > 0;
+  const bool to_x = HALO && ln.in_box && ln.ci == g.bx - 1 && I + 1 < g.nbx;
+  const bool to_y = HALO && ln.in_box && ln.cj == g.by - 1 && Jt + 1 < g.nby;
+  const int sx = 72 * g.by, sy = 72 * g.bx, szx = g.bz * sx, szy = g.bz * sy;
+  const int kx = ((-ln.ci - ln.cj) * g.by + ln.cj) * 72 + a * 24;
+  const int ky = ((-ln.ci - ln.cj) * g.bx + ln.ci) * 72 + a * 24;
+  const int get_x = from_x ? kx : kOut, get_y = from_y ? ky : kOut;
+  const int put_x = to_x ? kx : kOut, put_y = to_y ? ky : kOut;
+  const double* srcx = HALO ? v.eux + (size_t)(box - 1) * (szx / 8) : nullptr;
+  const double* srcy = HALO ? v.euy + (size_t)(box - g.nbx) * (szy / 8) : nullptr;
+  const __amdgpu_buffer_rsrc_t rsx = col_rsrc(srcx, HALO ? szx : 0),
+                               rsy = col_rsrc(srcy, HALO ? szy : 0);
+  const __amdgpu_buffer_rsrc_t rdx =
+      col_rsrc(HALO ? v.eux + (size_t)box * (szx / 8) : nullptr, HALO ? szx : 0);
+  const __amdgpu_buffer_rsrc_t rdy =
+      col_rsrc(HALO ? v.euy + (size_t)box * (szy / 8) : nullptr, HALO ? szy : 0);
+  auto data = [&](int s, const FacSlot& r, FacRow& b) __attribute__((always_inline)) {
+    load3(rj, r.diag + 24u * a, b.D);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) load3(rj, r.lo[q] + 24u * a, b.lo[q]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) b.up[q][e] = col_load<double>(rj, (int)(r.up[q] + 8u * a) + 24 * e);
+    if (HALO) {
+      const int l = min(s, L - 1);
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        b.hx[e] = col_load<double, kCoherent>(rsx, get_x + l * sx + 8 * e);
+        b.hy[e] = col_load<double, kCoherent>(rsy, get_y + l * sy + 8 * e);
+      }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  bool lost = false;
+  auto in_range = [](int off, int size) { return (unsigned)off < (unsigned)size; };
+  auto receive = [&](int s, FacRow& b, int par) __attribute__((always_inline)) {
+    if (!HALO) return;
+    const int l = min(s, L - 1);
+    const int ox = get_x + l * sx, oy = get_y + l * sy;
+    const bool wx = in_range(ox, szx), wy = in_range(oy, szy);
+    bool miss = v.spin == 0 && (wx || wy);
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      miss = miss || (wx && is_unset(b.hx[e])) || (wy && is_unset(b.hy[e]));
+    for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
+      if (it >= v.spin || lost) {
+        lost = true;
+        __hip_atomic_store(v.gave_up + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (f.status) *f.status = OPM_EHIP;
+        if (miss) {
+#pragma unroll
+          for (int e = 0; e < 3; ++e) b.hx[e] = b.hy[e] = 0.0;
+        }
+        break;
+      }
+      if (miss) {
+        miss = false;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          if (wx) b.hx[e] = coherent_reread(srcx + ox / 8 + e);
+          if (wy) b.hy[e] = coherent_reread(srcy + oy / 8 + e);
+          miss = miss || (wx && is_unset(b.hx[e])) || (wy && is_unset(b.hy[e]));
+        }
+      }
+      if ((it & 63) == 63 &&
+          __hip_atomic_load(v.gave_up + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        lost = true;
+    }
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      if (edge_i) ui[(par * R::kRows + R::kHalo + ln.cj) * kB + 3 * a + e] = b.hx[e];
+      if (edge_j) uj[(par * R::kRows + R::kHalo + ln.ci) * kB + 3 * a + e] = b.hy[e];
+    }
+  };
+  int row_i = R::kZero, row_j = R::kZero;
+  if (ln.c < g.bx * g.by) {
+    row_i = ln.ci > 0 ? ln.c - 1 : HALO ? R::kHalo + ln.cj : R::kZero;
+    row_j = ln.cj > 0 ? ln.c - g.bx : HALO ? R::kHalo + ln.ci : R::kZero;
+  }
+  double uk[9];   // the column's scaled block towards k + 1 on the previous level
+#pragma unroll
+  for (int e = 0; e < 9; ++e) uk[e] = 0.0;
+  // level s: the rows of the next DEPTH levels and the indices of the levels
+  // up to s + 5 in flight (512 threads have registers for one level of rows)
+  constexpr int DEPTH = NT < 512 ? 2 : 1, ND = DEPTH + 1;
+  FacRow rows[ND];
+  FacSlot slots[6];
+#pragma unroll
+  for (int s = 0; s < 5; ++s) slots[s] = slot_at(s);
+#pragma unroll
+  for (int s = 0; s < DEPTH; ++s) data(s, slots[s], rows[s]);
+  receive(0, rows[0], 0);
+  level_barrier<NT>();
+  auto step = [&](int s, int qq) __attribute__((always_inline)) {
+    const int par = qq & 1;
+    double Ui[9], Uj[9];   // column by column
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      Uj[e] = uj[(par * R::kRows + row_j) * kB + e];
+      Ui[e] = ui[(par * R::kRows + row_i) * kB + e];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    slots[(qq + 5) % 6] = slot_at(s + 5);
+    data(s + DEPTH, slots[(qq + DEPTH) % 6], rows[(qq + DEPTH) % ND]);
+    const FacRow& b = rows[qq % ND];
+    const FacSlot& r = slots[qq % 6];
+    const bool live = r.diag != kNoBlock && ln.c < C;
+    double D[3] = {b.D[0], b.D[1], b.D[2]};
+    auto update = [&](const double* A, const double* U) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        const double upd = dot3(A[0], U[3 * e], A[1], U[3 * e + 1], A[2], U[3 * e + 2]);
+        D[e] -= upd;
+      }
+    };
+    update(b.lo[0], uk);
+    update(b.lo[1], Uj);
+    update(b.lo[2], Ui);
+    double full[9], inv[9];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      full[e] = quad_lane<0>(D[e]);
+      full[3 + e] = quad_lane<1>(D[e]);
+      full[6 + e] = quad_lane<2>(D[e]);
+    }
+    const bool ok = inverse3(full, inv);
+    if (!ok && live && f.status) *f.status = OPM_ESINGULAR;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) inv[e] = ok && live ? inv[e] : 0.0;
+    // column a of D^{-1} A for the upper blocks
+    double U[3][3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        U[q][e] = dot3(inv[3 * e], b.up[q][0], inv[3 * e + 1], b.up[q][1], inv[3 * e + 2],
+                       b.up[q][2]);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      if (ln.eq < 3) {
+        ui[((par ^ 1) * R::kRows + ln.c) * kB + 3 * a + e] = U[0][e];
+        uj[((par ^ 1) * R::kRows + ln.c) * kB + 3 * a + e] = U[1][e];
+      }
+      uk[e] = quad_lane<0>(U[2][e]);
+      uk[3 + e] = quad_lane<1>(U[2][e]);
+      uk[6 + e] = quad_lane<2>(U[2][e]);
+    }
+    if (HALO) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        col_store<kCoherent>(U[0][e], rdx, put_x + s * sx + 8 * e);
+        col_store<kCoherent>(U[1][e], rdy, put_y + s * sy + 8 * e);
+      }
+    }
+    if (live && ln.eq < 3) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        const double di = a == 0 ? inv[e] : a == 1 ? inv[3 + e] : inv[6 + e];
+        const size_t at = (size_t)(3 * a + e) * f.ns + r.pos;
+        f.dinv64[at] = di;
+        if (sizeof(T) != sizeof(double)) ((T*)f.dinv)[at] = (T)di;
+      }
+    }
+    receive(s + 1, rows[(qq + 1) % ND], par ^ 1);
+    level_barrier<NT>();
+  };
+  for (int s = 0;; s += 6) {
+#pragma unroll
+    for (int qq = 0; qq < 6; ++qq) {
+      step(s + qq, qq);
+      if (s + qq + 1 >= L) return;
+    }
+  }
+}
+
+// The sweeps' records: row a of D^{-1} A for the lower blocks and of D^{-1}
+// (forward), of D^{-1} A for the upper blocks (backward).
+template <typename T>
+__global__ __launch_bounds__(256) void k_cols_records(ColView<T> v, FacIn f) {
+  typedef typename Vec16<T>::type V;
+  constexpr int ts = (int)sizeof(T), kV = 16 / ts;
+  const ColGrid& g = v.g;
+  const size_t slot = (size_t)blockIdx.x * 64 + threadIdx.x / 4;
+  const int a = (int)(threadIdx.x & 3u);
+  if (slot >= g.slots() || a == 3) return;
+  const FacSlot r = v.fac[slot];
+  const bool live = r.diag != kNoBlock;
+  double di[3];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) di[e] = live ? f.dinv64[(size_t)(3 * a + e) * f.ns + r.pos] : 0.0;
+  const __amdgpu_buffer_rsrc_t rj = col_rsrc(f.J, (size_t)f.nnzb * 72);
+  auto scaled = [&](unsigned o, T* S) {
+    double A[9];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) load3(rj, o + 24u * e, A + 3 * e);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) S[e] = (T)dot3(di[0], A[e], di[1], A[3 + e], di[2], A[6 + e]);
+  };
+  T wf[12], wb[9];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    scaled(r.lo[q], wf + 3 * q);
+    scaled(r.up[q], wb + 3 * q);
+    wf[9 + q] = (T)di[q];
+  }
+  const size_t c = slot % g.C, level = slot / g.C;
+  char* pf = (char*)v.rec_f + level * col_rec_bytes<T, true>(g.C) + (c * 3 + a) * 16;
+  char* pb = (char*)v.rec_b + level * col_rec_bytes<T, false>(g.C);
+#pragma unroll
+  for (int q = 0; q < 12 / kV; ++q) {
+    V w;
+#pragma unroll
+    for (int e = 0; e < kV; ++e) w[e] = wf[q * kV + e];
+    *reinterpret_cast<V*>(pf + (size_t)q * g.C * 48) = w;
+  }
+#pragma unroll
+  for (int q = 0; q < 8 / kV; ++q) {
+    V w;
+#pragma unroll
+    for (int e = 0; e < kV; ++e) w[e] = wb[q * kV + e];
+    *reinterpret_cast<V*>(pb + (size_t)q * g.C * 48 + (c * 3 + a) * 16) = w;
+  }
+  *reinterpret_cast<T*>(pb + (size_t)8 * g.C * 3 * ts + (c * 3 + a) * ts) = wb[8];
+}
+
+// Fills `n` values with the marker of a value not yet written.
+template <typename T>
+__device__ __forceinline__ void mark(T* p, size_t n, size_t first, size_t stride) {
+  T u;
+  unset_value(u);
+  for (size_t e = first; e < n; e += stride) p[e] = u;
+}
+
+// Before a factorisation: every exchange array holds the marker, no wait gave up.
+template <typename T>
+__global__ __launch_bounds__(256) void k_cols_reset(ColView<T> v) {
+  const size_t first = blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+  const size_t nx = (size_t)v.g.boxes() * v.g.bz * v.g.by, ny = (size_t)v.g.boxes() * v.g.bz * v.g.bx;
+  for (int q = 0; q < 2; ++q) {
+    mark(v.ex[q], 3 * nx, first, stride);
+    mark(v.ey[q], 3 * ny, first, stride);
+  }
+  mark(v.eux, 9 * nx, first, stride);
+  mark(v.euy, 9 * ny, first, stride);
+  if (first < 3) v.gave_up[first] = 0;
+}
+
+// --------------------------------------------------------------- sweeps
+// Start of a sweep kernel: the skip flag or the iteration's state word (read
+// once for the workgroup) and the LDS rows cleared.  Returns false if the
+// sweep does not run.
+template <typename T, int NT, bool HALO, int MODE>
+__device__ __forceinline__ bool cols_begin(Lds<T>* nb, const int32_t* skip, const kry::Fused& f,
+                                           int* word, int& state) {
+  int w = 0;
+  if (threadIdx.x == 0) w = MODE != kry::kFuseNone ? f.sc->state : skip ? *skip : 0;
+  for (int e = threadIdx.x; e < 8 * ColRows<NT, HALO>::kRows; e += NT) nb[e] = (T)0;
+  if (threadIdx.x == 0) *word = w;
+  __syncthreads();
+  state = *word;
+  if (MODE == kry::kFuseNone) return state == 0;
+  if (state != kry::kRunning) {
+    if (MODE == kry::kFuseBegin && state == kry::kHalfPending && blockIdx.x == 0 &&
+        threadIdx.x == 0)
+      f.sc->state = kry::kDone;
+    return false;
+  }
+  return true;
+}
+
+// the iteration's tests and scalars (every workgroup on the same partials)
+template <int NT, int MODE>
+__device__ __forceinline__ bool cols_gate(const kry::Fused& f, int state, double* red,
+                                          BlockRhs& q) {
+  if (MODE == kry::kFuseBegin)
+    return kry::begin_iteration<NT>(*f.sc, state, f.part_a, f.part_b, f.n_part, red, q.beta,
+                                    q.omega);
+  if (MODE == kry::kFuseS)
+    return kry::alpha_step<NT>(*f.sc, state, f.part_a, f.n_part, red, q.alpha);
+  return true;
+}
+
+// x = M^{-1} r of one box per workgroup, both sweeps.  MODE (kry::FusedMode):
+// the forward right-hand side is r, or the p or s update of a BiCGStab
+// iteration, preceded by the tests of that iteration; with the s update the
+// workgroup's partial of <s, s> goes to f.part_out.
+template <typename T, int NT, int DEPTH, int MODE>
+__global__ __launch_bounds__(NT) void k_cols_apply(ColView<T> v, const double* r, double* x,
+                                                    const int32_t* skip, kry::Fused f) {
+  __shared__ double red[NT / 64];
+  __shared__ int word;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  Lds<T>* nb = (Lds<T>*)reinterpret_cast<T*>(smem);
+  Lds<T>* zl = nb + 8 * ColRows<NT, false>::kRows;
+  int state;
+  if (!cols_begin<T, NT, false, MODE>(nb, skip, f, &word, state)) return;
+  BlockRhs q{r, f, 0.0, 0.0, 0.0};
+  double ss = 0.0;
+  const int box = (int)blockIdx.x;
+  if (!col_sweep<T, NT, DEPTH, true, MODE, false>(
+          v, box, q, nb, zl, x, ss,
+          [&](BlockRhs& qq) { return cols_gate<NT, MODE>(f, state, red, qq); }))
+    return;
+  if (MODE == kry::kFuseS) {
+    const double tot = block_sum<NT>(ss, red);
+    if (threadIdx.x == 0) f.part_out[box] = tot;
+  }
+  col_sweep<T, NT, DEPTH, false, MODE, false>(v, box, q, nb, zl, x, ss,
+                                              [](BlockRhs&) { return true; });
+}
+
+// One sweep of the tiles of a whole lattice.  Backward workgroups take the
+// tiles in descending order, so that they too wait on lower indices only.
+template <typename T, int NT, int DEPTH, bool FWD, int MODE>
+__global__ __launch_bounds__(NT) void k_cols_tiles(ColView<T> v, const double* r, double* x,
+                                                    const int32_t* skip, kry::Fused f) {
+  __shared__ double red[NT / 64];
+  __shared__ int word;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  Lds<T>* nb = (Lds<T>*)reinterpret_cast<T*>(smem);
+  int state;
+  // (the backward launch of a fused pair is skipped like its forward one: by
+  // the iteration's state, as `skip`)
+  constexpr int M = FWD ? MODE : kry::kFuseNone;
+  if (!cols_begin<T, NT, true, M>(nb, skip, f, &word, state)) return;
+  BlockRhs q{r, f, 0.0, 0.0, 0.0};
+  double ss = 0.0;
+  const int box = FWD ? (int)blockIdx.x : v.g.boxes() - 1 - (int)blockIdx.x;
+  if (!col_sweep<T, NT, DEPTH, FWD, M, true>(
+          v, box, q, nb, (Lds<T>*)nullptr, x, ss,
+          [&](BlockRhs& qq) { return cols_gate<NT, M>(f, state, red, qq); }))
+    return;
+  if (FWD && MODE == kry::kFuseS) {
+    const double tot = block_sum<NT>(ss, red);
+    if (threadIdx.x == 0) f.part_out[box] = tot;
+  }
+  // the other sweep's exchange arrays of this tile, and its give-up word
+  constexpr int o = FWD ? 1 : 0;
+  const size_t nx = (size_t)3 * v.g.bz * v.g.by, ny = (size_t)3 * v.g.bz * v.g.bx;
+  mark(v.ex[o] + box * nx, nx, threadIdx.x, NT);
+  mark(v.ey[o] + box * ny, ny, threadIdx.x, NT);
+  if (blockIdx.x == 0 && threadIdx.x == 0) v.gave_up[o] = 0;
+}
+
+// ------------------------------------------------------------ host side
+// one flag per kernel instantiation
+bool g_cols_lds_set[64] = {};
+
+template <typename K>
+int allow_lds(K kernel, int slot) {
+  if (!g_cols_lds_set[slot]) {
+    hipFuncAttributes at;
+    OPM_TRY_HIP(hipFuncGetAttributes(&at, reinterpret_cast<const void*>(kernel)));
+    OPM_TRY_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    160 * 1024 - (int)at.sharedSizeBytes));
+    g_cols_lds_set[slot] = true;
+  }
+  return OPM_OK;
+}
+
+int waves_of(const ColGrid& g) { return g.C / kColsPerWave; }
+// threads of a box's workgroup: a power of two of wavefronts
+int threads_of(const ColGrid& g) {
+  int nt = 64;
+  while (nt < 64 * waves_of(g)) nt *= 2;
+  return nt;
+}
+
+ColGrid make_grid(const opm_problem* pb, int bx, int by, int bz, bool halo) {
+  ColGrid g;
+  g.nx = pb->nx;
+  g.ny = pb->ny;
+  g.nz = pb->nz;
+  g.bx = std::min(bx, g.nx);
+  g.by = std::min(by, g.ny);
+  g.bz = std::min(bz, g.nz);
+  g.nbx = (g.nx + g.bx - 1) / g.bx;
+  g.nby = (g.ny + g.by - 1) / g.by;
+  g.nbz = (g.nz + g.bz - 1) / g.bz;
+  g.C = (int)((long)((long)g.bx * g.by + kColsPerWave - 1) / kColsPerWave * kColsPerWave);
+  g.L = g.bx + g.by + g.bz - 2;
+  g.n = pb->n_cells;
+  g.halo = halo && g.boxes() > 1;
+  return g;
+}
+
+template <typename T>
+size_t apply_lds(const ColGrid& g) {
+  const size_t rows = threads_of(g) / 4 + 1 + (g.halo ? kHaloRows : 0);
+  return sizeof(T) * 8 * rows + (g.halo ? 0 : sizeof(T) * 3 * (size_t)g.L * g.C);
+}
+size_t factor_lds(const ColGrid& g) {
+  const size_t rows = threads_of(g) / 4 + 1 + (g.halo ? kHaloRows : 0);
+  return sizeof(double) * 4 * 10 * rows;
+}
+
+bool fits(const ColGrid& g) {
+  // (LDS for FP64, so that both precisions take the same boxes; the
+  // records' and vectors' byte offsets stay below 2^31)
+  return (long)g.bx * g.by * 4 <= kMaxColThreads && apply_lds<double>(g) <= kMaxColLds &&
+         factor_lds(g) <= kMaxColLds && (size_t)g.L * g.C * 288 < ((size_t)1 << 30) &&
+         (!g.halo || (g.bx + g.by <= kHaloRows && g.nbz == 1)) && g.n < (1 << 26) &&
+         // at most twice as many slots as cells of the lattice, or few of them
+         (g.slots() <= 2 * (size_t)g.nx * g.ny * g.nz || g.slots() <= 65536);
+}
+
+bool lattice(const opm_problem* pb) {
+  return pb->n_cells > 0 && pb->nx > 0 && pb->ny > 0 && pb->nz > 0 && pb->box_cell &&
+         pb->cell_box && pb->row_ptr && pb->iperm && (long)pb->nx * pb->ny < (1 << 28) &&
+         (size_t)pb->nnzb * 72 < 0xfffffe00u;   // (byte offsets into the Jacobian)
+}
+
+// The boxes of a problem's preconditioner; false: not by columns.
+bool grid_of(const opm_problem* pb, ColGrid& g) {
+  if (!lattice(pb)) return false;
+  if (pb->n_sub > 1) {
+    const int bx = pb->ilu_box & 1023, by = (pb->ilu_box >> 10) & 1023, bz = (pb->ilu_box >> 20) & 1023;
+    if (bx <= 0 || by <= 0 || bz <= 0) return false;
+    g = make_grid(pb, bx, by, bz, false);
+    return fits(g);
+  }
+  // the whole system: one box of at most 128 columns (300 cells: an
+  // application 28 -> 24 us, and the updates of BiCGStab fused into it, 8
+  // launches per iteration -> 5), else tiles of 8x8 columns (500k cells: an
+  // application 1120 us by planes -> 463 us; factored 1900 -> 870 us)
+  if ((long)pb->nx * pb->ny <= 128) {
+    g = make_grid(pb, pb->nx, pb->ny, pb->nz, false);
+    if (fits(g)) return true;
+  }
+  g = make_grid(pb, 8, 8, pb->nz, true);
+  return fits(g);
+}
+
+template <typename T>
+size_t view_bytes_of(const ColGrid& g) {
+  const size_t s = g.slots();
+  size_t b = al256(sizeof(T) * 36 * s) + al256(sizeof(T) * 27 * s) + al256(4 * s) +
+             al256(sizeof(FacSlot) * s);
+  if (g.halo) {
+    const size_t nx = (size_t)g.boxes() * g.bz * g.by, ny = (size_t)g.boxes() * g.bz * g.bx;
+    b += al256(sizeof(T) * 3 * s) + 2 * (al256(sizeof(T) * 3 * nx) + al256(sizeof(T) * 3 * ny)) +
+         al256(72 * nx) + al256(72 * ny) + 256;
+  }
+  return b;
+}
+
+template <typename T>
+ColView<T> view_of(const ColGrid& g, void* base) {
+  ColView<T> v{};
+  v.g = g;
+  const size_t s = g.slots();
+  char* c = (char*)base;
+  auto take = [&](size_t bytes) {
+    char* p = c;
+    c += al256(bytes);
+    return p;
+  };
+  v.rec_f = (T*)take(sizeof(T) * 36 * s);
+  v.rec_b = (T*)take(sizeof(T) * 27 * s);
+  v.idx = (int32_t*)take(4 * s);
+  v.fac = (FacSlot*)take(sizeof(FacSlot) * s);
+  if (g.halo) {
+    const size_t nx = (size_t)g.boxes() * g.bz * g.by, ny = (size_t)g.boxes() * g.bz * g.bx;
+    v.z = (T*)take(sizeof(T) * 3 * s);
+    for (int q = 0; q < 2; ++q) {
+      v.ex[q] = (T*)take(sizeof(T) * 3 * nx);
+      v.ey[q] = (T*)take(sizeof(T) * 3 * ny);
+    }
+    v.eux = (double*)take(72 * nx);
+    v.euy = (double*)take(72 * ny);
+    v.gave_up = (int32_t*)take(256);
+  }
+  v.spin = (unsigned)g_plane_spin;
+  return v;
+}
+
+// The column arrays follow the inverse pivots (the other shapes' arrays lie
+// there too: an ILU buffer is swept by the shape that factored it).
+template <typename T>
+size_t pivot_bytes(const opm_problem* pb) {
+  return al256((sizeof(double) + (sizeof(T) != sizeof(double) ? sizeof(T) : 0)) * 9 *
+               ilu_padded(pb->n_cells));
+}
+
+template <typename T>
+int factor_impl(const opm_problem* pb, const ColGrid& g, const double* J, void* ilu,
+                int32_t* status, hipStream_t s) {
+  const ColView<T> v = view_of<T>(g, (char*)ilu + pivot_bytes<T>(pb));
+  const size_t ns = ilu_padded(pb->n_cells);
+  double* d64 = (double*)ilu;
+  const FacIn f{J, pb->row_ptr, pb->box_cell, pb->iperm, status, d64,
+                sizeof(T) == sizeof(double) ? (void*)d64 : (void*)(d64 + 9 * ns), (int)ns,
+                pb->nnzb};
+  if (g.halo)
+    hipLaunchKernelGGL(k_cols_reset<T>, dim3(256), dim3(256), 0, s, v);
+  const long slots = (long)g.slots();
+  hipLaunchKernelGGL(k_cols_slots<T>, dim3(blocks_for(slots, 256)), dim3(256), 0, s, v, f);
+  const size_t lds = factor_lds(g);
+  const int slot = (sizeof(T) == 8 ? 0 : 5);
+#define OPM_COLS_FACTOR(NT, SL)                                                              \
+  do {                                                                                       \
+    if (g.halo) {                                                                            \
+      hipLaunchKernelGGL((k_cols_pivots<T, (NT < 512 ? NT : 256), true>), dim3(g.boxes()),   \
+                         dim3(NT), lds, s, v, f);                                            \
+    } else {                                                                                 \
+      OPM_TRY(allow_lds(k_cols_pivots<T, NT, false>, slot + SL));                            \
+      hipLaunchKernelGGL((k_cols_pivots<T, NT, false>), dim3(g.boxes()), dim3(NT), lds, s, v, \
+                         f);                                                                 \
+    }                                                                                        \
+  } while (0)
+  switch (threads_of(g)) {
+    case 64: OPM_COLS_FACTOR(64, 0); break;
+    case 128: OPM_COLS_FACTOR(128, 1); break;
+    case 256: OPM_COLS_FACTOR(256, 2); break;
+    default: OPM_COLS_FACTOR(512, 3); break;
+  }
+#undef OPM_COLS_FACTOR
+  hipLaunchKernelGGL(k_cols_records<T>, dim3(blocks_for(slots, 64)), dim3(256), 0, s, v, f);
+  OPM_TRY_HIP(hipGetLastError());
+  return OPM_OK;
+}
+
+template <typename T, int MODE>
+int apply_impl(const opm_problem* pb, const ColGrid& g, void* ilu, const double* r, double* x,
+               const int32_t* skip, const kry::Fused& f, hipStream_t s) {
+  const ColView<T> v = view_of<T>(g, (char*)ilu + pivot_bytes<T>(pb));
+  const size_t lds = apply_lds<T>(g);
+  const int slot = 10 + (sizeof(T) == 8 ? 0 : 15) + 5 * MODE;
+  const int32_t* skip2 = MODE == kry::kFuseNone ? skip : &f.sc->state;
+#define OPM_COLS(NT, D, SL)                                                                  \
+  do {                                                                                       \
+    if (g.halo) {                                                                            \
+      hipLaunchKernelGGL((k_cols_tiles<T, (NT < 512 ? NT : 256), 3, true, MODE>),            \
+                         dim3(g.boxes()), dim3(NT), lds, s, v, r, x, skip, f);               \
+      hipLaunchKernelGGL((k_cols_tiles<T, (NT < 512 ? NT : 256), 3, false, kry::kFuseNone>), \
+                         dim3(g.boxes()), dim3(NT), lds, s, v, r, x, skip2, f);              \
+    } else {                                                                                 \
+      OPM_TRY(allow_lds(k_cols_apply<T, NT, D, MODE>, slot + SL));                           \
+      hipLaunchKernelGGL((k_cols_apply<T, NT, D, MODE>), dim3(g.boxes()), dim3(NT), lds, s,  \
+                         v, r, x, skip, f);                                                  \
+    }                                                                                        \
+  } while (0)
+  switch (threads_of(g)) {
+    case 64: OPM_COLS(64, 3, 0); break;
+    case 128: OPM_COLS(128, 3, 1); break;
+    case 256: OPM_COLS(256, 3, 2); break;
+    default: OPM_COLS(512, 3, 3); break;
+  }
+#undef OPM_COLS
+  OPM_TRY_HIP(hipGetLastError());
+  return OPM_OK;
+}
+
+}  // namespace
+
+// The preconditioner of pb is factored and applied by columns.
+bool cols_capable(const opm_problem* pb) {
+  ColGrid g;
+  return grid_of(pb, g);
+}
+
+// Workgroups of a sweep (the partial sums of a fused one).
+int cols_boxes(const opm_problem* pb) {
+  ColGrid g;
+  return grid_of(pb, g) ? g.boxes() : 0;
+}
+
+size_t cols_bytes(const opm_problem* pb, int precision) {
+  ColGrid g;
+  if (!grid_of(pb, g)) return 0;
+  return precision == OPM_PREC_MIXED ? pivot_bytes<float>(pb) + view_bytes_of<float>(g)
+                                     : pivot_bytes<double>(pb) + view_bytes_of<double>(g);
+}
+
+int cols_factor(const opm_problem* pb, const double* J, void* ilu, int precision,
+                int32_t* status, hipStream_t s) {
+  ColGrid g;
+  if (!grid_of(pb, g)) return OPM_EINVAL;
+  return precision == OPM_PREC_MIXED ? factor_impl<float>(pb, g, J, ilu, status, s)
+                                     : factor_impl<double>(pb, g, J, ilu, status, s);
+}
+
+// mode: kry::FusedMode; skip (may be null, mode kFuseNone only): the sweeps
+// return at once while *skip != 0.
+int cols_apply(const opm_problem* pb, void* ilu, int precision, int mode, const double* r,
+               double* x, const int32_t* skip, const kry::Fused& f, hipStream_t s) {
+  ColGrid g;
+  if (!grid_of(pb, g)) return OPM_EINVAL;
+  if (precision == OPM_PREC_MIXED) {
+    switch (mode) {
+      case kry::kFuseBegin: return apply_impl<float, kry::kFuseBegin>(pb, g, ilu, r, x, skip, f, s);
+      case kry::kFuseS: return apply_impl<float, kry::kFuseS>(pb, g, ilu, r, x, skip, f, s);
+      default: return apply_impl<float, kry::kFuseNone>(pb, g, ilu, r, x, skip, f, s);
+    }
+  }
+  switch (mode) {
+    case kry::kFuseBegin: return apply_impl<double, kry::kFuseBegin>(pb, g, ilu, r, x, skip, f, s);
+    case kry::kFuseS: return apply_impl<double, kry::kFuseS>(pb, g, ilu, r, x, skip, f, s);
+    default: return apply_impl<double, kry::kFuseNone>(pb, g, ilu, r, x, skip, f, s);
+  }
+}
+
+}  // namespace opm

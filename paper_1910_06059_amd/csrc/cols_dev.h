@@ -1,0 +1,476 @@
+// Column sweeps: the ILU(0) factorisation and triangular solves of a box of
+// lattice columns by one workgroup (paper sec. 2.3.1), shared by the kernels
+// of cols.hip.
+//
+// A workgroup owns a box of bx x by columns of up to bz cells.  Four lanes (a
+// quad) hold one column, lane eq < 3 its equation eq, and walk it one cell per
+// level: on level l the column (ci, cj) of the box is at cell k = l - ci - cj,
+// so its three lower neighbours are its own previous cell (its value is still
+// in the quad's registers), and the cells that the columns ci - 1 and cj - 1
+// handled on the previous level (their values are in LDS).  The backward sweep
+// walks the levels down.  Every address of a lane (records, neighbour rows,
+// exchange slots) is a constant plus a multiple of the level: there is no
+// neighbour index to load and no row position to compute.
+//
+// Why this shape: a sweep is a chain of dependent levels, and one wavefront per
+// SIMD pays for each instruction of a level.  With rows found by position (the
+// sweeps of ilu0.hip) most of a level is index arithmetic and nine LDS reads per
+// lane; here it is one LDS write, four reads, 12 fused multiply-adds and the
+// loads of a later level (about 65 instructions, 0.12-0.16 us per level of a
+// 4x4 box, against 0.24 us).  One application, both sweeps, by HIP events:
+// 9000 cells in 4x4x15 boxes 10.6 -> 8.9 us FP64, 10.1 -> 7.4 us FP32; 500k
+// cells in 4x4x50 boxes 56.8 -> 54.7 us (bound by bandwidth: 63 values per row
+// instead of 72), FP32 33.8 -> 27.1 us.  The dynamic LDS must be declared
+// 16-byte aligned: behind a static 4-byte word its 8-byte reads were misaligned
+// and split (8x8x60 cells, FP64: 131 against 43 us).
+//
+// Storage: slot (box, l, c) for every level and column, also where the column
+// has no cell (ahead of its first and past its last level, inactive cells,
+// columns past the box): those have zero records and the index 0, and their
+// value is zero.  Record of (slot, equation): forward the three scaled lower
+// blocks' rows (k, j, i) and the row of D^{-1}, 12 values in 16-byte chunks;
+// backward the scaled upper blocks' rows (i, j, k), 9 values, the last one in
+// an array of its own.  A level of a box is one contiguous piece.
+//
+// HALO: the boxes are tiles of one system (the ILU(0) of the whole lattice):
+// a tile's western and southern columns need the values of the eastern and
+// northern columns of its neighbours.  Those go through exchange arrays that
+// hold a marker (a signalling NaN, which no arithmetic returns) until they are
+// written through to the device's coherence point.  A tile loads them with the
+// records of their level, several levels ahead, and re-reads those that still
+// held the marker (bounded; a wait that gives up takes NaN, so that the solve
+// returns NaN instead of hanging).  Workgroups are dispatched in index order
+// and wait only on lower indices.  The forward launch refills the exchange
+// arrays of the backward one with the marker and the other way round.
+#pragma once
+
+#include "krylov_dev.h"
+#include "solver_dev.h"
+
+namespace opm {
+namespace ilu {
+
+constexpr int kColsPerWave = 16;
+constexpr int kMaxColThreads = 512;   // (FP64 spills registers at 1024)
+constexpr int kHaloRows = 32;   // most exchange rows (bx + by) of a tile
+
+struct ColGrid {
+  int nx, ny, nz;      // the lattice
+  int bx, by, bz;      // cells of a box per axis
+  int nbx, nby, nbz;   // boxes per axis
+  int C;               // columns of a box, padded to whole wavefronts
+  int L;               // levels of a box
+  int n;               // cells
+  int halo;            // the boxes are tiles of one system
+  __host__ __device__ int boxes() const { return nbx * nby * nbz; }
+  __host__ __device__ size_t slots() const { return (size_t)boxes() * L * C; }
+};
+
+// What the factorisation finds about a slot: byte offsets of the blocks of its
+// row in the Jacobian (lower k-, j-, i-, diagonal, upper i+, j+, k+; past its
+// end where there is none) and its position.
+struct alignas(16) FacSlot {
+  unsigned lo[3], diag, up[3];
+  int pos;
+};
+
+template <typename T>
+struct ColView {
+  ColGrid g;
+  T* rec_f;            // [box][L][12 values as chunks][C][3]
+  T* rec_b;            // [box][L][8 values as chunks, then one][C][3]
+  int32_t* idx;        // [box][L][C] cell + 1, 0: none
+  FacSlot* fac;        // [box][L][C]
+  T* z;                // HALO: [box][L][C][3] forward results
+  T* ex[2];            // HALO: [box][bz][by][3] of the forward / backward sweep
+  T* ey[2];            // HALO: [box][bz][bx][3]
+  double* eux;         // HALO: [box][bz][by][9] scaled upper blocks
+  double* euy;         // HALO: [box][bz][bx][9]
+  int32_t* gave_up;    // HALO: [3] a wait of the forward / backward sweep or the factorisation gave up
+  unsigned spin;       // polls of a wait before it gives up (0: at once)
+};
+
+// A value in LDS (address space 3: 32-bit addresses).
+template <typename T>
+using Lds = __attribute__((address_space(3))) T;
+// Word 3 of a raw buffer resource on gfx9 (32-bit data format, no swizzle).
+constexpr int kBufferWord3 = 0x00020000;
+// sc1: through to (from) the device's coherence point
+constexpr int kCoherent = 16;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t col_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0,
+                                           (int)(unsigned)(bytes < 0xffffffffu ? bytes : 0xffffffffu),
+                                           kBufferWord3);
+}
+
+template <typename T, int AUX = 0>
+__device__ __forceinline__ T col_load(__amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+  if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, AUX));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, AUX));
+}
+template <int AUX = 0>
+__device__ __forceinline__ void col_store(double x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), r, off, soff, AUX);
+}
+template <int AUX = 0>
+__device__ __forceinline__ void col_store(float x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, off, soff, AUX);
+}
+
+// the marker of a value not yet written (signalling NaNs: arithmetic
+// returns quiet ones)
+__device__ __forceinline__ void unset_value(double& v) {
+  v = __builtin_bit_cast(double, 0x7FF4A5A5A5A5A5A5ull);
+}
+__device__ __forceinline__ void unset_value(float& v) { v = __builtin_bit_cast(float, 0x7FA5A5A5u); }
+__device__ __forceinline__ bool is_unset(double v) {
+  return __builtin_bit_cast(unsigned long long, v) == 0x7FF4A5A5A5A5A5A5ull;
+}
+__device__ __forceinline__ bool is_unset(float v) {
+  return __builtin_bit_cast(unsigned, v) == 0x7FA5A5A5u;
+}
+
+// The re-read of a value found not yet written (the slow path): the load and
+// its wait in one block, so that the compiler counts no load of this loop
+// among those in flight (a counted load here would make it wait for every
+// prefetch issued since, at the next use of any of them).
+__device__ __forceinline__ double coherent_reread(const double* p) {
+  unsigned long long b;
+  asm volatile("global_load_dwordx2 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
+  return __builtin_bit_cast(double, b);
+}
+__device__ __forceinline__ float coherent_reread(const float* p) {
+  unsigned b;
+  asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
+  return __builtin_bit_cast(float, b);
+}
+
+// Value of lane K of the lane's quad (DPP quad permutation: a VALU move, no
+// LDS round trip).
+template <int K>
+__device__ __forceinline__ double quad_lane(double x) {
+  constexpr int ctrl = K | (K << 2) | (K << 4) | (K << 6);
+  const long long b = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, ctrl, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+template <int K>
+__device__ __forceinline__ float quad_lane(float x) {
+  constexpr int ctrl = K | (K << 2) | (K << 4) | (K << 6);
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), ctrl, 0xf, 0xf, false));
+}
+
+// The end of a level: a workgroup barrier, or for a one-wavefront
+// workgroup a wavefront-scope fence (the wavefront's LDS operations are
+// performed in order, so the next level's reads see this level's writes
+// without waiting for them to complete).
+template <int NT>
+__device__ __forceinline__ void level_barrier() {
+  if (NT == 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+// Forward right-hand side of a sweep: r itself, or (fused with BiCGStab)
+// p = r + beta (p - omega v) or s = r - alpha v, written back for the rows
+// of the level.
+struct BlockRhs {
+  const double* r;
+  kry::Fused f;
+  double beta, omega, alpha;
+};
+
+// The lane's place in its box: column c = (ci, cj), equation eq (lane 3 of a
+// quad holds none).
+struct ColLane {
+  int c, eq, ci, cj;
+  bool in_box;   // a column of the box, eq < 3
+  __device__ __forceinline__ explicit ColLane(const ColGrid& g) {
+    const int tid = (int)threadIdx.x;
+    c = tid >> 2;
+    eq = tid & 3;
+    in_box = c < g.bx * g.by && eq < 3;
+    cj = c / g.bx;
+    ci = c - cj * g.bx;
+  }
+};
+
+// Rows of the LDS exchange between levels: 4 values per column (equation eq
+// at eq), a zero row, then the exchange rows (HALO); two of these, used in
+// turn by even and odd levels.
+template <int NT, bool HALO>
+struct ColRows {
+  static constexpr int kZero = NT / 4, kHalo = NT / 4 + 1,
+                       kRows = NT / 4 + 1 + (HALO ? kHaloRows : 0);
+};
+template <typename T, int NT, bool HALO>
+constexpr size_t col_rows_bytes() {
+  return sizeof(T) * 2 * 4 * ColRows<NT, HALO>::kRows;
+}
+
+// Bytes of one level of the records.
+template <typename T, bool FWD>
+__host__ __device__ inline int col_rec_bytes(int C) {
+  return C * 3 * (FWD ? 12 : 9) * (int)sizeof(T);
+}
+
+template <typename T>
+struct ColJob {
+  T a[9];       // rows of the three scaled neighbour blocks
+  T d[3];       // forward: row of D^{-1}
+  T z;          // backward, HALO: the forward result
+  double u[3];  // forward: the vector values the right-hand side is made of
+  T hx, hy;     // HALO: this lane's value of the neighbouring tiles
+};
+
+// One sweep of box `box` by the workgroup of NT threads.
+//   nb: LDS rows (col_rows_bytes), all zero on entry to the forward sweep
+//   zl: !HALO: the box's forward results in LDS, [L][C][3]
+// DEPTH levels of loads are in flight while a level is computed.
+// No branch separates a load from its use: what a lane does not need lies
+// past the end of its buffer, reads zero and costs no traffic.
+template <typename T, int NT, int DEPTH, bool FWD, int MODE, bool HALO, typename Gate>
+__device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs& q, Lds<T>* nb,
+                                          Lds<T>* zl, double* x, double& ss, Gate gate) {
+  typedef typename Vec16<T>::type V;
+  typedef ColRows<NT, HALO> R;
+  constexpr int ts = (int)sizeof(T), kV = 16 / ts;
+  // jobs in a ring of ND steps, indices in one of 2 ND (an index is loaded ND
+  // steps ahead of the loads that need it, so it is older than any load they
+  // wait for, and kept until its level is computed); the steps are unrolled
+  // over 2 ND, so that every ring slot is a register of its own
+  constexpr int ND = DEPTH + 1, P = 2 * ND;
+  const ColGrid& g = v.g;
+  const int L = g.L, C = g.C;
+  const ColLane ln(g);
+  const int a = min(ln.eq, 2);
+  constexpr int kOut = (int)0x80000000;   // an offset past the end of any buffer here
+  const bool stored = ln.c < C && ln.eq < 3;
+  const int rb = col_rec_bytes<T, FWD>(C);
+  const __amdgpu_buffer_rsrc_t rrec =
+      col_rsrc((FWD ? v.rec_f : v.rec_b) + (size_t)box * L * C * 3 * (FWD ? 12 : 9),
+               (size_t)L * rb);
+  const __amdgpu_buffer_rsrc_t ridx = col_rsrc(v.idx + (size_t)box * L * C, (size_t)L * C * 4);
+  const int vrec = stored ? (ln.c * 3 + a) * 16 : kOut;
+  const int vlast = stored ? (ln.c * 3 + a) * ts : kOut;   // backward: the ninth value
+  const int vidx = stored ? ln.c * 4 : kOut;
+  const int vcell = a * 8 - 24;           // + 24 ix: this equation of the cell
+  const size_t vec_bytes = 24 * (size_t)g.n;
+  const __amdgpu_buffer_rsrc_t rz =
+      col_rsrc(HALO ? v.z + (size_t)box * L * C * 3 : nullptr, HALO ? (size_t)L * C * 3 * ts : 0);
+  const int vz = stored ? (ln.c * 3 + a) * ts : kOut;
+  // neighbour rows: the column before (forward) or after (backward) in i and j
+  const bool edge_i = FWD ? ln.ci == 0 : ln.ci == g.bx - 1;
+  const bool edge_j = FWD ? ln.cj == 0 : ln.cj == g.by - 1;
+  const bool col = ln.c < g.bx * g.by;
+  int row_i = R::kZero, row_j = R::kZero;
+  if (col) {
+    row_i = !edge_i ? (FWD ? ln.c - 1 : ln.c + 1) : HALO ? R::kHalo + ln.cj : R::kZero;
+    row_j = !edge_j ? (FWD ? ln.c - g.bx : ln.c + g.bx)
+                    : HALO ? R::kHalo + g.by + ln.ci : R::kZero;
+  }
+  // exchange with the neighbouring tiles: where this lane's column reads and
+  // writes at level l: base + l * stride
+  const int I = box % g.nbx, Jt = (box / g.nbx) % g.nby;
+  const int sx = 3 * ts * g.by, sy = 3 * ts * g.bx;
+  const int kx = HALO ? ((-ln.ci - ln.cj) * g.by + ln.cj) * 3 * ts + a * ts : 0;
+  const int ky = HALO ? ((-ln.ci - ln.cj) * g.bx + ln.ci) * 3 * ts + a * ts : 0;
+  const int szx = g.bz * sx, szy = g.bz * sy;
+  const bool from_x = HALO && ln.in_box && edge_i && (FWD ? I > 0 : I + 1 < g.nbx);
+  const bool from_y = HALO && ln.in_box && edge_j && (FWD ? Jt > 0 : Jt + 1 < g.nby);
+  const bool to_x = HALO && ln.in_box && (FWD ? ln.ci == g.bx - 1 && I + 1 < g.nbx
+                                              : ln.ci == 0 && I > 0);
+  const bool to_y = HALO && ln.in_box && (FWD ? ln.cj == g.by - 1 && Jt + 1 < g.nby
+                                              : ln.cj == 0 && Jt > 0);
+  // (a lane without such a value: past the end of the array at every level)
+  const int get_x = from_x ? kx : kOut, get_y = from_y ? ky : kOut;
+  const int put_x = to_x ? kx : kOut, put_y = to_y ? ky : kOut;
+  const T* srcx = HALO ? v.ex[FWD ? 0 : 1] + (size_t)(box + (FWD ? -1 : 1)) * (szx / ts) : nullptr;
+  const T* srcy = HALO ? v.ey[FWD ? 0 : 1] + (size_t)(box + (FWD ? -1 : 1) * g.nbx) * (szy / ts)
+                       : nullptr;
+  const __amdgpu_buffer_rsrc_t rsx = col_rsrc(srcx, HALO ? szx : 0), rsy = col_rsrc(srcy, HALO ? szy : 0);
+  const __amdgpu_buffer_rsrc_t rdx =
+      col_rsrc(HALO ? v.ex[FWD ? 0 : 1] + (size_t)box * (szx / ts) : nullptr, HALO ? szx : 0);
+  const __amdgpu_buffer_rsrc_t rdy =
+      col_rsrc(HALO ? v.ey[FWD ? 0 : 1] + (size_t)box * (szy / ts) : nullptr, HALO ? szy : 0);
+
+  auto level = [&](int s) {   // of step s (past the last one: the last one)
+    const int sc = min(s, L - 1);
+    return FWD ? sc : L - 1 - sc;
+  };
+  auto load_idx = [&](int s) { return col_load<int>(ridx, vidx, level(s) * C * 4); };
+  auto data = [&](int s, int ix, ColJob<T>& j, auto next_idx) __attribute__((always_inline)) {
+    const int l = level(s), so = l * rb;
+    // 8 or 12 values in whole chunks (backward: the ninth follows them)
+#pragma unroll
+    for (int c = 0; c < (FWD ? 12 : 8) / kV; ++c) {
+      const V w = __builtin_bit_cast(
+          V, __builtin_amdgcn_raw_buffer_load_b128(rrec, vrec, so + c * C * 48, 0));
+#pragma unroll
+      for (int e = 0; e < kV; ++e) {
+        if (c * kV + e < 9)
+          j.a[c * kV + e] = w[e];
+        else
+          j.d[c * kV + e - 9] = w[e];
+      }
+    }
+    if (!FWD) j.a[8] = col_load<T>(rrec, vlast, so + 8 * C * 3 * ts);
+    if (FWD) {
+      const int off = ix * 24 + vcell;
+      auto ld = [&](const double* base) { return col_load<double>(col_rsrc(base, vec_bytes), off); };
+      if (MODE == kry::kFuseNone) j.u[0] = ld(q.r);
+      if (MODE == kry::kFuseBegin) {
+        j.u[0] = ld(q.f.r);
+        j.u[1] = ld(q.f.p);
+        j.u[2] = ld(q.f.v);
+      }
+      if (MODE == kry::kFuseS) {
+        j.u[0] = ld(q.f.r);
+        j.u[1] = ld(q.f.v);
+      }
+    } else if (HALO) {
+      j.z = col_load<T>(rz, vz, l * C * 3 * ts);
+    }
+    if (HALO) {
+      j.hx = col_load<T, kCoherent>(rsx, get_x + l * sx);
+      j.hy = col_load<T, kCoherent>(rsy, get_y + l * sy);
+    }
+    next_idx();
+    // keep every load of the stage here, ahead of the computation of the
+    // current level, and the arithmetic on them after this point
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // HALO: the exchanged values of step s, re-read while they hold the marker
+  // (with those of the steps behind it, which the same wait makes ready too),
+  // then in LDS for the step
+  ColJob<T> jobs[ND];
+  bool lost = false;   // a wait of this wavefront gave up
+  auto in_range = [](int off, int size) { return (unsigned)off < (unsigned)size; };
+  auto receive = [&](int s, int slot, int par) __attribute__((always_inline)) {
+    if (!HALO) return;
+    const int l = level(s);
+    const int ox = get_x + l * sx, oy = get_y + l * sy;
+    const bool wait_x = in_range(ox, szx), wait_y = in_range(oy, szy);
+    T hx = jobs[slot].hx, hy = jobs[slot].hy;
+    bool miss = (wait_x && is_unset(hx)) || (wait_y && is_unset(hy));
+    if (v.spin == 0 && (wait_x || wait_y)) miss = true;
+    if (__builtin_amdgcn_ballot_w64(miss) != 0) {
+      for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
+        if (it >= v.spin || lost) {
+          lost = true;
+          if (miss) {
+            hx = (T)__builtin_nan("");
+            hy = (T)__builtin_nan("");
+          }
+          __hip_atomic_store(v.gave_up + (FWD ? 0 : 1), 1, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
+        if (miss) {
+          if (wait_x) hx = coherent_reread(srcx + ox / ts);
+          if (wait_y) hy = coherent_reread(srcy + oy / ts);
+          miss = (wait_x && is_unset(hx)) || (wait_y && is_unset(hy));
+        }
+        if ((it & 63) == 63 && __hip_atomic_load(v.gave_up + (FWD ? 0 : 1), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT) != 0)
+          lost = true;
+      }
+      // the steps behind it that are already loaded
+#pragma unroll
+      for (int u = 1; u < DEPTH; ++u) {
+        ColJob<T>& j = jobs[(slot + u) % ND];
+        const int lu = level(s + u);
+        const int px = get_x + lu * sx, py = get_y + lu * sy;
+        if (in_range(px, szx)) j.hx = coherent_reread(srcx + px / ts);
+        if (in_range(py, szy)) j.hy = coherent_reread(srcy + py / ts);
+      }
+    }
+    Lds<T>* h = nb + par * 4 * R::kRows + 4 * R::kHalo + ln.eq;
+    if (ln.in_box && edge_i) h[4 * ln.cj] = hx;
+    if (ln.in_box && edge_j) h[4 * (g.by + ln.ci)] = hy;
+  };
+
+  int idx[P];   // cell + 1, 0: none
+  // prologue: the data of steps 0 .. DEPTH-1, their indices and the ND after
+#pragma unroll
+  for (int s = 0; s < DEPTH + ND; ++s) idx[s] = load_idx(s);
+#pragma unroll
+  for (int s = 0; s < DEPTH; ++s) data(s, idx[s], jobs[s], []() {});
+  // with the first levels' loads in flight: the decisions that need the
+  // iteration's scalars (their loads overlap those of the sweep)
+  if (!gate(q)) return false;
+  T out = (T)0;
+  receive(0, 0, 0);
+  level_barrier<NT>();
+  // step s reads the rows of parity s % 2 and writes the others
+  auto step = [&](int s, int qq) __attribute__((always_inline)) {
+    const Lds<T>* rd = nb + (qq & 1) * 4 * R::kRows;
+    const Lds<T>* wi = rd + 4 * row_i;
+    const Lds<T>* wj = rd + 4 * row_j;
+    const T xi0 = wi[0], xi1 = wi[1], xi2 = wi[2];
+    const T xj0 = wj[0], xj1 = wj[1], xj2 = wj[2];
+    __builtin_amdgcn_sched_barrier(0);
+    data(s + DEPTH, idx[(qq + DEPTH) % P], jobs[(qq + DEPTH) % ND],
+         [&]() { idx[(qq + DEPTH + ND) % P] = load_idx(s + DEPTH + ND); });
+    const ColJob<T>& j = jobs[qq % ND];
+    const int ix = idx[qq];
+    const int l = level(s);
+    const T xk0 = quad_lane<0>(out), xk1 = quad_lane<1>(out), xk2 = quad_lane<2>(out);
+    // the same expressions as the unfused vector kernels of the iteration
+    double u = j.u[0];
+    if (FWD && MODE == kry::kFuseBegin) u = j.u[0] + q.beta * (j.u[1] - q.omega * j.u[2]);
+    if (FWD && MODE == kry::kFuseS) u = j.u[0] - q.alpha * j.u[1];
+    T o;
+    if (FWD) {
+      const T r = (T)u;
+      o = dot3(j.d[0], quad_lane<0>(r), j.d[1], quad_lane<1>(r), j.d[2], quad_lane<2>(r));
+      o = sub_dot3(o, j.a, xk0, xk1, xk2);
+      o = sub_dot3(o, j.a + 3, xj0, xj1, xj2);
+      o = sub_dot3(o, j.a + 6, xi0, xi1, xi2);
+    } else {
+      o = HALO ? j.z : zl[(l * C + min(ln.c, C - 1)) * 3 + a];
+      o = sub_dot3(o, j.a, xi0, xi1, xi2);
+      o = sub_dot3(o, j.a + 3, xj0, xj1, xj2);
+      o = sub_dot3(o, j.a + 6, xk0, xk1, xk2);
+    }
+    out = ix != 0 ? o : (T)0;
+    nb[((qq & 1) ^ 1) * 4 * R::kRows + 4 * ln.c + ln.eq] = out;
+    const int off = ix * 24 + vcell;
+    if (HALO) {
+      col_store<kCoherent>(out, rdx, put_x + l * sx);
+      col_store<kCoherent>(out, rdy, put_y + l * sy);
+      if (FWD) col_store(out, rz, vz, l * C * 3 * ts);
+    } else if (FWD && stored) {
+      zl[(l * C + ln.c) * 3 + a] = out;
+    }
+    if (!FWD) col_store((double)out, col_rsrc(x, vec_bytes), off);
+    if (FWD && MODE == kry::kFuseBegin) col_store(u, col_rsrc(q.f.p, vec_bytes), off);
+    if (FWD && MODE == kry::kFuseS) {
+      col_store(u, col_rsrc(q.f.s, vec_bytes), off);
+      ss += ix != 0 ? u * u : 0.0;
+    }
+    receive(s + 1, (qq + 1) % ND, (qq & 1) ^ 1);
+    level_barrier<NT>();
+  };
+  for (int s = 0;; s += P) {
+#pragma unroll
+    for (int qq = 0; qq < P; ++qq) {
+      step(s + qq, qq);
+      if (s + qq + 1 >= L) return true;
+    }
+  }
+}
+
+}  // namespace ilu
+}  // namespace opm

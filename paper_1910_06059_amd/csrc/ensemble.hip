@@ -253,11 +253,12 @@ __device__ int wg_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, doub
     if (cm <= o.tol_cnv && mm <= o.tol_mb) return OPM_OK;
     if (it >= o.max_newton) return OPM_ENOTCONV;
     // ILU(0)
-    for (int pos = tid; pos < n; pos += NT) ilu::pack_row<T>(tp, M.J, iv, pos);
     if (tid == 0) *flag = 0;
     __syncthreads();
     ilu::factor_levels_wg<T, FACWIN, NT, false>(tp, M.J, iv, flag, fwin);
     if (*flag != 0) return OPM_ESINGULAR;
+    for (int pos = tid; pos < n; pos += NT) ilu::pack_row<T>(tp, M.J, iv, pos);
+    __syncthreads();
     // BiCGStab: J d = R, Newton update y <- y - chop(d)
     int lits = 0;
     const int st = wg_bicgstab<T, NT>(M, tp, iv, M.R, M.d, o.lin_rtol, o.lin_maxit, red, swin,
@@ -638,11 +639,11 @@ __device__ int mw_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp&
     if (cm <= o.tol_cnv && mm <= o.tol_mb) return OPM_OK;
     if (it >= o.max_newton) return OPM_ENOTCONV;
     // block ILU(0) of the workgroup's subdomains
-    for_rows<NT>(tp, [&](int pos, int) { ilu::pack_row<T>(tp, M.J, iv, pos); });
     if (threadIdx.x == 0) *flag = 0;
     __syncthreads();
     ilu::factor_levels_wg<T, FACWIN, NT, false>(tp, M.J, iv, flag, fwin);
     __syncthreads();
+    for_rows<NT>(tp, [&](int pos, int) { ilu::pack_row<T>(tp, M.J, iv, pos); });
     double sing = *flag != 0 ? 1.0 : 0.0;
     if (!grp_reduce<NT, 1, 1u>(G, &sing, red, word)) return OPM_EHIP;
     if (sing != 0.0) return OPM_ESINGULAR;

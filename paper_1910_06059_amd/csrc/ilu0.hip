@@ -8,9 +8,13 @@
 //   D_i = A_ii - sum_{k<i, k in C(i)} A_ik D_k^{-1} A_ki .
 // Only D_i^{-1} has to be computed.  Rows are processed by dependency level
 // (all lower neighbours of a row sit on earlier levels), which gives the same
-// factors as the natural order.  The triangular solves of M = LU become
-//   forward:  y_i = D_i^{-1} (r_i - sum_{k<i} A_ik y_k)        (y = D^{-1} w)
-//   backward: x_i = y_i - D_i^{-1} sum_{j>i} A_ij x_j .
+// factors as the natural order.  The off-diagonal blocks are stored scaled by
+// their row's inverse pivot, so that the triangular solves of M = LU become
+//   forward:  z_i = D_i^{-1} r_i - sum_{k<i} (D_i^{-1} A_ik) z_k
+//   backward: x_i = z_i - sum_{j>i} (D_i^{-1} A_ij) x_j
+// with one block product between a neighbour's value and the row's own (the
+// product D_i^{-1} r_i does not wait for a neighbour), and no D^{-1} to read
+// in the backward sweep.
 //
 // Data layout: everything the sweeps read is in level order (position p of
 // the schedule, rows of one level contiguous) and structure-of-arrays
@@ -28,10 +32,19 @@
 //  - one launch per level over many workgroups (large systems).
 // Packing the off-diagonal blocks into level order does not depend on the
 // levels and runs as one wide kernel over all rows.
-#include "krylov_dev.h"
-#include "solver_dev.h"
+#include <algorithm>
+
+#include "cols_dev.h"
 
 namespace opm {
+
+bool cols_capable(const opm_problem* pb);
+int cols_boxes(const opm_problem* pb);
+size_t cols_bytes(const opm_problem* pb, int precision);
+int cols_factor(const opm_problem* pb, const double* J, void* ilu, int precision,
+                int32_t* status, hipStream_t s);
+int cols_apply(const opm_problem* pb, void* ilu, int precision, int mode, const double* r,
+               double* x, const int32_t* skip, const kry::Fused& f, hipStream_t s);
 
 extern int g_sweep_kernel;
 extern int g_block_depth;
@@ -120,7 +133,7 @@ __global__ __launch_bounds__(kWgThreads) void k_apply_ring(Topo t, IluView<T> v,
                                                             double* x, const int32_t* skip,
                                                             unsigned mask) {
   if (skip && *skip != 0) return;
-  extern __shared__ unsigned char smem[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   apply_levels_ring<T, kWgThreads>(t, v, r, x, reinterpret_cast<T*>(smem), mask);
 }
 
@@ -155,21 +168,6 @@ __global__ __launch_bounds__(kBlock) void k_pack_records(Topo t, IluView<T> v) {
   const int cell = t.perm[pos];
   v.idx_f[pos] = int4v{t.lo_pos[3 * p], t.lo_pos[3 * p + 1], t.lo_pos[3 * p + 2], cell};
   v.idx_b[pos] = int4v{t.up_pos[3 * p], t.up_pos[3 * p + 1], t.up_pos[3 * p + 2], cell};
-}
-
-// The end of a level: a workgroup barrier, or for a one-wavefront
-// workgroup a wavefront-scope fence (the wavefront's LDS operations are
-// performed in order, so the next level's reads see this level's writes
-// without waiting for them to complete).
-template <int NT>
-__device__ __forceinline__ void level_barrier() {
-  if (NT == 64) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
 }
 
 // ------------------------------------------------------------ block ILU0
@@ -353,8 +351,9 @@ __global__ __launch_bounds__(NT) void k_factor_blocks_pipe(Topo t, const double*
 }
 
 // Sweep records of the block ILU0, straight from the Jacobian (after the
-// pivot recursion).  Record (row, a) holds row a of the three off-diagonal
-// blocks (lower ones forward, upper ones backward) and row a of D^{-1}: 12
+// pivot recursion).  Record (row, a) holds row a of the three scaled
+// off-diagonal blocks D^{-1} A (lower ones forward, upper ones backward) and
+// row a of D^{-1} (read by the forward sweep only): 12
 // values as 16-byte chunks, chunk c of (position p, a) at [(c ns + p) 3 + a]
 // so that the three lanes of a row and consecutive rows read consecutive
 // chunks.  Index records: neighbours by slot in the subdomain, and the cell.
@@ -395,6 +394,9 @@ __global__ __launch_bounds__(256) void k_pack_block_records(Topo t, const int32_
       int loc[3];
 #pragma unroll
       for (int sl = 0; sl < 3; ++sl) loc[sl] = blk[sl] < 0 ? -1 : blk[sl] - rbase[g];
+      double d64[3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) d64[e] = v.dinv64[(size_t)(3 * a + e) * ns + up];
       V* rec = reinterpret_cast<V*>(fwd ? v.rec_f : v.rec_b);
 #pragma unroll
       for (unsigned c = 0; c < kC; ++c) {
@@ -405,7 +407,9 @@ __global__ __launch_bounds__(256) void k_pack_block_records(Topo t, const int32_
           T val;
           if (e < 9u) {
             const int sl = (int)e / 3, col = (int)e % 3;
-            val = loc[sl] < 0 ? (T)0 : (T)rows[g][9 * loc[sl] + 3 * a + col];
+            const double* B = rows[g] + 9 * max(loc[sl], 0) + col;
+            const double sv = dot3(d64[0], B[0], d64[1], B[3], d64[2], B[6]);
+            val = loc[sl] < 0 ? (T)0 : (T)sv;
           } else {
             val = v.dinv[(size_t)(3 * a + (int)e - 9) * ns + up];
           }
@@ -427,44 +431,21 @@ __global__ __launch_bounds__(256) void k_pack_block_records(Topo t, const int32_
 }
 
 // Block-ILU0 sweep rows are spread over a quad of lanes, lane a < 3 per
-// equation a: lane a holds row a of the three neighbour blocks and of
-// D^{-1} (12 values, the record of (row, a)), computes its partial sum
-//   acc_a = r_a - sum_s A_s[a][.] x_s   (forward; backward with + and 0),
-// takes acc_b of the two other lanes of the quad by DPP quad permutation
-// and finishes with D^{-1}[a][.] acc.  The arithmetic and its order per
+// equation a: lane a holds row a of the three scaled neighbour blocks and
+// (forward) of D^{-1}, the record of (row, a).  Forward it takes r_b of the
+// two other lanes of the quad by DPP quad permutation for D^{-1}[a][.] r,
+// which waits for no neighbour, and subtracts the three products
+// (D^{-1} A_s)[a][.] x_s in turn; backward it subtracts them from z_a.  The arithmetic and its order per
 // value are those of the other sweep kernels (bitwise equal results).  A
 // wavefront holds 16 rows (lanes 4q + a; lane 4q + 3 repeats lane 4q + 2's
 // work and stores nothing), the widest level of a 4x4 column.  Records,
 // right-hand sides and the index are read with buffer loads (one 32-bit
 // offset per level, chunk offsets in scalar registers).
 constexpr int kRowsPerWave = 16;
-// Word 3 of a raw buffer resource on gfx9 (32-bit data format, no swizzle).
-constexpr int kBufferWord3 = 0x00020000;
-// A value in LDS (address space 3: 32-bit addresses).
-template <typename T>
-using Lds = __attribute__((address_space(3))) T;
-
 __device__ __forceinline__ int block_lane_row() {
   return (int)(threadIdx.x >> 6) * kRowsPerWave + (int)(threadIdx.x & 63u) / 4;
 }
 __device__ __forceinline__ int block_lane_eq() { return (int)(threadIdx.x & 3u); }
-
-// Value of lane K of the lane's quad (DPP quad permutation: a VALU move, no
-// LDS round trip).
-template <int K>
-__device__ __forceinline__ double quad_lane(double x) {
-  constexpr int ctrl = K | (K << 2) | (K << 4) | (K << 6);
-  const long long b = __builtin_bit_cast(long long, x);
-  const int lo = __builtin_amdgcn_mov_dpp((int)b, ctrl, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xf, 0xf, false);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-template <int K>
-__device__ __forceinline__ float quad_lane(float x) {
-  constexpr int ctrl = K | (K << 2) | (K << 4) | (K << 6);
-  return __builtin_bit_cast(
-      float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), ctrl, 0xf, 0xf, false));
-}
 
 template <typename T>
 struct BlockJob {
@@ -476,15 +457,6 @@ struct BlockJob {
   int cell;
   int slot;
   bool live;
-};
-
-// Forward right-hand side of a sweep: r itself, or (fused with BiCGStab)
-// p = r + beta (p - omega v) or s = r - alpha v, written back for the rows
-// of the level.
-struct BlockRhs {
-  const double* r;
-  kry::Fused f;
-  double beta, omega, alpha;
 };
 
 // A sweep of one subdomain is a three-stage pipeline over its levels: the
@@ -545,7 +517,8 @@ __device__ __forceinline__ void block_data(IluView<T> v, const BlockRhs& q, cons
                                            int base, int zslot, const BlockStage& st,
                                            BlockJob<T>& j) {
   typedef typename Vec16<T>::type V;
-  constexpr unsigned kV = 16 / sizeof(T), kC = 12 / kV;
+  // the backward sweep leaves out the chunks that hold only D^{-1}
+  constexpr unsigned kV = 16 / sizeof(T), kC = 12 / kV, kCB = (9 + kV - 1) / kV;
   const int eq = block_lane_eq();
   const unsigned a = (unsigned)min(eq, 2);
   j.live = st.in && st.p0 + row < st.p1 && eq < 3;
@@ -563,7 +536,7 @@ __device__ __forceinline__ void block_data(IluView<T> v, const BlockRhs& q, cons
       (void*)(FWD ? v.rec_f : v.rec_b), (short)0, (int)(kC * ns * 48u), kBufferWord3);
   const int voff = (int)((up * 3u + a) * 16u);
 #pragma unroll
-  for (unsigned c = 0; c < kC; ++c) {
+  for (unsigned c = 0; c < (FWD ? kC : kCB); ++c) {
     const V w = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(
                                           rs, voff, (int)(c * ns * 48u), 0));
 #pragma unroll
@@ -571,7 +544,7 @@ __device__ __forceinline__ void block_data(IluView<T> v, const BlockRhs& q, cons
       const unsigned e = c * kV + qq;
       if (e < 9u)
         j.a[e] = w[qq];
-      else
+      else if (FWD)
         j.d[e - 9u] = w[qq];
     }
   }
@@ -633,16 +606,12 @@ __device__ __forceinline__ void block_row(const BlockJob<T>& j, const T* xv, Lds
   if (FWD && MODE == kry::kFuseBegin) u = j.u[0] + q.beta * (j.u[1] - q.omega * j.u[2]);
   if (FWD && MODE == kry::kFuseS) u = j.u[0] - q.alpha * j.u[1];
   const T rhs = FWD ? (T)u : j.rhs;
-  T acc = FWD ? rhs : (T)0;
+  T out = FWD ? dot3(j.d[0], quad_lane<0>(rhs), j.d[1], quad_lane<1>(rhs), j.d[2],
+                     quad_lane<2>(rhs))
+              : rhs;
 #pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const T t = j.a[3 * s] * xv[3 * s] + j.a[3 * s + 1] * xv[3 * s + 1] +
-                j.a[3 * s + 2] * xv[3 * s + 2];
-    acc = FWD ? acc - t : acc + t;
-  }
-  const T acc0 = quad_lane<0>(acc), acc1 = quad_lane<1>(acc), acc2 = quad_lane<2>(acc);
-  const T d = j.d[0] * acc0 + j.d[1] * acc1 + j.d[2] * acc2;
-  const T out = FWD ? d : j.rhs - d;
+  for (int s = 0; s < 3; ++s)
+    out = sub_dot3(out, j.a + 3 * s, xv[3 * s], xv[3 * s + 1], xv[3 * s + 2]);
   if (!j.live) return;
   zl[__umul24((unsigned)j.slot, 3u) + a] = out;
   if (!FWD) x[3u * (unsigned)j.cell + a] = (double)out;
@@ -774,7 +743,7 @@ __global__ __launch_bounds__(NT) void k_apply_blocks(IluView<T> v, const int32_t
   typedef const __attribute__((address_space(1))) int32_t GlobalWord;
   const int skipv = MODE == kry::kFuseNone ? *(GlobalWord*)(skip ? skip : &kZeroWord) : 0;
   const int st0 = MODE != kry::kFuseNone ? f.sc->state : 0;
-  extern __shared__ unsigned char smem[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // [max_sub + 1][3], the last row zero; an LDS-qualified pointer keeps the
   // address arithmetic in 32 bits
   Lds<T>* zl = (Lds<T>*)reinterpret_cast<T*>(smem);
@@ -836,7 +805,7 @@ template <typename T, int NT, bool WIDE, bool SKIP>
 __global__ __launch_bounds__(NT) void k_apply_ring2(Topo t, IluView<T> v, double* x,
                                                      const int32_t* skip, unsigned mask) {
   if (skip && *skip != 0) return;
-  extern __shared__ unsigned char smem[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   T* ring = reinterpret_cast<T*>(smem);
   ilu::ring2_sweep<T, NT, true, WIDE, SKIP>(t, v, x, ring, mask);
   // each lane reads back in the backward sweep only z values that it wrote
@@ -849,7 +818,7 @@ template <typename T>
 __global__ __launch_bounds__(kWgThreads) void k_apply_wg(Topo t, IluView<T> v, const double* r,
                                                           double* x, const int32_t* skip) {
   if (skip && *skip != 0) return;
-  extern __shared__ unsigned char smem[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   apply_levels_wg<T, kWgThreads>(t, v, r, x, reinterpret_cast<T*>(smem));
 }
 
@@ -981,19 +950,6 @@ __global__ __launch_bounds__(256) void k_plane_fill(Topo t, const int32_t* cell_
   atomicMax(e + 1, pos + 1);
 }
 
-// the marker of a value not yet written (signalling NaNs: arithmetic
-// returns quiet ones)
-__device__ __forceinline__ void unset_value(double& v) {
-  v = __builtin_bit_cast(double, 0x7FF4A5A5A5A5A5A5ull);
-}
-__device__ __forceinline__ void unset_value(float& v) { v = __builtin_bit_cast(float, 0x7FA5A5A5u); }
-__device__ __forceinline__ bool is_unset(double v) {
-  return __builtin_bit_cast(unsigned long long, v) == 0x7FF4A5A5A5A5A5A5ull;
-}
-__device__ __forceinline__ bool is_unset(float v) {
-  return __builtin_bit_cast(unsigned, v) == 0x7FA5A5A5u;
-}
-
 // Before a pair of sweeps: both exchange vectors hold the marker, no abort.
 template <typename T>
 __global__ __launch_bounds__(256) void k_plane_reset(IluView<T> v, PlaneTab p,
@@ -1028,21 +984,6 @@ __device__ __forceinline__ void coherent_store(float* p, float x) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The re-read of a value found not yet written (the slow path): the load and
-// its wait in one block, so that the compiler counts no load of this loop
-// among those in flight (a counted load here would make it wait for every
-// prefetch issued since, at the next use of any of them).
-__device__ __forceinline__ double coherent_reread(const double* p) {
-  unsigned long long b;
-  asm volatile("global_load_dwordx2 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
-  return __builtin_bit_cast(double, b);
-}
-__device__ __forceinline__ float coherent_reread(const float* p) {
-  unsigned b;
-  asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
-  return __builtin_bit_cast(float, b);
-}
-
 // A row of a plane step: its sweep data, and the value of its off-plane
 // neighbour (loaded with the data; re-read at use while it holds the marker).
 template <typename T>
@@ -1066,7 +1007,7 @@ __global__ __launch_bounds__(kPlaneThreads) void k_sweep_planes(Topo t, IluView<
                                                                 const double* r, double* x,
                                                                 const int32_t* skip) {
   if (skip && *skip != 0) return;
-  extern __shared__ unsigned char smem_planes[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_planes[];
   T* ring = reinterpret_cast<T*>(smem_planes);                      // [2][W][3]
   int2v* rl = reinterpret_cast<int2v*>(ring + 2 * 3 * (size_t)p.W);   // [D] the plane's rows per step
   // fail[s % 3]: a lane of step s gave up.  Read by every wave after the
@@ -1212,9 +1153,11 @@ __global__ __launch_bounds__(kPlaneThreads) void k_sweep_planes(Topo t, IluView<
   // then the results to the ring and the exchange vector.
   auto solve = [&](const PlaneJob<T>& J, const T* xo, const int2v& rg, int s) {
     const SweepJob<T>& j = J.j;
-    T acc[3];
+    T out[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) acc[c] = FWD ? j.rhs[c] : (T)0;
+    for (int a = 0; a < 3; ++a)
+      out[a] = FWD ? dot3(j.D[3 * a], j.rhs[0], j.D[3 * a + 1], j.rhs[1], j.D[3 * a + 2], j.rhs[2])
+                   : j.rhs[a];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int kp = j.kp[q];
@@ -1225,17 +1168,8 @@ __global__ __launch_bounds__(kPlaneThreads) void k_sweep_planes(Topo t, IluView<
 #pragma unroll
       for (int c = 0; c < 3; ++c) xv[c] = kp < 0 ? (T)0 : in_ring ? w[c] : xo[c];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const T t = j.a[9 * q + 3 * a] * xv[0] + j.a[9 * q + 3 * a + 1] * xv[1] +
-                    j.a[9 * q + 3 * a + 2] * xv[2];
-        acc[a] = FWD ? acc[a] - t : acc[a] + t;
-      }
-    }
-    T out[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const T d = j.D[3 * a] * acc[0] + j.D[3 * a + 1] * acc[1] + j.D[3 * a + 2] * acc[2];
-      out[a] = FWD ? d : j.rhs[a] - d;
+      for (int a = 0; a < 3; ++a)
+        out[a] = sub_dot3(out[a], j.a + 9 * q + 3 * a, xv[0], xv[1], xv[2]);
     }
     if (J.have) {
       const unsigned pos = (unsigned)J.pos;
@@ -1301,7 +1235,7 @@ template <typename T>
 __global__ __launch_bounds__(kPlaneThreads) void k_factor_planes(Topo t, const double* J,
                                                                  IluView<T> v, PlaneTab p,
                                                                  int32_t* status) {
-  extern __shared__ unsigned char smem_fplanes[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_fplanes[];
   double* ring = reinterpret_cast<double*>(smem_fplanes);               // [2][W][9]
   int2v* rl = reinterpret_cast<int2v*>(ring + 2 * 9 * (size_t)p.W);   // [D]
   __shared__ int fail[3];
@@ -1410,8 +1344,11 @@ int factor_impl(const opm_problem* pb, const double* J, void* ilu, int32_t* stat
     OPM_TRY_HIP(hipGetLastError());
     return OPM_OK;
   }
-  hipLaunchKernelGGL(k_pack<T>, dim3(blocks_for(pb->n_cells, kBlock)), dim3(kBlock), 0, s, t, J,
-                     v);
+  // the scaled off-diagonal blocks (after the pivots)
+  auto pack = [&]() {
+    hipLaunchKernelGGL(k_pack<T>, dim3(blocks_for(pb->n_cells, kBlock)), dim3(kBlock), 0, s, t, J,
+                       v);
+  };
   if (mode == 0) {
     if (pb->max_level <= kMaxFactorWindowRows) {
       OPM_TRY(allow_lds(k_factor_wg<T, true>, sizeof(T) == 8 ? 0 : 1));
@@ -1421,6 +1358,7 @@ int factor_impl(const opm_problem* pb, const double* J, void* ilu, int32_t* stat
       hipLaunchKernelGGL((k_factor_wg<T, false>), dim3(1), dim3(kFacThreads), 0, s, t, J, v,
                          status);
     }
+    pack();
     // the record sweep's copy of the factors (whenever a ring sweep can run)
     if (sizeof(T) * 3 * (size_t)ring_rows(pb->sweep_span, pb->max_level) <= kMaxRingBytes)
       hipLaunchKernelGGL(k_pack_records<T>, dim3(blocks_for(pb->n_cells, kBlock)), dim3(kBlock),
@@ -1450,6 +1388,7 @@ int factor_impl(const opm_problem* pb, const double* J, void* ilu, int32_t* stat
                          s, t, J, v, p0, p1, status);
     }
   }
+  pack();
   if (plane_capable(pb))   // the row records of the sweeps
     hipLaunchKernelGGL(k_pack_records<T>, dim3(blocks_for(pb->n_cells, kBlock)), dim3(kBlock), 0,
                        s, t, v);
@@ -1591,7 +1530,7 @@ size_t ilu_bytes(const opm_problem* pb, int precision) {
   const size_t v = precision == OPM_PREC_MIXED ? view_bytes<float>(pb->n_cells)
                                                : view_bytes<double>(pb->n_cells);
   const size_t pl = plane_bytes(pb);
-  return pl ? al256(v) + pl : v;
+  return std::max(pl ? al256(v) + pl : v, cols_bytes(pb, precision));
 }
 
 // Sweeps of mode 1 on a lattice: 1 plane-pipelined (default), 0 one launch
@@ -1611,10 +1550,14 @@ int g_sweep_kernel = 0;
 // levels whose data the block-ILU0 sweeps keep in flight: 0 automatic, 1, 2
 int g_block_depth = 0;
 
-// A block-ILU0 topology runs one workgroup per subdomain whenever the
+// A lattice is factored and swept by columns (mode 3: a workgroup per
+// subdomain, or per tile of the whole system) unless an option asks for
+// another shape or its boxes do not suit (cols.hip).  Otherwise a block-ILU0
+// topology runs one workgroup per subdomain whenever the
 // subdomain's vector fits in LDS; modes 0 and 1 also serve it (same
 // factors and sweeps, level by level over the whole system).
 int sweep_mode(const opm_problem* pb, int precision) {
+  if (g_sweep_mode == -1 && cols_capable(pb)) return 3;
   if (g_sweep_mode == 0 || g_sweep_mode == 1) {
     if (g_sweep_mode == 0 && pb->max_level > kMaxWindowRows) return 1;
     return g_sweep_mode;
@@ -1630,14 +1573,24 @@ int sweep_mode(const opm_problem* pb, int precision) {
 int ilu_factor(const opm_problem* pb, const double* J, void* ilu, int precision, int32_t* status,
                hipStream_t s) {
   const int mode = sweep_mode(pb, precision);
+  if (mode == 3) return cols_factor(pb, J, ilu, precision, status, s);
   if (precision == OPM_PREC_MIXED) return factor_impl<float>(pb, J, ilu, status, mode, s);
   return factor_impl<double>(pb, J, ilu, status, mode, s);
 }
 
+// Workgroups of a fused solve (its partial sums of <s, s>); 0: not fused.
+int ilu_fused_groups(const opm_problem* pb, int precision) {
+  const int mode = sweep_mode(pb, precision);
+  const int g = mode == 3 ? cols_boxes(pb) : mode == 2 ? pb->n_sub : 0;
+  return g <= kry::kMaxGrid ? g : 0;
+}
+
 // Block-ILU0 solve whose forward right-hand side is a BiCGStab vector
-// update (mode: kry::kFuseBegin or kry::kFuseS); only for sweep mode 2.
+// update (mode: kry::kFuseBegin or kry::kFuseS); only for sweep modes 2 and 3.
 int ilu_apply_fused(const opm_problem* pb, void* ilu, int precision, int mode,
                     const kry::Fused& f, double* x, hipStream_t s) {
+  if (sweep_mode(pb, precision) == 3)
+    return cols_apply(pb, ilu, precision, mode, nullptr, x, nullptr, f, s);
   if (precision == OPM_PREC_MIXED) {
     IluView<float> v = view<float>(pb, ilu);
     return mode == kry::kFuseBegin
@@ -1654,6 +1607,8 @@ int ilu_apply_fused(const opm_problem* pb, void* ilu, int precision, int mode,
 int ilu_apply(const opm_problem* pb, void* ilu, int precision, const double* r, double* x,
               hipStream_t s, const int32_t* skip) {
   const int mode = sweep_mode(pb, precision);
+  if (mode == 3)
+    return cols_apply(pb, ilu, precision, kry::kFuseNone, r, x, skip, kry::Fused{}, s);
   if (precision == OPM_PREC_MIXED) return apply_impl<float>(pb, ilu, r, x, mode, s, skip);
   return apply_impl<double>(pb, ilu, r, x, mode, s, skip);
 }

@@ -26,6 +26,7 @@ int ilu_apply(const opm_problem* pb, void* ilu, int precision, const double* r, 
 int ilu_apply_fused(const opm_problem* pb, void* ilu, int precision, int mode,
                     const kry::Fused& f, double* x, hipStream_t s);
 int sweep_mode(const opm_problem* pb, int precision = OPM_PREC_FP64);
+int ilu_fused_groups(const opm_problem* pb, int precision);
 
 namespace {
 
@@ -332,7 +333,7 @@ extern int g_block_depth;
 int chunk_size(const opm_problem* pb) {
   if (g_krylov_chunk > 0) return g_krylov_chunk;
   const int mode = sweep_mode(pb);
-  return mode == 1 ? 3 : mode == 2 ? 8 : 6;
+  return mode == 1 ? 3 : mode >= 2 ? 8 : 6;
 }
 
 size_t krylov_bytes(const opm_problem* pb) {
@@ -469,9 +470,10 @@ int bicgstab(const opm_problem* pb, const double* J, void* ilu, int precision, c
   hipLaunchKernelGGL(k_init2, dim3(1), dim3(kBlock), 0, st, w, G, rtol, maxit);
   OPM_TRY_HIP(hipGetLastError());
   const int chunk = chunk_size(pb);
-  // block ILU0 with one workgroup per subdomain: the p and s updates (and
-  // the tests before them) run inside the preconditioner sweeps
-  const bool fused = sweep_mode(pb, precision) == 2 && pb->n_sub <= kMaxGrid && !cpr;
+  // sweeps with one workgroup per subdomain or tile: the p and s updates (and
+  // the tests before them) run inside them
+  const int groups = cpr ? 0 : ilu_fused_groups(pb, precision);
+  const bool fused = groups > 0;
   kry::Fused fb{w.r, w.p, w.v, nullptr, w.part_rr, w.part_rhr, G, nullptr, w.sc};
   kry::Fused fs{w.r, nullptr, w.v, w.s, w.part_rv, nullptr, Gr, w.part_ss, w.sc};
   Scalars host;
@@ -493,7 +495,7 @@ int bicgstab(const opm_problem* pb, const double* J, void* ilu, int precision, c
                          pb->col_idx, J, w, wc);
   };
   auto spmv_t = [&](hipStream_t st, bool check) {
-    const int nss = check ? pb->n_sub : 0;
+    const int nss = check ? groups : 0;
     if (wide && check)
       hipLaunchKernelGGL((k_spmv_t<true, 2 * kBlock>), dim3(Gr), dim3(2 * kBlock), 0, st, n,
                          pb->row_ptr, pb->col_idx, J, w, nss, wc);

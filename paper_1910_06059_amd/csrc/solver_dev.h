@@ -34,8 +34,8 @@ struct IluView {
   int ns;          // SoA stride (n padded to 64)
   double* dinv64;  // [9][ns] FP64 inverse pivots (factor recursion)
   T* dinv;         // [9][ns] sweep copy (aliases dinv64 for FP64)
-  T* lov;          // [27][ns] A_ik of the lower neighbours, slot-major
-  T* upv;          // [27][ns] A_ij of the upper neighbours
+  T* lov;          // [27][ns] D_i^{-1} A_ik of the lower neighbours, slot-major
+  T* upv;          // [27][ns] D_i^{-1} A_ij of the upper neighbours
   T* z;            // [3][ns] level-ordered sweep scratch
   T* rec_f;        // forward sweep records (lower blocks, D^{-1})
   T* rec_b;        // backward sweep records (upper blocks, D^{-1})
@@ -114,24 +114,49 @@ __host__ __device__ inline int lvl_end(const Topo& t, int l) {
   return t.level_ptr[l * t.lstride + t.s1];
 }
 
+// Fixed-order 3-term products.  Every kernel of the factorisation and of the
+// sweeps forms its values through these, with the fused operations spelled
+// out and no contraction left to the compiler, so that all launch shapes
+// give the same bits.
+template <typename T>
+__device__ __forceinline__ T dot3(T a0, T b0, T a1, T b1, T a2, T b2) {
+#pragma clang fp contract(off)
+  T t = a0 * b0;
+  t = __builtin_elementwise_fma(a1, b1, t);
+  return __builtin_elementwise_fma(a2, b2, t);
+}
+// acc - a . x
+template <typename T>
+__device__ __forceinline__ T sub_dot3(T acc, const T* a, T x0, T x1, T x2) {
+#pragma clang fp contract(off)
+  const T t = dot3(a[0], x0, a[1], x1, a[2], x2);
+  return acc - t;
+}
+
 // Inverse of a 3x3 block by cofactors; false on a zero or non-finite
 // determinant.
 __device__ __forceinline__ bool inverse3(const double* a, double* inv) {
-  const double c0 = a[4] * a[8] - a[5] * a[7];
-  const double c1 = a[5] * a[6] - a[3] * a[8];
-  const double c2 = a[3] * a[7] - a[4] * a[6];
-  const double det = a[0] * c0 + a[1] * c1 + a[2] * c2;
+#pragma clang fp contract(off)
+  auto minor = [](double p, double q, double u, double w) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+    const double t = u * w;
+    return __builtin_elementwise_fma(p, q, -t);   // p q - u w
+  };
+  const double c0 = minor(a[4], a[8], a[5], a[7]);
+  const double c1 = minor(a[5], a[6], a[3], a[8]);
+  const double c2 = minor(a[3], a[7], a[4], a[6]);
+  const double det = dot3(a[0], c0, a[1], c1, a[2], c2);
   if (det == 0.0 || !isfinite(det)) return false;
   const double r = 1.0 / det;
   inv[0] = c0 * r;
-  inv[1] = (a[2] * a[7] - a[1] * a[8]) * r;
-  inv[2] = (a[1] * a[5] - a[2] * a[4]) * r;
+  inv[1] = minor(a[2], a[7], a[1], a[8]) * r;
+  inv[2] = minor(a[1], a[5], a[2], a[4]) * r;
   inv[3] = c1 * r;
-  inv[4] = (a[0] * a[8] - a[2] * a[6]) * r;
-  inv[5] = (a[2] * a[3] - a[0] * a[5]) * r;
+  inv[4] = minor(a[0], a[8], a[2], a[6]) * r;
+  inv[5] = minor(a[2], a[3], a[0], a[5]) * r;
   inv[6] = c2 * r;
-  inv[7] = (a[1] * a[6] - a[0] * a[7]) * r;
-  inv[8] = (a[0] * a[4] - a[1] * a[3]) * r;
+  inv[7] = minor(a[1], a[6], a[0], a[7]) * r;
+  inv[8] = minor(a[0], a[4], a[1], a[3]) * r;
   return true;
 }
 
@@ -140,18 +165,24 @@ __device__ __forceinline__ void mat3_mul(const double* A, const double* B, doubl
   for (int r = 0; r < 3; ++r)
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      C[3 * r + c] = A[3 * r] * B[c] + A[3 * r + 1] * B[3 + c] + A[3 * r + 2] * B[6 + c];
+      C[3 * r + c] = dot3(A[3 * r], B[c], A[3 * r + 1], B[3 + c], A[3 * r + 2], B[6 + c]);
 }
 
-// Level-ordered SoA copy of the off-diagonal blocks of one row position.
+// Level-ordered SoA copy of one row position's off-diagonal blocks scaled by
+// its inverse pivot, D_i^{-1} A_ij (after the pivot recursion; the products
+// in FP64, rounded once where the sweeps are FP32).
 template <typename T>
 __device__ __forceinline__ void pack_row(const Topo& t, const double* J, IluView<T> v, int pos) {
+  double D[9];
+#pragma unroll
+  for (int e = 0; e < 9; ++e) D[e] = v.dinv64[(size_t)e * v.ns + pos];
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     const int bl = t.lo_blk[3 * pos + s];
     const int bu = t.up_blk[3 * pos + s];
-    const double* Al = J + 9 * (size_t)(bl < 0 ? 0 : bl);
-    const double* Au = J + 9 * (size_t)(bu < 0 ? 0 : bu);
+    double Al[9], Au[9];
+    mat3_mul(D, J + 9 * (size_t)(bl < 0 ? 0 : bl), Al);
+    mat3_mul(D, J + 9 * (size_t)(bu < 0 ? 0 : bu), Au);
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
       v.lov[(size_t)(9 * s + e) * v.ns + pos] = bl < 0 ? (T)0 : (T)Al[e];
@@ -187,7 +218,7 @@ __device__ __forceinline__ void load_fac(const Topo& t, const double* J, int pos
   }
 }
 
-// D = A_ii - sum_k A_ik D_k^{-1} A_ki, then D^{-1}; `dk` fetches D_k^{-1}.
+// D = A_ii - sum_k A_ik (D_k^{-1} A_ki), then D^{-1}; `dk` fetches D_k^{-1}.
 template <typename T, typename DkFn>
 __device__ __forceinline__ void finish_fac(const FacJob& j, int pos, IluView<T> v, DkFn dk,
                                            int32_t* status, double* inv) {
@@ -199,8 +230,8 @@ __device__ __forceinline__ void finish_fac(const FacJob& j, int pos, IluView<T> 
     if (j.kp[s] < 0) continue;
     double Dk[9], tmp[9], upd[9];
     dk(j.kp[s], Dk);
-    mat3_mul(j.Aik[s], Dk, tmp);   // L_ik = A_ik D_k^{-1}
-    mat3_mul(tmp, j.Aki[s], upd);
+    mat3_mul(Dk, j.Aki[s], tmp);   // row k's scaled upper block
+    mat3_mul(j.Aik[s], tmp, upd);
 #pragma unroll
     for (int e = 0; e < 9; ++e) D[e] -= upd[e];
   }
@@ -303,32 +334,23 @@ __device__ __forceinline__ void load_bwd(const Topo& t, IluView<T> v, int pos, S
   for (unsigned s = 0; s < 3; ++s) j.kp[s] = t.up_pos[3u * up + s];
 #pragma unroll
   for (unsigned e = 0; e < 27; ++e) j.a[e] = v.upv[e * ns + up];
-#pragma unroll
-  for (unsigned e = 0; e < 9; ++e) j.D[e] = v.dinv[e * ns + up];
 }
 
-// forward: y = D^{-1} (r - sum_s A_s y_{k_s});  backward: x = y - D^{-1} sum_s A_s x_{k_s}
+// forward: z = D^{-1} r - sum_s (D^{-1} A_s) z_{k_s};  backward: x = z - sum_s (D^{-1} A_s) x_{k_s}
 template <typename T, bool FWD, typename NbrFn>
 __device__ __forceinline__ void solve_row(const SweepJob<T>& j, NbrFn nbr, T* out) {
-  T acc[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) acc[c] = FWD ? j.rhs[c] : (T)0;
+  for (int a = 0; a < 3; ++a)
+    out[a] = FWD ? dot3(j.D[3 * a], j.rhs[0], j.D[3 * a + 1], j.rhs[1], j.D[3 * a + 2], j.rhs[2])
+                 : j.rhs[a];
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     if (j.kp[s] < 0) continue;
     T xv[3];
     nbr(j.kp[s], xv);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const T t = j.a[9 * s + 3 * a] * xv[0] + j.a[9 * s + 3 * a + 1] * xv[1] +
-                  j.a[9 * s + 3 * a + 2] * xv[2];
-      acc[a] = FWD ? acc[a] - t : acc[a] + t;
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const T d = j.D[3 * a] * acc[0] + j.D[3 * a + 1] * acc[1] + j.D[3 * a + 2] * acc[2];
-    out[a] = FWD ? d : j.rhs[a] - d;
+    for (int a = 0; a < 3; ++a)
+      out[a] = sub_dot3(out[a], j.a + 9 * s + 3 * a, xv[0], xv[1], xv[2]);
   }
 }
 
@@ -466,185 +488,6 @@ __device__ __forceinline__ void spmv_row(const int32_t* row_ptr, const int32_t* 
   y3[0] = a0;
   y3[1] = a1;
   y3[2] = a2;
-}
-
-}  // namespace ilu
-}  // namespace opm
-
-namespace opm {
-namespace ilu {
-
-// ---------------------------------------------------------------------------
-// Quad sweep: x = (LU)^{-1} r by one workgroup of NT threads where four lanes
-// share one row (NT/4 rows per pass).  Lane q < 3 owns equation q of the row:
-// it holds row q of each neighbour block and of D^{-1} (13 values), so a
-// row's data is spread over three lanes and each lane can keep the data of
-// the next three levels in registers: the loads for level l+3 are issued
-// while level l is computed, which hides the memory latency of one level
-// behind three levels of work.  The three partial results of a row are
-// exchanged inside the quad.  Lane 3 of a quad only takes part in the
-// exchange.
-template <typename T>
-struct QuadJob {
-  T a[9];     // row q of the three neighbour blocks: a[3*s + c]
-  T d[3];     // row q of D^{-1}
-  T rhs;      // r_q (forward) or y_q (backward)
-  int kp[3];  // neighbour positions
-  int cell;
-};
-
-template <typename T, bool FWD>
-__device__ __forceinline__ void quad_load(const Topo& t, IluView<T> v, const double* r, int pos,
-                                          int q, QuadJob<T>& j) {
-  // 32-bit element offsets keep the addresses as (uniform base, lane offset)
-  const unsigned qq = q < 3 ? (unsigned)q : 0u;
-  const unsigned ns = (unsigned)v.ns, up = (unsigned)pos;
-  j.cell = t.perm[up];
-  const T* blk = FWD ? v.lov : v.upv;
-  const int32_t* kp = FWD ? t.lo_pos : t.up_pos;
-#pragma unroll
-  for (unsigned s = 0; s < 3; ++s) {
-    j.kp[s] = kp[3u * up + s];
-#pragma unroll
-    for (unsigned c = 0; c < 3; ++c) j.a[3 * s + c] = blk[(9u * s + 3u * qq + c) * ns + up];
-  }
-#pragma unroll
-  for (unsigned c = 0; c < 3; ++c) j.d[c] = v.dinv[(3u * qq + c) * ns + up];
-  j.rhs = FWD ? (T)r[3u * (unsigned)j.cell + qq] : v.z[qq * ns + up];
-}
-
-// One row by its quad: neighbour values come from the LDS window (previous
-// level) or from z; returns this lane's component.  The arithmetic is that of
-// solve_row, term by term, so both launch shapes give bitwise equal results.
-template <typename T, bool FWD>
-__device__ __forceinline__ T quad_row(const QuadJob<T>& j, IluView<T> v, const T* win_prev,
-                                      int prev0, int prev1) {
-  T acc = FWD ? j.rhs : (T)0;
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int kp = j.kp[s];
-    if (kp < 0) continue;
-    T xv[3];
-    if (kp >= prev0 && kp < prev1) {
-      const T* w = win_prev + (unsigned)(kp - prev0) * 3u;
-      xv[0] = w[0];
-      xv[1] = w[1];
-      xv[2] = w[2];
-    } else {
-#pragma unroll
-      for (unsigned c = 0; c < 3; ++c) xv[c] = v.z[c * (unsigned)v.ns + (unsigned)kp];
-    }
-    const T t = j.a[3 * s] * xv[0] + j.a[3 * s + 1] * xv[1] + j.a[3 * s + 2] * xv[2];
-    acc = FWD ? acc - t : acc + t;
-  }
-  // exchange the three components of the row inside the quad
-  const int base = (threadIdx.x & (kWave - 1)) & ~3;
-  const T t0 = __shfl(acc, base + 0, kWave);
-  const T t1 = __shfl(acc, base + 1, kWave);
-  const T t2 = __shfl(acc, base + 2, kWave);
-  const T d = j.d[0] * t0 + j.d[1] * t1 + j.d[2] * t2;
-  return FWD ? d : j.rhs - d;
-}
-
-template <typename T, bool FWD>
-__device__ __forceinline__ void quad_store(IluView<T> v, double* x, T* wcur, int p0, int pos,
-                                           int q, int cell, T val) {
-  if (q < 3) {
-    wcur[(unsigned)(pos - p0) * 3u + (unsigned)q] = val;
-    v.z[(unsigned)q * (unsigned)v.ns + (unsigned)pos] = val;
-    if (!FWD) x[3u * (unsigned)cell + (unsigned)q] = (double)val;
-  }
-}
-
-template <typename T, int NT, bool FWD>
-__device__ __forceinline__ void quad_level(const Topo& t, IluView<T> v, const double* r, double* x,
-                                           T* win, int L, int l, int& prev0, int& prev1, int& buf,
-                                           const QuadJob<T>& first) {
-  const int p0 = t.level_ptr[l], p1 = t.level_ptr[l + 1];
-  const int q = threadIdx.x & 3, row0 = threadIdx.x >> 2;
-  const T* wprev = win + (size_t)((buf ^ 1) * L) * 3;
-  T* wcur = win + (size_t)(buf * L) * 3;
-  if (p0 + row0 < p1) {   // first pass: data loaded levels ago
-    const T val = quad_row<T, FWD>(first, v, wprev, prev0, prev1);
-    quad_store<T, FWD>(v, x, wcur, p0, p0 + row0, q, first.cell, val);
-  }
-  for (int pos = p0 + row0 + NT / 4; pos < p1; pos += NT / 4) {   // wide levels
-    QuadJob<T> j;
-    quad_load<T, FWD>(t, v, r, pos, q, j);
-    const T val = quad_row<T, FWD>(j, v, wprev, prev0, prev1);
-    quad_store<T, FWD>(v, x, wcur, p0, pos, q, j.cell, val);
-  }
-  __syncthreads();
-  prev0 = p0;
-  prev1 = p1;
-  buf ^= 1;
-}
-
-// level index of the k-th step of a sweep (ascending forward, descending backward)
-template <bool FWD>
-__device__ __forceinline__ int sweep_level(const Topo& t, int k) {
-  return FWD ? k : t.nlev - 1 - k;
-}
-
-template <typename T, int NT, bool FWD>
-__device__ __forceinline__ void quad_prefetch(const Topo& t, IluView<T> v, const double* r, int k,
-                                              QuadJob<T>& j) {
-  if (k >= t.nlev) return;
-  const int l = sweep_level<FWD>(t, k);
-  const int pos = t.level_ptr[l] + (threadIdx.x >> 2);
-  if (pos < t.level_ptr[l + 1]) quad_load<T, FWD>(t, v, r, pos, threadIdx.x & 3, j);
-}
-
-// Three levels in flight (FP32 data fits the register budget of 1024 threads).
-template <typename T, int NT, bool FWD>
-__device__ __forceinline__ void quad_sweep3(const Topo& t, IluView<T> v, const double* r,
-                                            double* x, T* win) {
-  const int L = t.max_level;
-  int prev0 = 0, prev1 = 0, buf = 0;
-  QuadJob<T> ja, jb, jc;
-  quad_prefetch<T, NT, FWD>(t, v, r, 0, ja);
-  quad_prefetch<T, NT, FWD>(t, v, r, 1, jb);
-  quad_prefetch<T, NT, FWD>(t, v, r, 2, jc);
-  for (int k = 0; k < t.nlev; k += 3) {
-    quad_level<T, NT, FWD>(t, v, r, x, win, L, sweep_level<FWD>(t, k), prev0, prev1, buf, ja);
-    quad_prefetch<T, NT, FWD>(t, v, r, k + 3, ja);
-    if (k + 1 >= t.nlev) break;
-    quad_level<T, NT, FWD>(t, v, r, x, win, L, sweep_level<FWD>(t, k + 1), prev0, prev1, buf, jb);
-    quad_prefetch<T, NT, FWD>(t, v, r, k + 4, jb);
-    if (k + 2 >= t.nlev) break;
-    quad_level<T, NT, FWD>(t, v, r, x, win, L, sweep_level<FWD>(t, k + 2), prev0, prev1, buf, jc);
-    quad_prefetch<T, NT, FWD>(t, v, r, k + 5, jc);
-  }
-}
-
-// Two levels in flight (FP64).
-template <typename T, int NT, bool FWD>
-__device__ __forceinline__ void quad_sweep2(const Topo& t, IluView<T> v, const double* r,
-                                            double* x, T* win) {
-  const int L = t.max_level;
-  int prev0 = 0, prev1 = 0, buf = 0;
-  QuadJob<T> ja, jb;
-  quad_prefetch<T, NT, FWD>(t, v, r, 0, ja);
-  quad_prefetch<T, NT, FWD>(t, v, r, 1, jb);
-  for (int k = 0; k < t.nlev; k += 2) {
-    quad_level<T, NT, FWD>(t, v, r, x, win, L, sweep_level<FWD>(t, k), prev0, prev1, buf, ja);
-    quad_prefetch<T, NT, FWD>(t, v, r, k + 2, ja);
-    if (k + 1 >= t.nlev) break;
-    quad_level<T, NT, FWD>(t, v, r, x, win, L, sweep_level<FWD>(t, k + 1), prev0, prev1, buf, jb);
-    quad_prefetch<T, NT, FWD>(t, v, r, k + 3, jb);
-  }
-}
-
-template <typename T, int NT>
-__device__ __forceinline__ void apply_levels_quad(const Topo& t, IluView<T> v, const double* r,
-                                                  double* x, T* win) {
-  if (sizeof(T) == sizeof(double)) {
-    quad_sweep2<T, NT, true>(t, v, r, x, win);
-    quad_sweep2<T, NT, false>(t, v, r, x, win);
-  } else {
-    quad_sweep3<T, NT, true>(t, v, r, x, win);
-    quad_sweep3<T, NT, false>(t, v, r, x, win);
-  }
 }
 
 }  // namespace ilu
@@ -826,9 +669,11 @@ template <typename T, bool FWD, bool SKIP = false>
 __device__ __forceinline__ void ring2_row(const RingJob<T>& j, IluView<T> v, double* x, T* ring,
                                           unsigned mask) {
   if (SKIP && !j.live) return;
-  T acc[3];
+  T out[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) acc[c] = FWD ? j.rhs[c] : (T)0;
+  for (int a = 0; a < 3; ++a)
+    out[a] = FWD ? dot3(j.D[3 * a], j.rhs[0], j.D[3 * a + 1], j.rhs[1], j.D[3 * a + 2], j.rhs[2])
+                 : j.rhs[a];
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     const int kp = j.kp[s];
@@ -836,17 +681,7 @@ __device__ __forceinline__ void ring2_row(const RingJob<T>& j, IluView<T> v, dou
     const bool has = kp >= 0;
     const T x0 = has ? w[0] : (T)0, x1 = has ? w[1] : (T)0, x2 = has ? w[2] : (T)0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const T t = j.a[9 * s + 3 * a] * x0 + j.a[9 * s + 3 * a + 1] * x1 +
-                  j.a[9 * s + 3 * a + 2] * x2;
-      acc[a] = FWD ? acc[a] - t : acc[a] + t;
-    }
-  }
-  T out[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const T d = j.D[3 * a] * acc[0] + j.D[3 * a + 1] * acc[1] + j.D[3 * a + 2] * acc[2];
-    out[a] = FWD ? d : j.rhs[a] - d;
+    for (int a = 0; a < 3; ++a) out[a] = sub_dot3(out[a], j.a + 9 * s + 3 * a, x0, x1, x2);
   }
   if (!j.live) return;
   T* w = ring + ((unsigned)j.pos & mask) * 3u;

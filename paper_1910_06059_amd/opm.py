@@ -69,7 +69,7 @@ class Problem(ctypes.Structure):
                 ("n_wells", _i32), ("pad_w", _i32), ("well_conn_ptr", _vp), ("conn_cell", _vp),
                 ("conn_well", _vp), ("well_kind", _vp), ("well_phase", _vp), ("well_target", _vp),
                 ("well_vol", _vp), ("well_state", _vp), ("amg", _vp), ("well_limit", _vp),
-                ("well_ctrl", _vp), ("nx", _i32), ("ny", _i32), ("nz", _i32), ("pad_l", _i32),
+                ("well_ctrl", _vp), ("nx", _i32), ("ny", _i32), ("nz", _i32), ("ilu_box", _i32),
                 ("box_cell", _vp), ("cell_box", _vp)]
 
 
@@ -419,6 +419,9 @@ class GpuModel:
             self.pb.n_sub, self.pb.max_sub, self.pb.max_width = blk.n_sub, blk.max_sub, blk.max_width
             self.pb.sub_level_ptr = d["sub_level_ptr"].data_ptr()
             self.pb.slot = d["slot"].data_ptr()
+            bx, by, bz = (min(b, m) for b, m in zip(self.ilu_blocks, (nx, ny, nz)))
+            if max(bx, by, bz) < 1024:
+                self.pb.ilu_box = bx | by << 10 | bz << 20
         # meaning of the third variable per cell (0 s_g, 1 r_go): live oil only
         self.live = bool(f.live)
         self.meaning_t = torch.from_numpy(case.initial_meaning()).to(self.dev)
