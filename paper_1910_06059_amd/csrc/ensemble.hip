@@ -39,6 +39,7 @@ struct EnsMember {
   void* ilu;
   double *r, *rh, *p, *v, *ph, *s, *sh, *t;
   double* backup;        // copy of y kept by the autotuner between trials
+  int32_t* rows;         // [n] cells by workgroup (k_ensemble_mw)
   int32_t ring;          // 1: ILU(0) sweeps through the LDS ring, 0: the LDS window
   uint32_t ring_mask;    // ring capacity - 1 (rows)
 };
@@ -50,7 +51,7 @@ size_t member_bytes(const opm_problem& pb, int precision) {
   const size_t ilu = precision == OPM_PREC_MIXED ? ilu::view_bytes<float>(pb.n_cells)
                                                  : ilu::view_bytes<double>(pb.n_cells);
   return 13 * al256(sizeof(double) * N) + al256(sizeof(double) * 9 * (size_t)pb.nnzb) +
-         al256(ilu);
+         al256(ilu) + al256(sizeof(int32_t) * (size_t)pb.n_cells);
 }
 
 // LDS of the kernel: reduction scratch, sweep storage (the largest over the
@@ -66,6 +67,20 @@ struct LdsPlan {
 inline size_t window_bytes(size_t tsize, int max_level) { return tsize * 2 * 3 * (size_t)max_level; }
 inline size_t ring_bytes(size_t tsize, const opm_problem& pb) {
   return tsize * 3 * (size_t)ilu::ring_rows(pb.sweep_span, pb.max_level);
+}
+
+// The sweep storage of k_ensemble_mw: the window (the cell marks of its row
+// list share its place, where they take no more than kMaxMarks), then two
+// level bounds per level.
+constexpr size_t kMaxMarks = 64 * 1024;
+size_t mw_sweep_bytes(const opm_problem* members, int n, size_t tsize, int width) {
+  size_t marks = 0, levels = 0;
+  for (int m = 0; m < n; ++m) {
+    marks = std::max(marks, sizeof(unsigned) * (((size_t)members[m].n_cells + 31) / 32));
+    levels = std::max(levels, (size_t)members[m].n_levels);
+  }
+  return al256(std::max(al256(window_bytes(tsize, width)), marks <= kMaxMarks ? marks : 0) +
+               2 * sizeof(int) * levels);
 }
 
 LdsPlan lds_plan(size_t tsize, int threads, size_t sweep_bytes, int max_level, bool fac_window) {
@@ -452,36 +467,327 @@ __device__ bool grp_reduce(Grp& G, double* v, double* red, int* word) {
   return true;
 }
 
-// f(position, cell) for every row this workgroup owns
-template <int NT, typename F>
-__device__ __forceinline__ void for_rows(const Topo& t, F f) {
+// The rows a workgroup owns, as a list of their cells.  A loop over the local
+// levels instead would have a few dozen rows per level for 256 threads and a
+// chain of three loads (level bounds, position, cell) in every one.  The
+// workgroup has four wavefronts on its compute unit, so every phase below is
+// bound by the latencies it waits out; with the list, the loads ahead in the
+// product and the sweeps and the shares by largest range, a report step of 16
+// members of about 40k cells (FP32 factors, 256 workgroups) went from 151 to
+// 60 ms; per BiCGStab iteration of a workgroup of 2900 rows the two
+// applications take 0.22 ms, the two products 0.26 ms, the vectors 0.05 ms.
+struct Rows {
+  const int32_t* cell;
+  int count;
+};
+
+// Cells of the workgroup's rows into `out` at the place of its range of
+// subdomains in the member: in ascending order where a bit per cell fits the
+// LDS scratch (one pass marks them, one lists the set bits), else by level.
+template <int NT>
+__device__ __forceinline__ Rows list_rows(const Topo& t, int n, int32_t* out, unsigned* bits, size_t scratch) {
+  const int tid = threadIdx.x;
+  int before = 0, count = 0;   // rows of the earlier subdomains, and of this range
   for (int l = 0; l < t.nlev; ++l) {
-    const int p1 = ilu::lvl_end(t, l);
-    for (int pos = ilu::lvl_begin(t, l) + (int)threadIdx.x; pos < p1; pos += NT)
-      f(pos, t.perm[pos]);
+    before += t.level_ptr[l * t.lstride + t.s0] - t.level_ptr[l * t.lstride];
+    count += ilu::lvl_end(t, l) - ilu::lvl_begin(t, l);
   }
+  out += before;
+  const int nw = (n + 31) / 32;
+  if (sizeof(unsigned) * (size_t)nw <= scratch) {
+    for (int w = tid; w < nw; w += NT) bits[w] = 0;
+    __syncthreads();
+    for (int l = 0; l < t.nlev; ++l) {
+      const int p1 = ilu::lvl_end(t, l);
+      for (int pos = ilu::lvl_begin(t, l) + tid; pos < p1; pos += NT) {
+        const int c = t.perm[pos];
+        atomicOr(&bits[c >> 5], 1u << (c & 31));
+      }
+    }
+    __syncthreads();
+    // each thread lists a contiguous range of words, after the threads before it
+    const int per = (nw + NT - 1) / NT, w0 = min(tid * per, nw), w1 = min(w0 + per, nw);
+    int mine = 0;
+    for (int w = w0; w < w1; ++w) mine += __popc(bits[w]);
+    int at = mine;   // inclusive scan over the wavefront, then over the wavefronts
+    const int lane = tid & (kWave - 1);
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int o = __shfl_up(at, off, kWave);
+      if (lane >= off) at += o;
+    }
+    __shared__ int tot[NT / kWave];
+    if (lane == kWave - 1) tot[tid / kWave] = at;
+    __syncthreads();
+    for (int w = 0; w < tid / kWave; ++w) at += tot[w];
+    at -= mine;
+    for (int w = w0; w < w1; ++w)
+      for (unsigned b = bits[w]; b; b &= b - 1) out[at++] = 32 * w + __ffs((int)b) - 1;
+  } else {
+    int at = 0;
+    for (int l = 0; l < t.nlev; ++l) {
+      const int p0 = ilu::lvl_begin(t, l), p1 = ilu::lvl_end(t, l);
+      for (int pos = p0 + tid; pos < p1; pos += NT) out[at + pos - p0] = t.perm[pos];
+      at += p1 - p0;
+    }
+  }
+  __syncthreads();
+  return Rows{out, count};
+}
+
+// f(cell) for every row this workgroup owns
+template <int NT, typename F>
+__device__ __forceinline__ void for_rows(const Rows& r, F f) {
+  for (int q = threadIdx.x; q < r.count; q += NT) f(r.cell[q]);
+}
+
+// Vector operations on the workgroup's rows, four rows of a thread at a time:
+// load(u, k) reads what component k needs into slot u, store(u, k) follows
+// for the rows in range, so that four rows' loads are in flight together.
+template <int NT, typename L, typename S>
+__device__ __forceinline__ void for_values(const Rows& r, L load, S store) {
+  constexpr int U = 4;
+  for (int q0 = threadIdx.x; q0 < r.count; q0 += U * NT) {
+    int cell[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) cell[u] = r.cell[min(q0 + u * NT, r.count - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) load(3 * u + c, 3 * cell[u] + c);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (q0 + u * NT < r.count)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) store(3 * u + c, 3 * cell[u] + c);
+  }
+}
+
+// y = J x on the workgroup's rows, f(k, y_k, w_k) for each component: three rows
+// per wavefront as in spmv_group (21 lanes per row, lane (block, component)),
+// kSpmvBatch such groups at a time.  A batch goes through four dependent loads
+// (cell, row bounds, blocks and columns, vector): each is issued one batch
+// ahead of the next, so that a wavefront (a compute unit holds four here)
+// waits for one of them per batch and not for the chain.
+constexpr int kSpmvBatch = 4;
+template <int NT, typename F>
+__device__ __forceinline__ void spmv_rows(const Rows& r, const opm_problem& pb, const double* J,
+                                          const double* x, const double* w, F f) {
+  constexpr int U = kSpmvBatch, kWaves = NT / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int rl = min(lane / 21, 2), rem = lane - 21 * rl, blk = rem / 3, comp = rem - 3 * blk;
+  const int groups = (r.count + 2) / 3, batches = (groups + U - 1) / U;
+  struct Batch {   // one batch's registers: bounds, then blocks and columns, then the vector
+    int q0[U], q1[U], col[U];
+    double B[U][3], x[U][3];
+    unsigned in;   // bit u: the lane has a block of row u
+  };
+  struct Cells {
+    int c[U];
+  };
+  auto row_of = [&](int b, int u) { return 3 * ((wave + b * kWaves) * U + u) + rl; };
+  auto cells = [&](int b, Cells& c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) c.c[u] = r.cell[min(row_of(b, u), r.count - 1)];
+  };
+  auto bounds = [&](const Cells& c, Batch& p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      p.q0[u] = pb.row_ptr[c.c[u]];
+      p.q1[u] = pb.row_ptr[c.c[u] + 1];
+    }
+  };
+  auto blocks = [&](Batch& p) __attribute__((always_inline)) {
+    p.in = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int q = min(p.q0[u] + blk, p.q1[u] - 1);   // (a lane past the row's blocks adds zero)
+      if (lane < 63 && p.q0[u] + blk < p.q1[u]) p.in |= 1u << u;
+      p.col[u] = pb.col_idx[q];
+      const double* b = J + 9 * (size_t)q + 3 * comp;
+#pragma unroll
+      for (int e = 0; e < 3; ++e) p.B[u][e] = b[e];
+    }
+  };
+  auto vector = [&](Batch& p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) p.x[u][e] = x[3 * (size_t)p.col[u] + e];
+  };
+  // batch b from `own`; the vector of b + 1 into `p1`, the blocks of b + 2
+  // into `p2`, the row bounds of b + 3 into `own`'s place, the cells of b + 4
+  auto step = [&](int b, Batch& own, Batch& p1, Batch& p2, Cells& c0, const Cells& c3)
+      __attribute__((always_inline)) {
+    double wv[U], v[U];
+    int at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      at[u] = 3 * c0.c[u] + comp;
+      wv[u] = w[at[u]];
+    }
+    vector(p1);
+    blocks(p2);
+    cells(b + 4, c0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = own.B[u][0] * own.x[u][0] + own.B[u][1] * own.x[u][1] + own.B[u][2] * own.x[u][2];
+      if (!((own.in >> u) & 1u)) v[u] = 0.0;
+    }
+    bounds(c3, own);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      double sum = v[u];
+#pragma unroll
+      for (int k = 1; k < 7; ++k) sum += __shfl(v[u], lane + 3 * k, kWave);
+      if (lane < 63 && blk == 0 && row_of(b, u) < r.count) f(at[u], sum, wv[u]);
+    }
+  };
+  Cells k0, k1, k2, k3;
+  Batch p, q, o;
+  cells(0, k0);
+  cells(1, k1);
+  cells(2, k2);
+  cells(3, k3);
+  bounds(k0, p);
+  bounds(k1, q);
+  bounds(k2, o);
+  blocks(p);
+  blocks(q);
+  vector(p);
+  for (int b = 0; wave + b * kWaves < batches; b += 12) {
+    step(b, p, q, o, k0, k3);
+    step(b + 1, q, o, p, k1, k0);
+    step(b + 2, o, p, q, k2, k1);
+    step(b + 3, p, q, o, k3, k2);
+    step(b + 4, q, o, p, k0, k3);
+    step(b + 5, o, p, q, k1, k0);
+    step(b + 6, p, q, o, k2, k1);
+    step(b + 7, q, o, p, k3, k2);
+    step(b + 8, o, p, q, k0, k3);
+    step(b + 9, p, q, o, k1, k0);
+    step(b + 10, q, o, p, k2, k1);
+    step(b + 11, o, p, q, k3, k2);
+  }
+}
+
+// x = (LU)^{-1} r for the workgroup's rows: the sweeps of wg_sweep with the
+// level bounds in LDS (`lvl`, two per level; so a level's loads wait for no
+// other load), one (FP32: two) levels of rows in flight (jobs in turn, every load
+// clamped and in straight-line code), and every neighbour value from the LDS
+// window (a row's neighbours lie on the level just finished).
+template <typename T, bool FWD>
+__device__ __forceinline__ void mw_row(const ilu::SweepJob<T>& j, IluView<T> v, double* x, T* win,
+                                       int L, int par, int prev0, int p0, int pos) {
+  T out[3];
+  ilu::solve_row<T, FWD>(j, [&](int kp, T* xv) {
+    const T* w = win + (unsigned)((par ^ 1) * L + (kp - prev0)) * 3u;
+    xv[0] = w[0];
+    xv[1] = w[1];
+    xv[2] = w[2];
+  }, out);
+  T* w = win + (unsigned)(par * L + (pos - p0)) * 3u;
+#pragma unroll
+  for (unsigned c = 0; c < 3; ++c) {
+    w[c] = out[c];
+    if (FWD)
+      v.z[c * (unsigned)v.ns + (unsigned)pos] = out[c];
+    else
+      x[3u * (unsigned)j.cell + c] = (double)out[c];
+  }
+}
+
+template <typename T, int NT, bool FWD>
+__device__ __forceinline__ void mw_sweep(const Topo& t, IluView<T> v, const double* r, double* x,
+                                         T* win, const int* lvl) {
+  constexpr int ND = 2;
+  const int L = t.max_level, tid = threadIdx.x;
+  auto level = [&](int k) {
+    const int kc = min(k, t.nlev - 1);
+    return FWD ? kc : t.nlev - 1 - kc;
+  };
+  auto position = [&](int k) {
+    const int l = level(k);
+    return max(min(lvl[2 * l] + tid, lvl[2 * l + 1] - 1), 0);
+  };
+  auto cell_of = [&](int k) { return t.perm[position(k)]; };
+  // the row of level k, its cell loaded ND steps ago (older than any load that
+  // a level waits for)
+  auto fetch = [&](int k, int& cell, ilu::SweepJob<T>& j) __attribute__((always_inline)) {
+    const unsigned ns = (unsigned)v.ns, up = (unsigned)position(k);
+    const int32_t* kp = FWD ? t.lo_pos : t.up_pos;
+    const T* blk = FWD ? v.lov : v.upv;
+    j.cell = cell;
+#pragma unroll
+    for (unsigned c = 0; c < 3; ++c)
+      j.rhs[c] = FWD ? (T)r[3u * (unsigned)cell + c] : v.z[c * ns + up];
+#pragma unroll
+    for (unsigned s = 0; s < 3; ++s) j.kp[s] = kp[3u * up + s];
+#pragma unroll
+    for (unsigned e = 0; e < 27; ++e) j.a[e] = blk[e * ns + up];
+    if (FWD)
+#pragma unroll
+      for (unsigned e = 0; e < 9; ++e) j.D[e] = v.dinv[e * ns + up];
+    cell = cell_of(k + ND);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int prev0 = 0;
+  // level k from `own`, the level ND - 1 behind it into `last`
+  auto step = [&](int k, int par, const ilu::SweepJob<T>& own, ilu::SweepJob<T>& last, int& cell)
+      __attribute__((always_inline)) {
+    const int l = level(k), p0 = lvl[2 * l], p1 = lvl[2 * l + 1];
+    fetch(k + ND - 1, cell, last);
+    if (p0 + tid < p1) mw_row<T, FWD>(own, v, x, win, L, par, prev0, p0, p0 + tid);
+    __syncthreads();
+    prev0 = p0;
+    return k + 1 < t.nlev;
+  };
+  ilu::SweepJob<T> a, b, c;
+  int ca = cell_of(0), cb = cell_of(1), cc = ND == 3 ? cell_of(2) : 0;
+  fetch(0, ca, a);
+  if (ND == 3) {
+    fetch(1, cb, b);
+    for (int k = 0;; k += 6)
+      if (!step(k, 0, a, c, cc) || !step(k + 1, 1, b, a, ca) || !step(k + 2, 0, c, b, cb) ||
+          !step(k + 3, 1, a, c, cc) || !step(k + 4, 0, b, a, ca) || !step(k + 5, 1, c, b, cb))
+        return;
+  }
+  for (int k = 0;; k += 2)
+    if (!step(k, 0, a, b, cb) || !step(k + 1, 1, b, a, ca)) return;
+}
+
+template <typename T, int NT>
+__device__ __forceinline__ void mw_apply(const Topo& t, IluView<T> v, const double* r, double* x,
+                                         T* win, const int* lvl) {
+  if (t.max_level > NT) {   // levels wider than the workgroup
+    ilu::apply_levels_wg<T, NT>(t, v, r, x, win);
+    return;
+  }
+  mw_sweep<T, NT, true>(t, v, r, x, win, lvl);
+  mw_sweep<T, NT, false>(t, v, r, x, win, lvl);
 }
 
 // Right-preconditioned BiCGStab for J d = b over the member's workgroups
 // (the steps of wg_bicgstab, each on the workgroup's rows).
 template <typename T, int NT>
-__device__ int mw_bicgstab(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp& G,
-                           const double* b, double* x, double rtol, int maxit, double* red,
-                           int* word, T* swin, int* its_out) {
+__device__ __forceinline__ int mw_bicgstab(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp& G,
+                           const Rows& rows, const double* b, double* x, double rtol, int maxit,
+                           double* red, int* word, T* swin, const int* lvl, int* its_out) {
   double bb = 0.0;
-  for_rows<NT>(tp, [&](int, int i) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const int k = 3 * i + c;
-      const double bv = b[k];
-      x[k] = 0.0;
-      M.r[k] = bv;
-      M.rh[k] = bv;
-      M.p[k] = 0.0;
-      M.v[k] = 0.0;
-      bb += bv * bv;
-    }
-  });
+  {
+    double bv[12];
+    for_values<NT>(rows, [&](int u, int k) { bv[u] = b[k]; },
+                   [&](int u, int k) {
+                     x[k] = 0.0;
+                     M.r[k] = bv[u];
+                     M.rh[k] = bv[u];
+                     M.p[k] = 0.0;
+                     M.v[k] = 0.0;
+                     bb += bv[u] * bv[u];
+                   });
+  }
   if (!grp_reduce<NT, 1>(G, &bb, red, word)) return OPM_EHIP;
   *its_out = 0;
   if (bb == 0.0) return OPM_OK;
@@ -492,76 +798,81 @@ __device__ int mw_bicgstab(const EnsMember& M, const Topo& tp, IluView<T> iv, Gr
     *its_out = it;
     if (fabs(rho) < 1e-300) return OPM_EBREAKDOWN;
     const double beta = it == 1 ? 0.0 : (rho / rho0) * (alpha / omega);
-    for_rows<NT>(tp, [&](int, int i) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int k = 3 * i + c;
-        M.p[k] = M.r[k] + beta * (M.p[k] - omega * M.v[k]);
-      }
-    });
+    {
+      double rv[12], pv[12], vv[12];
+      for_values<NT>(rows,
+                     [&](int u, int k) {
+                       rv[u] = M.r[k];
+                       pv[u] = M.p[k];
+                       vv[u] = M.v[k];
+                     },
+                     [&](int u, int k) { M.p[k] = rv[u] + beta * (pv[u] - omega * vv[u]); });
+    }
     __syncthreads();
-    ilu::apply_levels_wg<T, NT>(tp, iv, M.p, M.ph, swin);
+    mw_apply<T, NT>(tp, iv, M.p, M.ph, swin, lvl);
     if (!grp_barrier(G, word)) return OPM_EHIP;   // the neighbours' ph
     double rv = 0.0;
-    for_rows<NT>(tp, [&](int, int i) {
-      double y3[3];
-      ilu::spmv_row(M.pb.row_ptr, M.pb.col_idx, M.J, M.ph, i, y3);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        M.v[3 * i + c] = y3[c];
-        rv += M.rh[3 * i + c] * y3[c];
-      }
+    spmv_rows<NT>(rows, M.pb, M.J, M.ph, M.rh, [&](int k, double y, double w) {
+      M.v[k] = y;
+      rv += w * y;
     });
     if (!grp_reduce<NT, 1>(G, &rv, red, word)) return OPM_EHIP;
     if (rv == 0.0) return OPM_EBREAKDOWN;
     alpha = rho / rv;
     double ss = 0.0;
-    for_rows<NT>(tp, [&](int, int i) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int k = 3 * i + c;
-        const double sv = M.r[k] - alpha * M.v[k];
-        M.s[k] = sv;
-        ss += sv * sv;
-      }
-    });
+    {
+      double r0[12], v0[12];
+      for_values<NT>(rows,
+                     [&](int u, int k) {
+                       r0[u] = M.r[k];
+                       v0[u] = M.v[k];
+                     },
+                     [&](int u, int k) {
+                       const double sv = r0[u] - alpha * v0[u];
+                       M.s[k] = sv;
+                       ss += sv * sv;
+                     });
+    }
     if (!grp_reduce<NT, 1>(G, &ss, red, word)) return OPM_EHIP;
     if (sqrt(ss) <= tol) {
-      for_rows<NT>(tp, [&](int, int i) {
+      for_rows<NT>(rows, [&](int i) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) x[3 * i + c] += alpha * M.ph[3 * i + c];
       });
       __syncthreads();
       return OPM_OK;
     }
-    ilu::apply_levels_wg<T, NT>(tp, iv, M.s, M.sh, swin);
+    mw_apply<T, NT>(tp, iv, M.s, M.sh, swin, lvl);
     if (!grp_barrier(G, word)) return OPM_EHIP;   // the neighbours' sh
     double tv[2] = {0.0, 0.0};
-    for_rows<NT>(tp, [&](int, int i) {
-      double y3[3];
-      ilu::spmv_row(M.pb.row_ptr, M.pb.col_idx, M.J, M.sh, i, y3);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        M.t[3 * i + c] = y3[c];
-        tv[0] += y3[c] * M.s[3 * i + c];
-        tv[1] += y3[c] * y3[c];
-      }
+    spmv_rows<NT>(rows, M.pb, M.J, M.sh, M.s, [&](int k, double y, double w) {
+      M.t[k] = y;
+      tv[0] += y * w;
+      tv[1] += y * y;
     });
     if (!grp_reduce<NT, 2>(G, tv, red, word)) return OPM_EHIP;
     if (tv[1] == 0.0) return OPM_EBREAKDOWN;
     omega = tv[0] / tv[1];
     double rv2[2] = {0.0, 0.0};
-    for_rows<NT>(tp, [&](int, int i) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int k = 3 * i + c;
-        x[k] += alpha * M.ph[k] + omega * M.sh[k];
-        const double rk = M.s[k] - omega * M.t[k];
-        M.r[k] = rk;
-        rv2[0] += rk * rk;
-        rv2[1] += M.rh[k] * rk;
-      }
-    });
+    {
+      double xv[12], pv[12], hv[12], sv[12], tt[12], rh[12];
+      for_values<NT>(rows,
+                     [&](int u, int k) {
+                       xv[u] = x[k];
+                       pv[u] = M.ph[k];
+                       hv[u] = M.sh[k];
+                       sv[u] = M.s[k];
+                       tt[u] = M.t[k];
+                       rh[u] = M.rh[k];
+                     },
+                     [&](int u, int k) {
+                       x[k] = xv[u] + (alpha * pv[u] + omega * hv[u]);
+                       const double rk = sv[u] - omega * tt[u];
+                       M.r[k] = rk;
+                       rv2[0] += rk * rk;
+                       rv2[1] += rh[u] * rk;
+                     });
+    }
     if (!grp_reduce<NT, 2>(G, rv2, red, word)) return OPM_EHIP;
     if (sqrt(rv2[0]) <= tol) return OPM_OK;
     if (omega == 0.0) return OPM_EBREAKDOWN;
@@ -573,11 +884,12 @@ __device__ int mw_bicgstab(const EnsMember& M, const Topo& tp, IluView<T> iv, Gr
 
 // The Newton iteration of wg_newton over the member's workgroups.
 template <typename T, int NT, bool FACWIN>
-__device__ int mw_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp& G, double h,
-                         const opm_newton_opts& o, double* red, int* word, T* swin, double* fwin,
-                         int* flag, opm_ensemble_report& rep) {
+__device__ __forceinline__ int mw_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp& G,
+                         const Rows& rows, double h, const opm_newton_opts& o, double* red,
+                         int* word, T* swin, const int* lvl, double* fwin, int* flag,
+                         opm_ensemble_report& rep) {
   const int n = M.pb.n_cells;
-  for_rows<NT>(tp, [&](int, int i) {
+  for_rows<NT>(rows, [&](int i) {
     FaceProps P;
     CellAcc A;
     asmdev::properties<false>(M.pb.fluid, M.y_save[3 * i], M.y_save[3 * i + 1],
@@ -617,7 +929,7 @@ __device__ int mw_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp&
   for (int it = 0;; ++it) {
     // max CNV (3, NaN-propagating) and the mass-balance sums (7)
     double nv[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for_rows<NT>(tp, [&](int, int i) {
+    for_rows<NT>(rows, [&](int i) {
       double part[kNormStride];
       asmdev::assemble_row<false>(a, i, h, part);
 #pragma unroll
@@ -643,17 +955,17 @@ __device__ int mw_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp&
     __syncthreads();
     ilu::factor_levels_wg<T, FACWIN, NT, false>(tp, M.J, iv, flag, fwin);
     __syncthreads();
-    for_rows<NT>(tp, [&](int pos, int) { ilu::pack_row<T>(tp, M.J, iv, pos); });
+    for_rows<NT>(rows, [&](int i) { ilu::pack_row<T>(tp, M.J, iv, M.pb.iperm[i]); });
     double sing = *flag != 0 ? 1.0 : 0.0;
     if (!grp_reduce<NT, 1, 1u>(G, &sing, red, word)) return OPM_EHIP;
     if (sing != 0.0) return OPM_ESINGULAR;
     int lits = 0;
-    const int st = mw_bicgstab<T, NT>(M, tp, iv, G, M.R, M.d, o.lin_rtol, o.lin_maxit, red, word,
-                                      swin, &lits);
+    const int st = mw_bicgstab<T, NT>(M, tp, iv, G, rows, M.R, M.d, o.lin_rtol, o.lin_maxit, red,
+                                      word, swin, lvl, &lits);
     rep.lin_its += lits;
     if (st != OPM_OK) return st;
     double bad = 0.0;
-    for_rows<NT>(tp, [&](int, int i) {
+    for_rows<NT>(rows, [&](int i) {
       const double p = M.y[3 * i];
       double dp = -M.d[3 * i];
       const double lim = o.dp_max_rel * fabs(p);
@@ -681,8 +993,8 @@ __device__ int mw_newton(const EnsMember& M, const Topo& tp, IluView<T> iv, Grp&
 }
 
 template <int NT>
-__device__ __forceinline__ void rows_copy(const Topo& t, double* dst, const double* src) {
-  for_rows<NT>(t, [&](int, int i) {
+__device__ __forceinline__ void rows_copy(const Rows& rows, double* dst, const double* src) {
+  for_rows<NT>(rows, [&](int i) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) dst[3 * i + c] = src[3 * i + c];
   });
@@ -714,16 +1026,26 @@ __global__ __launch_bounds__(NT) void k_ensemble_mw(const EnsMember* tab, const 
   tp.max_level = W.width;
   Grp G{W.w, W.g, part + (size_t)2 * kPartStride * (blockIdx.x - W.w), sync + W.m, spin, 0};
   IluView<T> iv = ilu::view<T>(&M.pb, M.ilu);
+  // the level bounds lie behind the sweep window
+  const size_t lvl_bytes = 2 * sizeof(int) * (size_t)tp.nlev;
+  const Rows rows = list_rows<NT>(tp, M.pb.n_cells, M.rows, reinterpret_cast<unsigned*>(swin),
+                                  sweep_bytes - lvl_bytes);
+  int* lvl = reinterpret_cast<int*>(reinterpret_cast<char*>(swin) + sweep_bytes - lvl_bytes);
+  for (int l = threadIdx.x; l < tp.nlev; l += NT) {
+    lvl[2 * l] = ilu::lvl_begin(tp, l);
+    lvl[2 * l + 1] = ilu::lvl_end(tp, l);
+  }
+  __syncthreads();
   opm_ensemble_report rep = {};
   int status = OPM_OK;
   for (int step = 0; step < n_steps && status == OPM_OK; ++step) {
-    rows_copy<NT>(tp, M.y_save, M.y);
+    rows_copy<NT>(rows, M.y_save, M.y);
     double t = 0.0, dt_try = dt_report;
     int cuts = 0;
     while (dt_report - t > 1e-9 * dt_report) {
       const double h = fmin(dt_try, dt_report - t);
-      const int st = mw_newton<T, NT, FACWIN>(M, tp, iv, G, h, o, red, &word, swin, fwin, &flag,
-                                              rep);
+      const int st = mw_newton<T, NT, FACWIN>(M, tp, iv, G, rows, h, o, red, &word, swin, lvl,
+                                              fwin, &flag, rep);
       __syncthreads();
       if (st == OPM_EHIP) {   // the member's workgroups lost each other
         status = st;
@@ -732,9 +1054,9 @@ __global__ __launch_bounds__(NT) void k_ensemble_mw(const EnsMember* tab, const 
       if (st == OPM_OK) {
         t += h;
         rep.substeps += 1;
-        rows_copy<NT>(tp, M.y_save, M.y);
+        rows_copy<NT>(rows, M.y_save, M.y);
       } else {
-        rows_copy<NT>(tp, M.y, M.y_save);
+        rows_copy<NT>(rows, M.y, M.y_save);
         dt_try = 0.5 * h;
         rep.cuts += 1;
         if (++cuts > o.max_cuts) {
@@ -904,75 +1226,105 @@ size_t members_offset(int n_members) {
   return part_offset(n_members) + al256(sizeof(double) * 2 * kPartStride * (size_t)kMaxEnsWgs);
 }
 
-// Workgroups per member for a launch of `budget` workgroups: in proportion
-// to the rows, at least one, at most one per subdomain (one for a member
-// without subdomains), each member's subdomains split into contiguous ranges
-// of about equal rows.  Writes the table (members in order, a member's
-// workgroups consecutive) and returns the number of workgroups.
+// Contiguous ranges of the subdomains with at most `cap` rows each, as few as
+// possible (their first subdomains, then n_sub); empty if one has more.
+std::vector<int> split_ranges(const std::vector<long>& rows, long cap) {
+  std::vector<int> first;
+  long acc = cap + 1;
+  for (int s = 0; s < (int)rows.size(); ++s) {
+    if (rows[s] > cap) return {};
+    if (acc + rows[s] > cap) {
+      first.push_back(s);
+      acc = 0;
+    }
+    acc += rows[s];
+  }
+  first.push_back((int)rows.size());
+  return first;
+}
+
+// Workgroups per member for a launch of `budget` workgroups: at least one, at
+// most one per subdomain (one for a member without subdomains), each owning a
+// contiguous range of the member's subdomains.  A member takes as long as its
+// workgroup with the most rows, so the rest goes, a step at a time, to the
+// member whose largest range is the largest of all, as many more workgroups as
+// make that range smaller (16 workgroups for 36 equal subdomains are no faster
+// than 12).  Writes the table (members in order, a member's workgroups
+// consecutive).
 int build_wg_table(const opm_problem* members, int n, int budget, std::vector<EnsWg>& out) {
   out.clear();
   if (budget < n) return OPM_EINVAL;
-  double total = 0.0;
-  for (int m = 0; m < n; ++m) total += members[m].n_cells;
-  std::vector<int> g(n), cap(n);
-  int used = 0;
+  struct Plan {
+    std::vector<int32_t> slp;    // host copy of sub_level_ptr
+    std::vector<long> rows;      // per subdomain
+    std::vector<int> first;      // the ranges' first subdomains, and the end
+    long largest = 0;            // rows of the largest range
+  };
+  std::vector<Plan> plan(n);
+  int used = n;
   for (int m = 0; m < n; ++m) {
-    cap[m] = members[m].n_sub > 1 ? members[m].n_sub : 1;
-    g[m] = std::max(1, std::min(cap[m], (int)std::floor(budget * members[m].n_cells / total)));
-    used += g[m];
+    const opm_problem& pb = members[m];
+    Plan& p = plan[m];
+    p.largest = pb.n_cells;
+    if (pb.n_sub <= 1) continue;
+    const size_t ns1 = (size_t)pb.n_sub + 1;
+    p.slp.resize((size_t)pb.n_levels * ns1);
+    OPM_TRY_HIP(hipMemcpy(p.slp.data(), pb.sub_level_ptr, sizeof(int32_t) * p.slp.size(),
+                          hipMemcpyDeviceToHost));
+    p.rows.assign(pb.n_sub, 0);
+    for (int l = 0; l < pb.n_levels; ++l)
+      for (int sd = 0; sd < pb.n_sub; ++sd)
+        p.rows[sd] += p.slp[l * ns1 + sd + 1] - p.slp[l * ns1 + sd];
+    p.first = {0, pb.n_sub};
   }
-  // the floor and the minimum of one can overshoot: take back from the largest
-  while (used > budget) {
-    int mx = 0;
-    for (int m = 1; m < n; ++m)
-      if (g[m] > g[mx]) mx = m;
-    if (g[mx] <= 1) return OPM_EINVAL;
-    --g[mx];
-    --used;
-  }
-  // what is left goes, one at a time, to the member with the most rows per
-  // workgroup that can still take one
-  while (used < budget) {
-    int best = -1;
+  // the fewest workgroups that make the largest range smaller: the largest
+  // sums of neighbouring subdomains below it are the candidates
+  auto smaller = [](const Plan& p) {
+    long best = 0;
+    for (size_t s = 0; s < p.rows.size(); ++s) {
+      long acc = 0;
+      for (size_t e = s; e < p.rows.size() && acc + p.rows[e] < p.largest; ++e) acc += p.rows[e];
+      best = std::max(best, acc);
+    }
+    return best > 0 ? split_ranges(p.rows, best) : std::vector<int>{};
+  };
+  std::vector<char> done(n, 0);
+  for (;;) {
+    int mx = -1;
     for (int m = 0; m < n; ++m)
-      if (g[m] < cap[m] &&
-          (best < 0 || (double)members[m].n_cells / g[m] > (double)members[best].n_cells / g[best]))
-        best = m;
-    if (best < 0) break;
-    ++g[best];
-    ++used;
+      if (!done[m] && (mx < 0 || plan[m].largest > plan[mx].largest)) mx = m;
+    if (mx < 0) break;
+    Plan& p = plan[mx];
+    const std::vector<int> f = p.rows.empty() ? std::vector<int>{} : smaller(p);
+    const int more = (int)f.size() - (int)p.first.size();
+    if (f.empty() || used + more > budget) {
+      done[mx] = 1;   // cannot be split further
+      continue;
+    }
+    used += more;
+    p.first = f;
+    p.largest = 0;
+    for (size_t w = 0; w + 1 < f.size(); ++w) {
+      long acc = 0;
+      for (int sd = f[w]; sd < f[w + 1]; ++sd) acc += p.rows[sd];
+      p.largest = std::max(p.largest, acc);
+    }
   }
   for (int m = 0; m < n; ++m) {
     const opm_problem& pb = members[m];
-    if (g[m] == 1) {
+    const Plan& p = plan[m];
+    const int g = std::max(1, (int)p.first.size() - 1);
+    if (g == 1) {
       out.push_back(EnsWg{m, 0, 1, 0, 1, pb.max_level, {0, 0}});
       continue;
     }
-    // rows per subdomain from the device copy of sub_level_ptr
     const size_t ns1 = (size_t)pb.n_sub + 1;
-    std::vector<int32_t> slp((size_t)pb.n_levels * ns1);
-    OPM_TRY_HIP(hipMemcpy(slp.data(), pb.sub_level_ptr, sizeof(int32_t) * slp.size(),
-                          hipMemcpyDeviceToHost));
-    std::vector<long> rows(pb.n_sub, 0);
-    for (int l = 0; l < pb.n_levels; ++l)
-      for (int sd = 0; sd < pb.n_sub; ++sd) rows[sd] += slp[l * ns1 + sd + 1] - slp[l * ns1 + sd];
-    int s0 = 0;
-    long acc = 0;
-    for (int w = 0; w < g[m]; ++w) {
-      // close range w once it reaches its share of the rows, leaving at
-      // least one subdomain for each later workgroup
-      const long target = (long)std::llround((double)pb.n_cells * (w + 1) / g[m]);
-      int s1 = s0 + 1;
-      acc += rows[s0];
-      while (s1 < pb.n_sub - (g[m] - 1 - w) && acc + rows[s1] / 2 < target) acc += rows[s1++];
-      if (w == g[m] - 1) {
-        while (s1 < pb.n_sub) acc += rows[s1++];
-      }
+    for (int w = 0; w < g; ++w) {
+      const int s0 = p.first[w], s1 = p.first[w + 1];
       int width = 0;
       for (int l = 0; l < pb.n_levels; ++l)
-        width = std::max(width, slp[l * ns1 + s1] - slp[l * ns1 + s0]);
-      out.push_back(EnsWg{m, w, g[m], s0, s1, width, {0, 0}});
-      s0 = s1;
+        width = std::max(width, p.slp[l * ns1 + s1] - p.slp[l * ns1 + s0]);
+      out.push_back(EnsWg{m, w, g, s0, s1, width, {0, 0}});
     }
   }
   return (int)out.size() <= kMaxEnsWgs ? OPM_OK : OPM_EINVAL;
@@ -1040,6 +1392,8 @@ int opm_ensemble_prepare(const opm_problem* members, double* const* y, int32_t n
     e.ilu = cur;
     cur += al256(precision == OPM_PREC_MIXED ? ilu::view_bytes<float>(pb.n_cells)
                                              : ilu::view_bytes<double>(pb.n_cells));
+    e.rows = (int32_t*)cur;
+    cur += al256(sizeof(int32_t) * N / 3);
     e.ring = 0;
     e.ring_mask = (uint32_t)ilu::ring_rows(pb.sweep_span, pb.max_level) - 1u;
   }
@@ -1068,7 +1422,7 @@ int opm_ensemble_configure(const opm_problem* members, int32_t n_members, int pr
     int width = 0;
     for (const EnsWg& e : wt) width = std::max(width, e.width);
     const size_t ts = precision == OPM_PREC_MIXED ? sizeof(float) : sizeof(double);
-    c.sweep_bytes = (int32_t)al256(window_bytes(ts, width));
+    c.sweep_bytes = (int32_t)mw_sweep_bytes(members, n_members, ts, width);
     if (lds_plan(ts, c.threads, (size_t)c.sweep_bytes, width, false).total > kEnsLds)
       return OPM_EINVAL;
   } else if (!plan_members(members, n_members, precision, c, &ring, &max_level)) {
