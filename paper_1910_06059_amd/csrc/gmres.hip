@@ -70,8 +70,8 @@ struct GmWork {
   double* V;      // [m + 1][Np] basis
   double* Z;      // [m][Np] preconditioned basis vectors
   double* w;      // [Np]
-  double* pa;     // [kMaxRestart + 1][kGmGrid] partials
-  double* pb;     // [kMaxRestart + 1][kGmGrid] partials
+  double* pa;     // [kGmGrid][kMaxRestart] partials
+  double* pb;     // [kGmGrid][kMaxRestart] partials
   double* pn;     // [kGmGrid] partials of a norm
   GmScalars* sc;
   int Np;
@@ -107,39 +107,130 @@ GmWork gm_carve(int n, int m, void* work) {
 
 inline int vec_grid(int N) { return std::min(kGmGrid, std::max(1, blocks_for(N, kGmBlock))); }
 
-// Rows 0..k of the partials part[i][0 .. G) summed into out[i] (LDS), each
-// row by one wavefront: lanes strided over the partials, then a fixed
-// shuffle tree.  Same order in every workgroup.
-__device__ __forceinline__ void sum_rows(const double* part, int G, int k, double* out) {
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  for (int i = wv; i <= k; i += kGmBlock / kWave) {
-    double v = 0.0;
-    for (int q = lane; q < G; q += kWave) v += part[(size_t)i * kGmGrid + q];
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off, kWave);
-    if (lane == 0) out[i] = v;
+// The sums over the wavefront of acc[0 .. JB), JB a power of two: each step
+// gives half of a lane's rows to the lane they are exchanged with and adds the
+// other half, so JB - 1 exchanges leave one row per lane (64 / JB lanes hold
+// the same one, added last) where JB separate sums take 6 JB.  Lane l returns
+// the sum of row l / (64 / JB).
+// With distance 32 or 16 the swap instructions of the lane halves or rows
+// exchange a pair in place; below, a shuffle.
+template <int W>
+__device__ __forceinline__ double halve_pair(double a, double b) {
+  if constexpr (W >= 16) {
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a);
+    const unsigned long long ub = __builtin_bit_cast(unsigned long long, b);
+    auto swap = [](unsigned p, unsigned q) {
+      if constexpr (W == 32)
+        return __builtin_amdgcn_permlane32_swap(p, q, false, false);
+      else
+        return __builtin_amdgcn_permlane16_swap(p, q, false, false);
+    };
+    const auto lo = swap((unsigned)ua, (unsigned)ub);
+    const auto hi = swap((unsigned)(ua >> 32), (unsigned)(ub >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+  } else {
+    const bool up = (threadIdx.x & W) != 0;
+    return (up ? b : a) + __shfl_xor(up ? a : b, W, kWave);
   }
-  __syncthreads();
+}
+template <int HALF, int W, int JB>
+__device__ __forceinline__ double halve_rows(double (&acc)[JB]) {
+  if constexpr (HALF >= 1) {
+#pragma unroll
+    for (int i = 0; i < HALF; ++i) acc[i] = halve_pair<W>(acc[i], acc[i + HALF]);
+    return halve_rows<HALF / 2, W / 2, JB>(acc);
+  } else {
+    double v = acc[0];
+#pragma unroll
+    for (int w = W; w >= 1; w /= 2) v += __shfl_xor(v, w, kWave);
+    return v;
+  }
+}
+template <int JB>
+__device__ __forceinline__ double wave_rows(double (&acc)[JB]) {
+  return halve_rows<JB / 2, kWave / 2, JB>(acc);
 }
 
-// The workgroup's sums of acc[i] (i <= k) into part[i][blockIdx.x].
+// The workgroup's sums of acc[i] (i <= j) into part[blockIdx.x][i].
 template <int JB>
-__device__ __forceinline__ void store_rows(const double (&acc)[JB], int k, double* part,
+__device__ __forceinline__ void store_rows(double (&acc)[JB], int j, double* part,
                                            double (*red)[JB]) {
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-#pragma unroll
-  for (int i = 0; i < JB; ++i) {
-    if (i <= k) {
-      double v = acc[i];
-      for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off, kWave);
-      if (lane == 0) red[wv][i] = v;
-    }
-  }
+  const double v = wave_rows<JB>(acc);
+  if (lane % (kWave / JB) == 0) red[wv][lane / (kWave / JB)] = v;
   __syncthreads();
-  if ((int)threadIdx.x <= k) {
+  if ((int)threadIdx.x <= j) {
     double s = 0.0;
+#pragma unroll
     for (int q = 0; q < kGmBlock / kWave; ++q) s += red[q][threadIdx.x];
-    part[(size_t)threadIdx.x * kGmGrid + blockIdx.x] = s;
+    part[(size_t)blockIdx.x * kMaxRestart + threadIdx.x] = s;
   }
+}
+
+// The sums h[i], i < JB, of the partials part[0 .. G)[i] (zero for i > j), in
+// the same fixed order in every workgroup: thread t adds row t % JB of the
+// partials t / JB, t / JB + 512 / JB, ..., then the wavefront and the
+// workgroup.  The first kFirst of a thread are loaded by `first`, to be issued
+// ahead of other loads.
+template <int JB>
+struct RowSums {
+  static constexpr int kStep = kGmBlock / JB, kFirst = 4;
+  double v[kFirst];
+  __device__ __forceinline__ void first(const double* part, int G) {
+    const int row = threadIdx.x % JB, q0 = threadIdx.x / JB;
+#pragma unroll
+    for (int u = 0; u < kFirst; ++u)
+      v[u] = part[(size_t)min(q0 + u * kStep, G - 1) * kMaxRestart + row];
+  }
+  __device__ __forceinline__ void finish(const double* part, int G, int j, double (*red)[JB],
+                                         double* h) {
+    const int row = threadIdx.x % JB, q0 = threadIdx.x / JB;
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < kFirst; ++u) t += q0 + u * kStep < G ? v[u] : 0.0;
+    for (int q = q0 + kFirst * kStep; q < G; q += kStep) t += part[(size_t)q * kMaxRestart + row];
+#pragma unroll
+    for (int w = JB; w < kWave; w *= 2) t += __shfl_xor(t, w, kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    if (lane < JB) red[threadIdx.x / kWave][lane] = t;
+    __syncthreads();
+    if ((int)threadIdx.x < JB) {
+      double sum = 0.0;
+#pragma unroll
+      for (int q = 0; q < kGmBlock / kWave; ++q) sum += red[q][threadIdx.x];
+      h[threadIdx.x] = (int)threadIdx.x <= j ? sum : 0.0;
+    }
+    __syncthreads();
+  }
+};
+
+// The sum of the partials part[0 .. G), G <= kGmGrid, in every lane of every
+// wavefront (in the same order): loads and end of it.
+struct NormSum {
+  static constexpr int kLoads = kGmGrid / kWave;
+  double v[kLoads];
+  __device__ __forceinline__ void first(const double* part, int G) {
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) v[u] = part[min(lane + u * kWave, G - 1)];
+  }
+  __device__ __forceinline__ double finish(int G) {
+    const int lane = threadIdx.x & (kWave - 1);
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) t += lane + u * kWave < G ? v[u] : 0.0;
+#pragma unroll
+    for (int w = kWave / 2; w >= 1; w /= 2) t += __shfl_xor(t, w, kWave);
+    return t;
+  }
+};
+
+// Keeps loads issued before this point, ahead of the tests and the arithmetic
+// after it.
+__device__ __forceinline__ void loads_issued() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 __device__ __forceinline__ int read_state(const GmScalars* sc, int* word) {
@@ -163,11 +254,11 @@ __global__ __launch_bounds__(kGmBlock) void k_gm_init(int N, const double* b, do
 
 __global__ __launch_bounds__(kGmBlock) void k_gm_init2(GmWork w, int G, double rtol, int maxit,
                                                         int m) {
-  __shared__ double tot[1];
-  sum_rows(w.pn, G, 0, tot);
+  NormSum ns;
+  ns.first(w.pn, G);
+  const double t = ns.finish(G);
   if (threadIdx.x == 0) {
     GmScalars& c = *w.sc;
-    const double t = tot[0];
     c.bnorm = sqrt(t);
     c.tol = rtol * c.bnorm;
     c.relres = t == 0.0 ? 0.0 : 1.0;
@@ -188,8 +279,7 @@ __global__ __launch_bounds__(kBlock) void k_gm_spmv(int n, const int32_t* row_pt
                                                      const int32_t* col, const double* J,
                                                      const double* x, const double* b, double* y,
                                                      const GmScalars* sc, int want, WellCorr wc) {
-  __shared__ int word;
-  const int st = read_state(sc, &word);
+  const int st = sc->state;   // (not changed by this kernel)
   if (RES ? st == kGmDone : st != want) return;
   const int lane = threadIdx.x & (kWave - 1);
   const int group = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
@@ -216,13 +306,14 @@ __global__ __launch_bounds__(kGmBlock) void k_gm_norm0(int N, GmWork w) {
 // with maxit = 0, since a cycle that reaches it ends the solve), convergence,
 // or g = beta e_0 and run.
 __global__ __launch_bounds__(kGmBlock) void k_gm_start(GmWork w, int G) {
-  __shared__ double tot[1];
   __shared__ int word;
   if (read_state(w.sc, &word) == kGmDone) return;
-  sum_rows(w.pn, G, 0, tot);
+  NormSum ns;
+  ns.first(w.pn, G);
+  const double tot = ns.finish(G);
   if (threadIdx.x != 0) return;
   GmScalars& c = *w.sc;
-  const double beta = sqrt(tot[0]);
+  const double beta = sqrt(tot);
   c.relres = c.bnorm > 0.0 ? beta / c.bnorm : 0.0;
   c.k_used = 0;
   c.its0 = c.its;
@@ -248,30 +339,36 @@ __global__ __launch_bounds__(kGmBlock) void k_gm_scale0(int N, GmWork w) {
     w.V[k] *= f;
 }
 
-// The first JB projection coefficients in LDS, zero past j: the update loops
-// run over all JB basis rows without a branch (rows past j are read as row
-// j, a cache hit, and weighted by zero), so all loads of an element are in
-// flight at once.
+// The three kernels of the orthogonalisation are latencies more than bytes
+// (9000 cells: 7 MB of basis vectors from the caches), so each asks for all it
+// needs first, the state word, the partials of the sums and the first element's
+// vectors, and then waits once.  The basis rows are read for all JB rows without
+// a branch (rows past j as row j, a cache hit, and weighted by zero).  9000
+// cells, 16 to 32 rows: dots 12.1 -> 5.7 us, cgs1 13.5 -> 5.9 us, cgs2 6.7 -> 4.9 us
+// (before: sums one row after another, and after the state and the partials).
 template <int JB>
-__device__ __forceinline__ void coeffs(const double* h, int j, double* hs) {
-  if ((int)threadIdx.x < JB) hs[threadIdx.x] = (int)threadIdx.x <= j ? h[threadIdx.x] : 0.0;
-  __syncthreads();
+__device__ __forceinline__ void load_rows(const GmWork& w, int j, int k, double (&vk)[JB]) {
+#pragma unroll
+  for (int i = 0; i < JB; ++i) vk[i] = w.V[(size_t)min(i, j) * w.Np + k];
 }
 
 // Partials of the first projections h1_i = <v_i, w>, i <= j.
 template <int JB>
 __global__ __launch_bounds__(kGmBlock) void k_gm_dots(int N, GmWork w, int j) {
   __shared__ double red[kGmBlock / kWave][JB];
-  __shared__ int word;
-  if (read_state(w.sc, &word) != kGmRunning) return;
-  double acc[JB];
+  const int state = w.sc->state;   // (not changed by this kernel)
+  const int k0 = blockIdx.x * kGmBlock + threadIdx.x;
+  double acc[JB], vk[JB];
+  load_rows<JB>(w, j, min(k0, N - 1), vk);
+  double wk = w.w[min(k0, N - 1)];
+  loads_issued();
+  if (state != kGmRunning) return;
+  if (k0 >= N) wk = 0.0;
 #pragma unroll
-  for (int i = 0; i < JB; ++i) acc[i] = 0.0;
-  for (int k = blockIdx.x * kGmBlock + threadIdx.x; k < N; k += gridDim.x * kGmBlock) {
-    double vk[JB];
-#pragma unroll
-    for (int i = 0; i < JB; ++i) vk[i] = w.V[(size_t)min(i, j) * w.Np + k];
-    const double wk = w.w[k];
+  for (int i = 0; i < JB; ++i) acc[i] = k0 < N ? vk[i] * wk : 0.0;
+  for (int k = k0 + gridDim.x * kGmBlock; k < N; k += gridDim.x * kGmBlock) {
+    load_rows<JB>(w, j, k, vk);
+    wk = w.w[k];
     __builtin_amdgcn_sched_barrier(0);   // every load of the element issued before the arithmetic
 #pragma unroll
     for (int i = 0; i < JB; ++i) acc[i] += vk[i] * wk;
@@ -283,22 +380,27 @@ __global__ __launch_bounds__(kGmBlock) void k_gm_dots(int N, GmWork w, int j) {
 // it) and the partials of the second projections h2_i = <v_i, w>.
 template <int JB>
 __global__ __launch_bounds__(kGmBlock) void k_gm_cgs1(int N, GmWork w, int j, int G) {
-  __shared__ double hsum[kMaxRestart + 1];
   __shared__ double h[JB];
   __shared__ double red[kGmBlock / kWave][JB];
-  __shared__ int word;
-  if (read_state(w.sc, &word) != kGmRunning) return;
-  sum_rows(w.pa, G, j, hsum);
-  if (blockIdx.x == 0 && (int)threadIdx.x <= j) w.sc->h1[threadIdx.x] = hsum[threadIdx.x];
-  coeffs<JB>(hsum, j, h);
-  double acc[JB];
+  const int state = w.sc->state;
+  RowSums<JB> rs;
+  rs.first(w.pa, G);
+  const int k0 = blockIdx.x * kGmBlock + threadIdx.x;
+  double acc[JB], vk[JB];
+  load_rows<JB>(w, j, min(k0, N - 1), vk);
+  double v = w.w[min(k0, N - 1)];
+  loads_issued();
+  if (state != kGmRunning) return;
+  rs.finish(w.pa, G, j, red, h);
+  if (blockIdx.x == 0 && (int)threadIdx.x <= j) w.sc->h1[threadIdx.x] = h[threadIdx.x];
 #pragma unroll
-  for (int i = 0; i < JB; ++i) acc[i] = 0.0;
-  for (int k = blockIdx.x * kGmBlock + threadIdx.x; k < N; k += gridDim.x * kGmBlock) {
-    double vk[JB];
+  for (int i = 0; i < JB; ++i) v -= h[i] * vk[i];
+  if (k0 < N) w.w[k0] = v;
 #pragma unroll
-    for (int i = 0; i < JB; ++i) vk[i] = w.V[(size_t)min(i, j) * w.Np + k];
-    double v = w.w[k];
+  for (int i = 0; i < JB; ++i) acc[i] = k0 < N ? vk[i] * v : 0.0;
+  for (int k = k0 + gridDim.x * kGmBlock; k < N; k += gridDim.x * kGmBlock) {
+    load_rows<JB>(w, j, k, vk);
+    v = w.w[k];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < JB; ++i) v -= h[i] * vk[i];
@@ -312,20 +414,27 @@ __global__ __launch_bounds__(kGmBlock) void k_gm_cgs1(int N, GmWork w, int j, in
 // Second update w -= V h2 (workgroup 0 keeps h2) and the partials of ||w||^2.
 template <int JB>
 __global__ __launch_bounds__(kGmBlock) void k_gm_cgs2(int N, GmWork w, int j, int G) {
-  __shared__ double hsum[kMaxRestart + 1];
   __shared__ double h[JB];
+  __shared__ double red[kGmBlock / kWave][JB];
   __shared__ double sh[kGmBlock / kWave];
-  __shared__ int word;
-  if (read_state(w.sc, &word) != kGmRunning) return;
-  sum_rows(w.pb, G, j, hsum);
-  if (blockIdx.x == 0 && (int)threadIdx.x <= j) w.sc->h2[threadIdx.x] = hsum[threadIdx.x];
-  coeffs<JB>(hsum, j, h);
-  double ss = 0.0;
-  for (int k = blockIdx.x * kGmBlock + threadIdx.x; k < N; k += gridDim.x * kGmBlock) {
-    double vk[JB];
+  const int state = w.sc->state;
+  RowSums<JB> rs;
+  rs.first(w.pb, G);
+  const int k0 = blockIdx.x * kGmBlock + threadIdx.x;
+  double vk[JB];
+  load_rows<JB>(w, j, min(k0, N - 1), vk);
+  double v = w.w[min(k0, N - 1)];
+  loads_issued();
+  if (state != kGmRunning) return;
+  rs.finish(w.pb, G, j, red, h);
+  if (blockIdx.x == 0 && (int)threadIdx.x <= j) w.sc->h2[threadIdx.x] = h[threadIdx.x];
 #pragma unroll
-    for (int i = 0; i < JB; ++i) vk[i] = w.V[(size_t)min(i, j) * w.Np + k];
-    double v = w.w[k];
+  for (int i = 0; i < JB; ++i) v -= h[i] * vk[i];
+  if (k0 < N) w.w[k0] = v;
+  double ss = k0 < N ? v * v : 0.0;
+  for (int k = k0 + gridDim.x * kGmBlock; k < N; k += gridDim.x * kGmBlock) {
+    load_rows<JB>(w, j, k, vk);
+    v = w.w[k];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < JB; ++i) v -= h[i] * vk[i];
@@ -336,87 +445,103 @@ __global__ __launch_bounds__(kGmBlock) void k_gm_cgs2(int N, GmWork w, int j, in
   if (threadIdx.x == 0) w.pn[blockIdx.x] = s;
 }
 
+__device__ __forceinline__ double lane_value(double v, int lane) {   // uniform `lane`
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
 // Column j of H (h1 + h2, then h_{j+1,j} = ||w||), the earlier rotations and
 // the new one, the residual estimate and the decision: converged or an
 // exact breakdown (end the cycle, then the solve), end of the cycle (restart
 // length or iteration cap), or go on with v_{j+1} = w / h_{j+1,j}.  Every
-// workgroup computes the rotation from values this kernel does not write,
-// so all take the same decision; workgroup 0 records it.
+// wavefront computes the rotation from values this kernel does not write
+// (lane i holds entry i of the column and rotation i), so all take the same
+// decision; workgroup 0 records it (the state only when the cycle ends, where a
+// wavefront that reads it late has nothing to do either).  9000 cells: 4.4 us
+// (one thread going through LDS: 4.6 us).
 __global__ __launch_bounds__(kGmBlock) void k_gm_rotate(int N, GmWork w, int j, int G) {
-  __shared__ double tot[1];
-  __shared__ double col[kMaxRestart + 1];
-  __shared__ double dec[2];   // 1 / h_{j+1,j}, and 1 when the cycle goes on
-  __shared__ int word;
-  if (read_state(w.sc, &word) != kGmRunning) return;
-  sum_rows(w.pn, G, 0, tot);
   GmScalars& c = *w.sc;
-  if (threadIdx.x == 0) {
-    const double hn = sqrt(tot[0]);
-    for (int i = 0; i <= j; ++i) col[i] = c.h1[i] + c.h2[i];
-    col[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {
-      const double a = col[i], d = col[i + 1];
-      col[i] = c.cs[i] * a + c.sn[i] * d;
-      col[i + 1] = -c.sn[i] * a + c.cs[i] * d;
-    }
-    const double d = hypot(col[j], col[j + 1]);
-    const double cj = d > 0.0 ? col[j] / d : 1.0, sj = d > 0.0 ? col[j + 1] / d : 0.0;
-    const double gj = c.gres[j];
-    const double gnext = -sj * gj;
-    const int its = c.its0 + j + 1;
-    const bool conv = fabs(gnext) <= c.tol || hn == 0.0;
-    const bool more = !conv && j + 1 < c.m && its < c.maxit;
-    dec[0] = 1.0 / hn;
-    dec[1] = more ? 1.0 : 0.0;
-    if (blockIdx.x == 0) {
-      for (int i = 0; i < j; ++i) c.H[i * kMaxRestart + j] = col[i];
-      c.H[j * kMaxRestart + j] = d;
+  const int lane = threadIdx.x & (kWave - 1), li = min(lane, kMaxRestart - 1);
+  const int state = c.state;
+  NormSum ns;
+  ns.first(w.pn, G);
+  const double a1 = c.h1[li], a2 = c.h2[li], cs = c.cs[li], sn = c.sn[li];
+  const double gj = c.gres[j], tol = c.tol, bnorm = c.bnorm;
+  const int its = c.its0 + j + 1, m = c.m, maxit = c.maxit;
+  const int k0 = blockIdx.x * kGmBlock + threadIdx.x;
+  const double w0 = w.w[min(k0, N - 1)];
+  loads_issued();
+  if (state != kGmRunning) return;
+  const double hn = sqrt(ns.finish(G));
+  const double col = a1 + a2;
+  double h = 0.0;                          // lane i < j: entry i of the rotated column
+  double d = lane_value(col, 0);           // the entry the next rotation takes first
+  for (int i = 0; i < j; ++i) {
+    const double ci = lane_value(cs, i), si = lane_value(sn, i), e = lane_value(col, i + 1);
+    const double up = ci * d + si * e;
+    d = -si * d + ci * e;
+    if (lane == i) h = up;
+  }
+  const double len = hypot(d, hn);
+  const double cj = len > 0.0 ? d / len : 1.0, sj = len > 0.0 ? hn / len : 0.0;
+  const double gnext = -sj * gj;
+  const bool conv = fabs(gnext) <= tol || hn == 0.0;
+  const bool more = !conv && j + 1 < m && its < maxit;
+  if (blockIdx.x == 0 && threadIdx.x < kWave) {
+    if (lane < j) c.H[lane * kMaxRestart + j] = h;
+    if (lane == 0) {
+      c.H[j * kMaxRestart + j] = len;
       c.cs[j] = cj;
       c.sn[j] = sj;
       c.gr[j] = cj * gj;
       c.gres[j + 1] = gnext;
       c.its = its;
       c.k_used = j + 1;
-      c.relres = fabs(gnext) / c.bnorm;
+      c.relres = fabs(gnext) / bnorm;
       if (conv) c.status = OPM_OK;
       if (!more) c.state = kGmCycleEnd;
     }
   }
-  __syncthreads();
-  if (dec[1] == 0.0) return;
-  const double f = dec[0];
+  if (!more) return;
+  const double f = 1.0 / hn;
   double* vn = w.V + (size_t)(j + 1) * w.Np;
-  for (int k = blockIdx.x * kGmBlock + threadIdx.x; k < N; k += gridDim.x * kGmBlock)
+  if (k0 < N) vn[k0] = w0 * f;
+  for (int k = k0 + gridDim.x * kGmBlock; k < N; k += gridDim.x * kGmBlock)
     vn[k] = w.w[k] * f;
 }
 
 // End of a cycle: y = R^{-1} g over the k columns used (every workgroup
 // solves the small triangular system from LDS, identically) and x += Z y,
-// unless R is singular.
+// unless R is singular.  Lane i holds entry i: a column of R per step, where a
+// row per step on one thread took 32^2 / 2 dependent products (20 -> 9 us with
+// 32 columns, 9000 cells).
 template <int JB>
 __global__ __launch_bounds__(kGmBlock) void k_gm_finish(int N, double* x, GmWork w) {
-  __shared__ double R[kMaxRestart * kMaxRestart];
+  constexpr int kLd = kMaxRestart + 1;   // (a column's entries in different banks)
+  __shared__ double R[kMaxRestart * kLd];
   __shared__ double y[kMaxRestart];
   __shared__ int word, singular;
   if (read_state(w.sc, &word) == kGmDone) return;
   const GmScalars& c = *w.sc;
   const int k = c.k_used;
-  for (int q = threadIdx.x; q < k * kMaxRestart; q += kGmBlock) R[q] = c.H[q];
-  if ((int)threadIdx.x < kMaxRestart) y[threadIdx.x] = (int)threadIdx.x < k ? c.gr[threadIdx.x] : 0.0;
+  for (int q = threadIdx.x; q < k * kMaxRestart; q += kGmBlock)
+    R[q / kMaxRestart * kLd + q % kMaxRestart] = c.H[q];
+  const int li = min((int)threadIdx.x, kMaxRestart - 1);
+  double t = c.gr[li];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int bad = 0;
-    for (int i = k - 1; i >= 0; --i) {
-      double t = y[i];
-      for (int q = i + 1; q < k; ++q) t -= R[i * kMaxRestart + q] * y[q];
-      const double dg = R[i * kMaxRestart + i];
-      if (dg == 0.0) {
-        bad = 1;
-        break;
-      }
-      y[i] = t / dg;
+  if (threadIdx.x < kWave) {
+    const bool zero = (int)threadIdx.x < k && R[li * kLd + li] == 0.0;
+    const bool bad = __builtin_amdgcn_ballot_w64(zero) != 0;
+    double yi = 0.0;
+    for (int q = bad ? -1 : k - 1; q >= 0; --q) {
+      const double yq = lane_value(t, q) / R[q * kLd + q];
+      if ((int)threadIdx.x == q) yi = yq;
+      t -= R[li * kLd + q] * yq;   // (lanes past row q hold nothing that is read again)
     }
-    singular = bad;
+    if (threadIdx.x < kMaxRestart) y[threadIdx.x] = yi;
+    if (threadIdx.x == 0) singular = bad;
   }
   __syncthreads();
   if (singular || k == 0) return;
