@@ -8,8 +8,9 @@ namespace opm {
 
 // Device workspace: the quasi-IMPES weights, the pressure column of every
 // block of J (stored compactly for the second-stage residual), per level the
-// matrix values, diagonal, right-hand side, restricted-to-be residual and
-// smoothed solution, the inverse of the coarsest matrix, and the
+// matrix values, diagonal, right-hand side, pre-smoothed iterate,
+// restricted-to-be residual and smoothed solution, the inverse of the coarsest
+// matrix, the cycle's operator on the small levels at the bottom, and the
 // second-stage residual.
 struct CprWork {
   double* w;
@@ -17,9 +18,11 @@ struct CprWork {
   double* a[OPM_AMG_MAX_LEVELS];
   double* d[OPM_AMG_MAX_LEVELS];
   double* b[OPM_AMG_MAX_LEVELS];
+  double* x[OPM_AMG_MAX_LEVELS];
   double* res[OPM_AMG_MAX_LEVELS];
   double* y[OPM_AMG_MAX_LEVELS];
   double* inv;
+  double* tail;
   double* r2;
 };
 
