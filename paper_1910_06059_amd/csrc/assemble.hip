@@ -33,27 +33,46 @@ double* g_scratch_ptr[kScratchDevices] = {};
 
 using namespace asmdev;
 
+// The workgroup's share of the norms: components 0..2 by maximum, the others by
+// sum, in the order of block_max and block_sum; thread k < kNormStride returns
+// component k.  All components go through each exchange together (one of them
+// after the other costs ten times its latency and twenty barriers).
+// red: [kBlock / kWave][kNormStride]
+__device__ __forceinline__ double block_norms(double (&part)[kNormStride], double* red) {
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    double o[kNormStride];
+#pragma unroll
+    for (int k = 0; k < kNormStride; ++k) o[k] = __shfl_down(part[k], off, kWave);
+#pragma unroll
+    for (int k = 0; k < kNormStride; ++k)
+      part[k] = k < 3 ? nan_max(part[k], o[k]) : part[k] + o[k];
+  }
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < kNormStride; ++k) red[w * kNormStride + k] = part[k];
+  __syncthreads();
+  const int k = min((int)threadIdx.x, kNormStride - 1);
+  double s = k < 3 ? red[k] : 0.0 + red[k];
+  for (int q = 1; q < kBlock / kWave; ++q) {
+    const double v = red[q * kNormStride + k];
+    s = k < 3 ? nan_max(s, v) : s + v;
+  }
+  return s;
+}
+
 template <bool LIVE, bool WET = false>
 __global__ __launch_bounds__(kBlock) void k_assemble(AsmArgs a) {
-  __shared__ double sh[kBlock / kWave];
+  __shared__ double red[kBlock / kWave * kNormStride];
   const int i = blockIdx.x * kBlock + threadIdx.x;
   double part[kNormStride];
 #pragma unroll
   for (int k = 0; k < kNormStride; ++k) part[k] = 0.0;
   if (i < a.n) assemble_row<LIVE, WET>(a, i, a.dt, part);
   if (a.partials) {
-    double out[kNormStride];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) out[c] = block_max<kBlock>(part[c], sh);
-#pragma unroll
-    for (int k = 3; k < kNormStride; ++k) out[k] = block_sum<kBlock>(part[k], sh);
-    if (threadIdx.x < kNormStride) {
-      double v = out[0];
-#pragma unroll
-      for (int k = 1; k < kNormStride; ++k)
-        if ((int)threadIdx.x == k) v = out[k];
-      a.partials[(size_t)blockIdx.x * kNormStride + threadIdx.x] = v;
-    }
+    const double v = block_norms(part, red);
+    if (threadIdx.x < kNormStride) a.partials[(size_t)blockIdx.x * kNormStride + threadIdx.x] = v;
   }
 }
 
@@ -137,7 +156,6 @@ struct TileFaceLds {
   double p[kSlots], z[kSlots];
   double b[kSlots], mv[kSlots], m1[kSlots], m2[kSlots];
   double ex[3][7][kTile];   // face (L, own) of each lane's -x, -y, -z face
-  int32_t cell[kSlots];
 };
 constexpr int kWaveStage = (int)(sizeof(TileFaceLds) / sizeof(double)) / (kTile / kWave);
 static_assert(kWaveStage >= 4 * kRunStage, "four x-runs of block rows per wavefront");
@@ -146,7 +164,7 @@ struct TileLds {
     TileFaceLds f;
     double rows[kTile / kWave][kWaveStage];
   } u;
-  double red[kBlock / kWave];
+  double red[kBlock / kWave * kNormStride];
 };
 
 // Flux of component a from the lower cell L to the upper cell H (eqs. flux1,
@@ -228,39 +246,39 @@ __global__ __launch_bounds__(kBlock, 2) void k_assemble_tiled(TileArgs a) {
   const int t = blockIdx.x;
   const int x0 = (t % a.tiles_x) * kTX, y0 = ((t / a.tiles_x) % a.tiles_y) * kTY,
             z0 = (t / (a.tiles_x * a.tiles_y)) * kTZ;
+  // Everything the tile reads is asked for in four steps, each all at once and
+  // ahead of the arithmetic: cells, their values and row starts, the faces of
+  // the six blocks, their transmissibilities (what a lane lacks is read from a
+  // place that exists: no branch between the loads).  A tile holds its lanes'
+  // block rows in registers, two wavefronts per SIMD, so that these latencies,
+  // and not bytes or arithmetic, bound the kernel.
+  // (cells are looked up where they exist: out of the lattice at the origin)
   auto cell_at = [&](int x, int y, int z) -> int {
-    if (x < 0 || y < 0 || z < 0 || x >= a.nx || y >= a.ny || z >= a.nz) return -1;
-    return a.box_cell[x + a.nx * (y + a.ny * z)];
+    const bool in = x >= 0 && y >= 0 && z >= 0 && x < a.nx && y < a.ny && z < a.nz;
+    const int v = a.box_cell[in ? x + a.nx * (y + a.ny * z) : 0];
+    return in ? v : -1;
   };
   // ---- phase 1: properties of the own cell and of one halo cell
-  const int c = cell_at(x0 + lx, y0 + ly, z0 + lz);
+  const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
+  const int c = cell_at(gx, gy, gz);
   int hx, hy, hz;
   halo_coord(l, hx, hy, hz);
   const int ch = cell_at(x0 + hx, y0 + hy, z0 + hz);
-  TileProps P, Ph;
+  // the six neighbours: -x, +x, -y, +y, -z, +z
+  const int near[6] = {cell_at(gx - 1, gy, gz), cell_at(gx + 1, gy, gz), cell_at(gx, gy - 1, gz),
+                       cell_at(gx, gy + 1, gz), cell_at(gx, gy, gz - 1), cell_at(gx, gy, gz + 1)};
   const int cs = c >= 0 ? c : 0, chs = ch >= 0 ? ch : 0;
-  tile_props(f, a.y[3 * cs], a.y[3 * cs + 1], a.y[3 * cs + 2], P);
-  tile_props(f, a.y[3 * chs], a.y[3 * chs + 1], a.y[3 * chs + 2], Ph);
-  S.u.f.p[l] = P.p;
-  S.u.f.p[kTile + l] = Ph.p;
-  S.u.f.z[l] = a.depth[cs];
-  S.u.f.z[kTile + l] = a.depth[chs];
-  // slots of the six neighbours: -x, +x, -y, +y, -z, +z
-  int nb[6];
-  nb[0] = lx > 0 ? l - 1 : kTile + (ly + kTY * lz);
-  nb[1] = lx < kTX - 1 ? l + 1 : kTile + 32 + (ly + kTY * lz);
-  nb[2] = ly > 0 ? l - kTX : kTile + 64 + (lx + kTX * lz);
-  nb[3] = ly < kTY - 1 ? l + kTX : kTile + 96 + (lx + kTX * lz);
-  nb[4] = lz > 0 ? l - kTX * kTY : kTile + 128 + (lx + kTX * ly);
-  nb[5] = lz < kTZ - 1 ? l + kTX * kTY : kTile + 192 + (lx + kTX * ly);
-  S.u.f.cell[l] = c;
-  S.u.f.cell[kTile + l] = ch;
-  __syncthreads();
+  const int q0 = a.row_ptr[cs];
+  const double y0v = a.y[3 * cs], y1v = a.y[3 * cs + 1], y2v = a.y[3 * cs + 2];
+  const double h0v = a.y[3 * chs], h1v = a.y[3 * chs + 1], h2v = a.y[3 * chs + 2];
+  const double zo = a.depth[cs], zh = a.depth[chs];
+  const double pv = a.pv[cs];
+  const double old[3] = {a.acc0[3 * cs], a.acc0[3 * cs + 1], a.acc0[3 * cs + 2]};
+  const int w0 = a.cell_conn_ptr[cs], w1 = a.cell_conn_ptr[cs + 1];
   bool has[6];
 #pragma unroll
-  for (int d = 0; d < 6; ++d) has[d] = c >= 0 && S.u.f.cell[nb[d]] >= 0;
+  for (int d = 0; d < 6; ++d) has[d] = c >= 0 && near[d] >= 0;
   // block positions in the row: (-z, -y, -x, diag, +x, +y, +z) by column
-  const int q0 = c >= 0 ? a.row_ptr[c] : 0;
   int qn[6];
   qn[4] = q0;
   qn[2] = qn[4] + (has[4] ? 1 : 0);
@@ -269,9 +287,29 @@ __global__ __launch_bounds__(kBlock, 2) void k_assemble_tiled(TileArgs a) {
   qn[1] = qd + 1;
   qn[3] = qn[1] + (has[1] ? 1 : 0);
   qn[5] = qn[3] + (has[3] ? 1 : 0);
+  int face[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d) face[d] = a.blk_face[has[d] ? qn[d] : q0];
   double T[6];
 #pragma unroll
-  for (int d = 0; d < 6; ++d) T[d] = has[d] ? a.trans[a.blk_face[qn[d]]] : 0.0;
+  for (int d = 0; d < 6; ++d) T[d] = *(has[d] ? a.trans + face[d] : a.pv + cs);
+#pragma unroll
+  for (int d = 0; d < 6; ++d) T[d] = has[d] ? T[d] : 0.0;
+  TileProps P, Ph;
+  tile_props(f, y0v, y1v, y2v, P);
+  tile_props(f, h0v, h1v, h2v, Ph);
+  S.u.f.p[l] = P.p;
+  S.u.f.p[kTile + l] = Ph.p;
+  S.u.f.z[l] = zo;
+  S.u.f.z[kTile + l] = zh;
+  // slots of the six neighbours: -x, +x, -y, +y, -z, +z
+  int nb[6];
+  nb[0] = lx > 0 ? l - 1 : kTile + (ly + kTY * lz);
+  nb[1] = lx < kTX - 1 ? l + 1 : kTile + 32 + (ly + kTY * lz);
+  nb[2] = ly > 0 ? l - kTX : kTile + 64 + (lx + kTX * lz);
+  nb[3] = ly < kTY - 1 ? l + kTX : kTile + 96 + (lx + kTX * lz);
+  nb[4] = lz > 0 ? l - kTX * kTY : kTile + 128 + (lx + kTX * ly);
+  nb[5] = lz < kTZ - 1 ? l + kTX * kTY : kTile + 192 + (lx + kTX * ly);
   // a lane computes its lower faces, and its upper faces whose cell is in
   // the halo; the other upper faces arrive from the neighbour's lane
   const bool up_halo[3] = {lx == kTX - 1, ly == kTY - 1, lz == kTZ - 1};
@@ -354,7 +392,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_assemble_tiled(TileArgs a) {
 #pragma unroll
   for (int k = 0; k < kNormStride; ++k) part[k] = 0.0;
   if (c >= 0) {
-    const double pv = a.pv[c];
     const double w = pv / a.dt;
     const double so = (1.0 - P.sw) - P.sg;
     const double s[3] = {P.sw, so, P.sg};
@@ -375,11 +412,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_assemble_tiled(TileArgs a) {
     double rr[3], dd[9];
 #pragma unroll
     for (int al = 0; al < 3; ++al) {
-      rr[al] = (acc[al][0] - a.acc0[3 * c + al]) * w;
+      rr[al] = (acc[al][0] - old[al]) * w;
 #pragma unroll
       for (int v = 0; v < 3; ++v) dd[3 * al + v] = acc[al][1 + v] * w;
     }
-    for (int tq = a.cell_conn_ptr[c]; tq < a.cell_conn_ptr[c + 1]; ++tq) {
+    for (int tq = w0; tq < w1; ++tq) {
       const int k = a.cell_conn[tq];
       if (a.conn_kind[k] == OPM_WELL_RATE_INJ) {
         const int ph = a.conn_phase[k];
@@ -418,18 +455,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_assemble_tiled(TileArgs a) {
     part[9] = pv;
   }
   if (a.partials) {
-    double out[kNormStride];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) out[k] = block_max<kBlock>(part[k], S.red);
-#pragma unroll
-    for (int k = 3; k < kNormStride; ++k) out[k] = block_sum<kBlock>(part[k], S.red);
-    if (l < kNormStride) {
-      double v = out[0];
-#pragma unroll
-      for (int k = 1; k < kNormStride; ++k)
-        if (l == k) v = out[k];
-      a.partials[(size_t)blockIdx.x * kNormStride + l] = v;
-    }
+    const double v = block_norms(part, S.red);
+    if (l < kNormStride) a.partials[(size_t)blockIdx.x * kNormStride + l] = v;
   }
   // ---- phase 4: the block rows.  The rows of an x-run of the tile are
   // consecutive in J; each run's rows are staged in LDS in J's order and the
@@ -502,22 +529,29 @@ __global__ __launch_bounds__(kBlock, 2) void k_assemble_tiled(TileArgs a) {
 // (CNV_w, CNV_o, CNV_g, MB_w, MB_o, MB_g, max CNV, max MB).
 __global__ __launch_bounds__(kBlock) void k_norms_final(const double* partials, int nblk, int n,
                                                          double dt, double* norms) {
-  __shared__ double sh[kBlock / kWave];
+  __shared__ double red[kBlock / kWave * kNormStride];
+  __shared__ double out[kNormStride];
   double part[kNormStride];
 #pragma unroll
   for (int k = 0; k < kNormStride; ++k) part[k] = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += kBlock) {
-    const double* pb = partials + (size_t)b * kNormStride;
+  // four partials of a thread at a time in flight
+  for (int b = threadIdx.x; b < nblk; b += 4 * kBlock) {
+    double v[4][kNormStride];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) part[c] = nan_max(part[c], pb[c]);
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int k = 3; k < kNormStride; ++k) part[k] += pb[k];
+      for (int k = 0; k < kNormStride; ++k)
+        v[u][k] = partials[(size_t)min(b + u * kBlock, nblk - 1) * kNormStride + k];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (b + u * kBlock < nblk)
+#pragma unroll
+        for (int k = 0; k < kNormStride; ++k)
+          part[k] = k < 3 ? nan_max(part[k], v[u][k]) : part[k] + v[u][k];
   }
-  double out[kNormStride];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) out[c] = block_max<kBlock>(part[c], sh);
-#pragma unroll
-  for (int k = 3; k < kNormStride; ++k) out[k] = block_sum<kBlock>(part[k], sh);
+  const double tot = block_norms(part, red);
+  if (threadIdx.x < kNormStride) out[threadIdx.x] = tot;
+  __syncthreads();
   if (threadIdx.x == 0) {
     double cmax = 0.0, mmax = 0.0;
     for (int c = 0; c < 3; ++c) {
