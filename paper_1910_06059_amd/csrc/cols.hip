@@ -75,7 +75,11 @@ __global__ __launch_bounds__(256) void k_cols_slots(ColView<T> v, FacIn f) {
   const int k = box / (g.nbx * g.nby) * g.bz + kk;
   FacSlot rec{{kNoBlock, kNoBlock, kNoBlock}, kNoBlock, {kNoBlock, kNoBlock, kNoBlock}, 0};
   int cell = -1;
-  if (c < g.bx * g.by && gi < g.nx && gj < g.ny && kk >= 0 && kk < g.bz && k < g.nz) {
+  if (c >= g.bx * g.by || kk < 0 || kk >= g.bz) {   // (no record is read there)
+    v.idx[slot] = 0;
+    return;
+  }
+  if (gi < g.nx && gj < g.ny && k < g.nz) {
     const int sxy = g.nx * g.ny;
     const int32_t* b = f.box_cell + gi + g.nx * gj + (size_t)sxy * k;
     cell = b[0];
@@ -100,7 +104,7 @@ __global__ __launch_bounds__(256) void k_cols_slots(ColView<T> v, FacIn f) {
     }
   }
   v.fac[slot] = rec;
-  v.idx[slot] = cell + 1;
+  v.idx[slot] = 24 * (cell + 1);
 }
 
 // three consecutive doubles
@@ -139,9 +143,9 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
   const int vslot = ln.c < C ? ln.c * 32 : kOut;
   auto slot_at = [&](int s) {
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    const int so = min(s, L - 1) * C * 32;
-    const u4 p = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vslot, so, 0));
-    const u4 q = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vslot, so + 16, 0));
+    const int l = min(s, L - 1), so = l * C * 32, vs = ln.at(l, g.bz) ? vslot : kOut;
+    const u4 p = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vs, so, 0));
+    const u4 q = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vs, so + 16, 0));
     return FacSlot{{p[0], p[1], p[2]}, p[3], {q[0], q[1], q[2]}, (int)q[3]};
   };
   // HALO exchange: the scaled upper blocks of the boundary columns
@@ -163,13 +167,15 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
   const __amdgpu_buffer_rsrc_t rdy =
       col_rsrc(HALO ? v.euy + (size_t)box * (szy / 8) : nullptr, HALO ? szy : 0);
   auto data = [&](int s, const FacSlot& r, FacRow& b) __attribute__((always_inline)) {
-    load3(rj, r.diag + 24u * a, b.D);
+    const unsigned none = ln.at(min(s, L - 1), g.bz) ? 0u : kNoBlock;   // (sets every bit that matters)
+    load3(rj, (r.diag | none) + 24u * a, b.D);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) load3(rj, r.lo[q] + 24u * a, b.lo[q]);
+    for (int q = 0; q < 3; ++q) load3(rj, (r.lo[q] | none) + 24u * a, b.lo[q]);
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
-      for (int e = 0; e < 3; ++e) b.up[q][e] = col_load<double>(rj, (int)(r.up[q] + 8u * a) + 24 * e);
+      for (int e = 0; e < 3; ++e)
+        b.up[q][e] = col_load<double>(rj, (int)((r.up[q] | none) + 8u * a) + 24 * e);
     if (HALO) {
       const int l = min(s, L - 1);
 #pragma unroll
@@ -203,14 +209,16 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
         }
         break;
       }
-      if (miss) {
-        miss = false;
+      const double *px = wx ? srcx + ox / 8 : v.eux, *py = wy ? srcy + oy / 8 : v.euy;
+      double hx[3], hy[3];
+      coherent_poll(px, px + 1, px + 2, py, py + 1, py + 2, hx[0], hx[1], hx[2], hy[0], hy[1],
+                      hy[2]);
+      miss = false;
 #pragma unroll
-        for (int e = 0; e < 3; ++e) {
-          if (wx) b.hx[e] = coherent_reread(srcx + ox / 8 + e);
-          if (wy) b.hy[e] = coherent_reread(srcy + oy / 8 + e);
-          miss = miss || (wx && is_unset(b.hx[e])) || (wy && is_unset(b.hy[e]));
-        }
+      for (int e = 0; e < 3; ++e) {
+        if (wx) b.hx[e] = hx[e];
+        if (wy) b.hy[e] = hy[e];
+        miss = miss || (wx && is_unset(hx[e])) || (wy && is_unset(hy[e]));
       }
       if ((it & 63) == 63 &&
           __hip_atomic_load(v.gave_up + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
@@ -254,7 +262,7 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
     data(s + DEPTH, slots[(qq + DEPTH) % 6], rows[(qq + DEPTH) % ND]);
     const FacRow& b = rows[qq % ND];
     const FacSlot& r = slots[qq % 6];
-    const bool live = r.diag != kNoBlock && ln.c < C;
+    const bool live = ln.at(s, g.bz) && r.diag != kNoBlock;
     double D[3] = {b.D[0], b.D[1], b.D[2]};
     auto update = [&](const double* A, const double* U) {
 #pragma unroll
@@ -333,6 +341,8 @@ __global__ __launch_bounds__(256) void k_cols_records(ColView<T> v, FacIn f) {
   const size_t slot = (size_t)blockIdx.x * 64 + threadIdx.x / 4;
   const int a = (int)(threadIdx.x & 3u);
   if (slot >= g.slots() || a == 3) return;
+  const int col = (int)(slot % g.C), kk = (int)(slot / g.C % g.L) - col % g.bx - col / g.bx;
+  if (col >= g.bx * g.by || kk < 0 || kk >= g.bz) return;   // (never read)
   const FacSlot r = v.fac[slot];
   const bool live = r.diag != kNoBlock;
   double di[3];
@@ -550,7 +560,7 @@ ColGrid make_grid(const opm_problem* pb, int bx, int by, int bz, bool halo) {
 template <typename T>
 size_t apply_lds(const ColGrid& g) {
   const size_t rows = threads_of(g) / 4 + 1 + (g.halo ? kHaloRows : 0);
-  return sizeof(T) * 8 * rows + (g.halo ? 0 : sizeof(T) * 3 * (size_t)g.L * g.C);
+  return sizeof(T) * 8 * rows + (g.halo ? 0 : sizeof(T) * (3 * (size_t)g.L * g.C + 1));
 }
 size_t factor_lds(const ColGrid& g) {
   const size_t rows = threads_of(g) / 4 + 1 + (g.halo ? kHaloRows : 0);

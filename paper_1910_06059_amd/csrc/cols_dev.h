@@ -79,7 +79,7 @@ struct ColView {
   ColGrid g;
   T* rec_f;            // [box][L][12 values as chunks][C][3]
   T* rec_b;            // [box][L][8 values as chunks, then one][C][3]
-  int32_t* idx;        // [box][L][C] cell + 1, 0: none
+  int32_t* idx;        // [box][L][C] 24 (cell + 1): past the cell's values, 0: none
   FacSlot* fac;        // [box][L][C]
   T* z;                // HALO: [box][L][C][3] forward results
   T* ex[2];            // HALO: [box][bz][by][3] of the forward / backward sweep
@@ -148,6 +148,46 @@ __device__ __forceinline__ float coherent_reread(const float* p) {
   asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
   return __builtin_bit_cast(float, b);
 }
+// All the values of a poll in one round trip.
+__device__ __forceinline__ void coherent_poll(const double* p0, const double* p1,
+                                                const double* p2, const double* p3,
+                                                const double* p4, const double* p5, double& v0,
+                                                double& v1, double& v2, double& v3, double& v4,
+                                                double& v5) {
+  unsigned long long b0, b1, b2, b3, b4, b5;
+  asm volatile(
+      "global_load_dwordx2 %0, %6, off sc1\n\tglobal_load_dwordx2 %1, %7, off sc1\n\t"
+      "global_load_dwordx2 %2, %8, off sc1\n\tglobal_load_dwordx2 %3, %9, off sc1\n\t"
+      "global_load_dwordx2 %4, %10, off sc1\n\tglobal_load_dwordx2 %5, %11, off sc1\n\t"
+      "s_waitcnt vmcnt(0)"
+      : "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3), "=&v"(b4), "=&v"(b5)
+      : "v"(p0), "v"(p1), "v"(p2), "v"(p3), "v"(p4), "v"(p5));
+  v0 = __builtin_bit_cast(double, b0);
+  v1 = __builtin_bit_cast(double, b1);
+  v2 = __builtin_bit_cast(double, b2);
+  v3 = __builtin_bit_cast(double, b3);
+  v4 = __builtin_bit_cast(double, b4);
+  v5 = __builtin_bit_cast(double, b5);
+}
+__device__ __forceinline__ void coherent_poll(const float* p0, const float* p1, const float* p2,
+                                                const float* p3, const float* p4, const float* p5,
+                                                float& v0, float& v1, float& v2, float& v3,
+                                                float& v4, float& v5) {
+  unsigned b0, b1, b2, b3, b4, b5;
+  asm volatile(
+      "global_load_dword %0, %6, off sc1\n\tglobal_load_dword %1, %7, off sc1\n\t"
+      "global_load_dword %2, %8, off sc1\n\tglobal_load_dword %3, %9, off sc1\n\t"
+      "global_load_dword %4, %10, off sc1\n\tglobal_load_dword %5, %11, off sc1\n\t"
+      "s_waitcnt vmcnt(0)"
+      : "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3), "=&v"(b4), "=&v"(b5)
+      : "v"(p0), "v"(p1), "v"(p2), "v"(p3), "v"(p4), "v"(p5));
+  v0 = __builtin_bit_cast(float, b0);
+  v1 = __builtin_bit_cast(float, b1);
+  v2 = __builtin_bit_cast(float, b2);
+  v3 = __builtin_bit_cast(float, b3);
+  v4 = __builtin_bit_cast(float, b4);
+  v5 = __builtin_bit_cast(float, b5);
+}
 
 // Value of lane K of the lane's quad (DPP quad permutation: a VALU move, no
 // LDS round trip).
@@ -194,6 +234,7 @@ struct BlockRhs {
 // quad holds none).
 struct ColLane {
   int c, eq, ci, cj;
+  int lag;       // level of the column's first cell (far past the last level: no column)
   bool in_box;   // a column of the box, eq < 3
   __device__ __forceinline__ explicit ColLane(const ColGrid& g) {
     const int tid = (int)threadIdx.x;
@@ -202,6 +243,11 @@ struct ColLane {
     in_box = c < g.bx * g.by && eq < 3;
     cj = c / g.bx;
     ci = c - cj * g.bx;
+    lag = c < g.bx * g.by ? ci + cj : 1 << 29;
+  }
+  // the column has a place on level l
+  __device__ __forceinline__ bool at(int l, int bz) const {
+    return (unsigned)(l - lag) < (unsigned)bz;
   }
 };
 
@@ -235,7 +281,8 @@ struct ColJob {
 
 // One sweep of box `box` by the workgroup of NT threads.
 //   nb: LDS rows (col_rows_bytes), all zero on entry to the forward sweep
-//   zl: !HALO: the box's forward results in LDS, [L][C][3]
+//   zl: !HALO: the box's forward results in LDS, [L][C][3] and one value more
+//   (written by the lanes that hold none)
 // DEPTH levels of loads are in flight while a level is computed.
 // No branch separates a load from its use: what a lane does not need lies
 // past the end of its buffer, reads zero and costs no traffic.
@@ -251,7 +298,9 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
   // over 2 ND, so that every ring slot is a register of its own
   constexpr int ND = DEPTH + 1, P = 2 * ND;
   const ColGrid& g = v.g;
-  const int L = g.L, C = g.C;
+  // (one and two wavefronts: every column of the workgroup, so that the
+  // distances between the chunks of a record are constants of the loads)
+  const int L = g.L, C = NT <= 128 ? NT / 4 : g.C;
   const ColLane ln(g);
   const int a = min(ln.eq, 2);
   constexpr int kOut = (int)0x80000000;   // an offset past the end of any buffer here
@@ -264,7 +313,7 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
   const int vrec = stored ? (ln.c * 3 + a) * 16 : kOut;
   const int vlast = stored ? (ln.c * 3 + a) * ts : kOut;   // backward: the ninth value
   const int vidx = stored ? ln.c * 4 : kOut;
-  const int vcell = a * 8 - 24;           // + 24 ix: this equation of the cell
+  const int vcell = a * 8 - 24;           // + its index: this equation of the cell
   const size_t vec_bytes = 24 * (size_t)g.n;
   const __amdgpu_buffer_rsrc_t rz =
       col_rsrc(HALO ? v.z + (size_t)box * L * C * 3 : nullptr, HALO ? (size_t)L * C * 3 * ts : 0);
@@ -308,14 +357,37 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     const int sc = min(s, L - 1);
     return FWD ? sc : L - 1 - sc;
   };
-  auto load_idx = [&](int s) { return col_load<int>(ridx, vidx, level(s) * C * 4); };
+  // With one wavefront a step is its instructions more than anything else (156
+  // ns of 70 instructions; 53 of them, the loads' chunks at constant distances
+  // and these offsets carried along, take 138 ns), so what can be carried from one to the next is: the byte offsets of
+  // the next level to load (the last one again past the end), the lane's place in
+  // its column there and the place of its forward result.  Nothing is loaded for
+  // a column on levels above and below it: a box has bx + by - 2 more levels than
+  // bz (6 of 56 for 4 x 4 x 50 cells).
+  const int last_idx = (L - 1) * C * 4, last_rec = (L - 1) * rb;
+  int so_idx = 0, so_rec = 0;   // (backward: from the last level down)
+  int kk = (FWD ? 0 : L - 1) - ln.lag;
+  auto load_idx = [&]() __attribute__((always_inline)) {
+    const int i = col_load<int>(ridx, vidx, FWD ? so_idx : last_idx - so_idx);
+    so_idx = min(so_idx + C * 4, last_idx);
+    return i;
+  };
+  Lds<T>* zp = HALO ? nullptr
+                    : zl + (stored ? ((FWD ? 0 : L - 1) * C + ln.c) * 3 + a : L * C * 3);
+  const int zstep = HALO || !stored ? 0 : FWD ? C * 3 : -C * 3;
   auto data = [&](int s, int ix, ColJob<T>& j, auto next_idx) __attribute__((always_inline)) {
-    const int l = level(s), so = l * rb;
+    const int l = level(s), so = FWD ? so_rec : last_rec - so_rec;   // (l: HALO)
+    const bool at = (unsigned)kk < (unsigned)g.bz;
+    const int vr = at ? vrec : kOut;
+    so_rec = min(so_rec + rb, last_rec);
+    kk += FWD ? 1 : -1;
     // 8 or 12 values in whole chunks (backward: the ninth follows them)
 #pragma unroll
     for (int c = 0; c < (FWD ? 12 : 8) / kV; ++c) {
       const V w = __builtin_bit_cast(
-          V, __builtin_amdgcn_raw_buffer_load_b128(rrec, vrec, so + c * C * 48, 0));
+          V, NT <= 128
+                 ? __builtin_amdgcn_raw_buffer_load_b128(rrec, vr + c * C * 48, so, 0)
+                 : __builtin_amdgcn_raw_buffer_load_b128(rrec, vr, so + c * C * 48, 0));
 #pragma unroll
       for (int e = 0; e < kV; ++e) {
         if (c * kV + e < 9)
@@ -324,9 +396,9 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
           j.d[c * kV + e - 9] = w[e];
       }
     }
-    if (!FWD) j.a[8] = col_load<T>(rrec, vlast, so + 8 * C * 3 * ts);
+    if (!FWD) j.a[8] = col_load<T>(rrec, at ? vlast : kOut, so + 8 * C * 3 * ts);
     if (FWD) {
-      const int off = ix * 24 + vcell;
+      const int off = ix + vcell;
       auto ld = [&](const double* base) { return col_load<double>(col_rsrc(base, vec_bytes), off); };
       if (MODE == kry::kFuseNone) j.u[0] = ld(q.r);
       if (MODE == kry::kFuseBegin) {
@@ -339,7 +411,7 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
         j.u[1] = ld(q.f.v);
       }
     } else if (HALO) {
-      j.z = col_load<T>(rz, vz, l * C * 3 * ts);
+      j.z = col_load<T>(rz, at ? vz : kOut, l * C * 3 * ts);
     }
     if (HALO) {
       j.hx = col_load<T, kCoherent>(rsx, get_x + l * sx);
@@ -366,6 +438,19 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     bool miss = (wait_x && is_unset(hx)) || (wait_y && is_unset(hy));
     if (v.spin == 0 && (wait_x || wait_y)) miss = true;
     if (__builtin_amdgcn_ballot_w64(miss) != 0) {
+      // a poll reads the values of this step and of the loaded ones behind it
+      // (a lane or step without one: the array's first value, not used)
+      static_assert(DEPTH == 3, "the values of a poll");
+      const T *px[DEPTH], *py[DEPTH];
+      bool wx[DEPTH], wy[DEPTH];
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+        const int lu = level(s + u), ux = get_x + lu * sx, uy = get_y + lu * sy;
+        wx[u] = in_range(ux, szx);
+        wy[u] = in_range(uy, szy);
+        px[u] = wx[u] ? srcx + ux / ts : v.ex[FWD ? 0 : 1];
+        py[u] = wy[u] ? srcy + uy / ts : v.ey[FWD ? 0 : 1];
+      }
       for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
         if (it >= v.spin || lost) {
           lost = true;
@@ -377,23 +462,19 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
                              __HIP_MEMORY_SCOPE_AGENT);
           break;
         }
-        if (miss) {
-          if (wait_x) hx = coherent_reread(srcx + ox / ts);
-          if (wait_y) hy = coherent_reread(srcy + oy / ts);
-          miss = (wait_x && is_unset(hx)) || (wait_y && is_unset(hy));
-        }
+        T x0, x1, x2, y0, y1, y2;
+        coherent_poll(px[0], py[0], px[1], py[1], px[2], py[2], x0, y0, x1, y1, x2, y2);
+        if (wx[0]) hx = x0;
+        if (wy[0]) hy = y0;
+        ColJob<T>&j1 = jobs[(slot + 1) % ND], &j2 = jobs[(slot + 2) % ND];
+        if (wx[1]) j1.hx = x1;
+        if (wy[1]) j1.hy = y1;
+        if (wx[2]) j2.hx = x2;
+        if (wy[2]) j2.hy = y2;
+        miss = (wx[0] && is_unset(hx)) || (wy[0] && is_unset(hy));
         if ((it & 63) == 63 && __hip_atomic_load(v.gave_up + (FWD ? 0 : 1), __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT) != 0)
           lost = true;
-      }
-      // the steps behind it that are already loaded
-#pragma unroll
-      for (int u = 1; u < DEPTH; ++u) {
-        ColJob<T>& j = jobs[(slot + u) % ND];
-        const int lu = level(s + u);
-        const int px = get_x + lu * sx, py = get_y + lu * sy;
-        if (in_range(px, szx)) j.hx = coherent_reread(srcx + px / ts);
-        if (in_range(py, szy)) j.hy = coherent_reread(srcy + py / ts);
       }
     }
     Lds<T>* h = nb + par * 4 * R::kRows + 4 * R::kHalo + ln.eq;
@@ -401,10 +482,10 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     if (ln.in_box && edge_j) h[4 * (g.by + ln.ci)] = hy;
   };
 
-  int idx[P];   // cell + 1, 0: none
+  int idx[P];
   // prologue: the data of steps 0 .. DEPTH-1, their indices and the ND after
 #pragma unroll
-  for (int s = 0; s < DEPTH + ND; ++s) idx[s] = load_idx(s);
+  for (int s = 0; s < DEPTH + ND; ++s) idx[s] = load_idx();
 #pragma unroll
   for (int s = 0; s < DEPTH; ++s) data(s, idx[s], jobs[s], []() {});
   // with the first levels' loads in flight: the decisions that need the
@@ -422,7 +503,7 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     const T xj0 = wj[0], xj1 = wj[1], xj2 = wj[2];
     __builtin_amdgcn_sched_barrier(0);
     data(s + DEPTH, idx[(qq + DEPTH) % P], jobs[(qq + DEPTH) % ND],
-         [&]() { idx[(qq + DEPTH + ND) % P] = load_idx(s + DEPTH + ND); });
+         [&]() { idx[(qq + DEPTH + ND) % P] = load_idx(); });
     const ColJob<T>& j = jobs[qq % ND];
     const int ix = idx[qq];
     const int l = level(s);
@@ -439,20 +520,22 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
       o = sub_dot3(o, j.a + 3, xj0, xj1, xj2);
       o = sub_dot3(o, j.a + 6, xi0, xi1, xi2);
     } else {
-      o = HALO ? j.z : zl[(l * C + min(ln.c, C - 1)) * 3 + a];
+      o = HALO ? j.z : *zp;
+      if (!HALO) zp += zstep;
       o = sub_dot3(o, j.a, xi0, xi1, xi2);
       o = sub_dot3(o, j.a + 3, xj0, xj1, xj2);
       o = sub_dot3(o, j.a + 6, xk0, xk1, xk2);
     }
     out = ix != 0 ? o : (T)0;
     nb[((qq & 1) ^ 1) * 4 * R::kRows + 4 * ln.c + ln.eq] = out;
-    const int off = ix * 24 + vcell;
+    const int off = ix + vcell;
     if (HALO) {
       col_store<kCoherent>(out, rdx, put_x + l * sx);
       col_store<kCoherent>(out, rdy, put_y + l * sy);
-      if (FWD) col_store(out, rz, vz, l * C * 3 * ts);
-    } else if (FWD && stored) {
-      zl[(l * C + ln.c) * 3 + a] = out;
+      if (FWD) col_store(out, rz, ix != 0 ? vz : kOut, l * C * 3 * ts);
+    } else if (FWD) {
+      *zp = out;
+      zp += zstep;
     }
     if (!FWD) col_store((double)out, col_rsrc(x, vec_bytes), off);
     if (FWD && MODE == kry::kFuseBegin) col_store(u, col_rsrc(q.f.p, vec_bytes), off);
@@ -463,13 +546,20 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     receive(s + 1, (qq + 1) % ND, (qq & 1) ^ 1);
     level_barrier<NT>();
   };
-  for (int s = 0;; s += P) {
+  // (the last levels apart: an exit inside the loop meets its back edge in the
+  // compiled code, which then waits there as for the loads of the shortest way)
+  int s = 0;
+#pragma clang loop unroll(disable)
+  for (; s + P <= L; s += P) {
 #pragma unroll
-    for (int qq = 0; qq < P; ++qq) {
-      step(s + qq, qq);
-      if (s + qq + 1 >= L) return true;
-    }
+    for (int qq = 0; qq < P; ++qq) step(s + qq, qq);
   }
+#pragma unroll
+  for (int qq = 0; qq < P; ++qq) {
+    if (s + qq >= L) return true;
+    step(s + qq, qq);
+  }
+  return true;
 }
 
 }  // namespace ilu
