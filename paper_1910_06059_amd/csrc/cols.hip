@@ -42,7 +42,9 @@ inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 //    and its products in the chain).
 // Factorisation with its records, by HIP events, against the recursion by
 // position and a packing pass: 9000 cells 40.2 -> 25.7 us, 500k cells
-// (4x4x50 boxes) 304 -> 201 us FP64.
+// (4x4x50 boxes) 304 -> 201 us FP64.  Whole lattices, the exchange in the
+// computing wavefronts -> beside them: 30 x 30 x 10 165 -> 109 us, 100 x 100 x 50
+// 875 -> 766 us.
 struct FacIn {
   const double* J;
   const int32_t* row_ptr;
@@ -119,10 +121,64 @@ __device__ __forceinline__ void load3(__amdgpu_buffer_rsrc_t r, unsigned off, do
 struct FacRow {
   double lo[3][3], D[3];   // row a of the lower blocks (k-, j-, i-) and of the diagonal
   double up[3][3];         // column a of the upper blocks (i+, j+, k+)
-  double hx[3], hy[3];     // HALO: column a of the neighbouring tiles' scaled upper blocks
 };
+// The exchange of a tile's factorisation, by two wavefronts as in the sweeps
+// (tile_send, tile_receive): the scaled upper blocks of the edge columns, three
+// values per lane.
+template <typename R, int kB>
+__device__ __forceinline__ void factor_send(const ColGrid& g, double* eux, double* euy, int box,
+                                            const Lds<double>* ui, const Lds<double>* uj) {
+  const TileEdge<double> e = tile_edge<double, 9, true, true, R>(g, eux, euy, box);
+  const Lds<double>* u = (e.x ? ui : uj) + e.row * kB + 3 * e.a;
+  __syncthreads();
+  for (int s = 0; s < g.L; ++s) {
+    __syncthreads();
+    if (e.has(s))
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        __hip_atomic_store(e.base + e.off + s * e.step + k,
+                           (double)u[((s + 1) & 1) * R::kRows * kB + k], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+template <typename R, int kB>
+__device__ __forceinline__ void factor_receive(const ColGrid& g, double* eux, double* euy,
+                                               int box, int32_t* gave_up, unsigned spin,
+                                               int32_t* status, Lds<double>* ui,
+                                               Lds<double>* uj) {
+  const TileEdge<double> e = tile_edge<double, 9, true, false, R>(g, eux, euy, box);
+  Lds<double>* u = (e.x ? ui : uj) + e.row * kB + 3 * e.a;
+  bool lost = false;
+  for (int s = 0; s <= g.L; ++s) {   // level s before its barrier
+    const bool want = s < g.L && e.has(s);
+    const double* p = want ? e.base + e.off + s * e.step : e.base;   // (or the array's first)
+    double h[3];
+    bool miss = want;
+    for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
+      if (it > spin || spin == 0 || lost) {
+        lost = true;
+        __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (status) *status = OPM_EHIP;
+        if (miss) h[0] = h[1] = h[2] = 0.0;
+        break;
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        h[k] = __hip_atomic_load(p + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      miss = want && (is_unset(h[0]) || is_unset(h[1]) || is_unset(h[2]));
+      if ((it & 63) == 63 &&
+          __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        lost = true;
+    }
+    if (want)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) u[(s & 1) * R::kRows * kB + k] = h[k];
+    __syncthreads();
+  }
+}
+
 template <typename T, int NT, bool HALO>
-__global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
+__global__ __launch_bounds__(NT + (HALO ? kExchange : 0)) void k_cols_pivots(ColView<T> v, FacIn f) {
   typedef ColRows<NT, HALO> R;
   constexpr int kB = 10;   // doubles of a block's place in LDS
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -134,9 +190,19 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
   const int box = (int)blockIdx.x, L = g.L, C = g.C;
   const ColLane ln(g);
   const int a = min(ln.eq, 2);
-  const int I = box % g.nbx, Jt = (box / g.nbx) % g.nby;
-  for (int e = threadIdx.x; e < 4 * kB * R::kRows; e += NT) ui[e] = 0.0;
+  for (int e = threadIdx.x; e < 4 * kB * R::kRows; e += NT + (HALO ? kExchange : 0)) ui[e] = 0.0;
   __syncthreads();
+  if (HALO) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+    if (wave == NT / 64) {
+      factor_send<R, kB>(g, v.eux, v.euy, box, ui, uj);
+      return;
+    }
+    if (wave > NT / 64) {
+      factor_receive<R, kB>(g, v.eux, v.euy, box, v.gave_up + 2, v.spin, f.status, ui, uj);
+      return;
+    }
+  }
   constexpr int kOut = (int)0x80000000;
   const __amdgpu_buffer_rsrc_t rslot = col_rsrc(v.fac + (size_t)box * L * C, (size_t)L * C * 32);
   const __amdgpu_buffer_rsrc_t rj = col_rsrc(f.J, (size_t)f.nnzb * 72);
@@ -148,24 +214,6 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
     const u4 q = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(rslot, vs, so + 16, 0));
     return FacSlot{{p[0], p[1], p[2]}, p[3], {q[0], q[1], q[2]}, (int)q[3]};
   };
-  // HALO exchange: the scaled upper blocks of the boundary columns
-  const bool edge_i = HALO && ln.in_box && ln.ci == 0, edge_j = HALO && ln.in_box && ln.cj == 0;
-  const bool from_x = edge_i && I > 0, from_y = edge_j && Jt > 0;
-  const bool to_x = HALO && ln.in_box && ln.ci == g.bx - 1 && I + 1 < g.nbx;
-  const bool to_y = HALO && ln.in_box && ln.cj == g.by - 1 && Jt + 1 < g.nby;
-  const int sx = 72 * g.by, sy = 72 * g.bx, szx = g.bz * sx, szy = g.bz * sy;
-  const int kx = ((-ln.ci - ln.cj) * g.by + ln.cj) * 72 + a * 24;
-  const int ky = ((-ln.ci - ln.cj) * g.bx + ln.ci) * 72 + a * 24;
-  const int get_x = from_x ? kx : kOut, get_y = from_y ? ky : kOut;
-  const int put_x = to_x ? kx : kOut, put_y = to_y ? ky : kOut;
-  const double* srcx = HALO ? v.eux + (size_t)(box - 1) * (szx / 8) : nullptr;
-  const double* srcy = HALO ? v.euy + (size_t)(box - g.nbx) * (szy / 8) : nullptr;
-  const __amdgpu_buffer_rsrc_t rsx = col_rsrc(srcx, HALO ? szx : 0),
-                               rsy = col_rsrc(srcy, HALO ? szy : 0);
-  const __amdgpu_buffer_rsrc_t rdx =
-      col_rsrc(HALO ? v.eux + (size_t)box * (szx / 8) : nullptr, HALO ? szx : 0);
-  const __amdgpu_buffer_rsrc_t rdy =
-      col_rsrc(HALO ? v.euy + (size_t)box * (szy / 8) : nullptr, HALO ? szy : 0);
   auto data = [&](int s, const FacSlot& r, FacRow& b) __attribute__((always_inline)) {
     const unsigned none = ln.at(min(s, L - 1), g.bz) ? 0u : kNoBlock;   // (sets every bit that matters)
     load3(rj, (r.diag | none) + 24u * a, b.D);
@@ -176,59 +224,8 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
 #pragma unroll
       for (int e = 0; e < 3; ++e)
         b.up[q][e] = col_load<double>(rj, (int)((r.up[q] | none) + 8u * a) + 24 * e);
-    if (HALO) {
-      const int l = min(s, L - 1);
-#pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        b.hx[e] = col_load<double, kCoherent>(rsx, get_x + l * sx + 8 * e);
-        b.hy[e] = col_load<double, kCoherent>(rsy, get_y + l * sy + 8 * e);
-      }
-    }
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-  };
-  bool lost = false;
-  auto in_range = [](int off, int size) { return (unsigned)off < (unsigned)size; };
-  auto receive = [&](int s, FacRow& b, int par) __attribute__((always_inline)) {
-    if (!HALO) return;
-    const int l = min(s, L - 1);
-    const int ox = get_x + l * sx, oy = get_y + l * sy;
-    const bool wx = in_range(ox, szx), wy = in_range(oy, szy);
-    bool miss = v.spin == 0 && (wx || wy);
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-      miss = miss || (wx && is_unset(b.hx[e])) || (wy && is_unset(b.hy[e]));
-    for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
-      if (it >= v.spin || lost) {
-        lost = true;
-        __hip_atomic_store(v.gave_up + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (f.status) *f.status = OPM_EHIP;
-        if (miss) {
-#pragma unroll
-          for (int e = 0; e < 3; ++e) b.hx[e] = b.hy[e] = 0.0;
-        }
-        break;
-      }
-      const double *px = wx ? srcx + ox / 8 : v.eux, *py = wy ? srcy + oy / 8 : v.euy;
-      double hx[3], hy[3];
-      coherent_poll(px, px + 1, px + 2, py, py + 1, py + 2, hx[0], hx[1], hx[2], hy[0], hy[1],
-                      hy[2]);
-      miss = false;
-#pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        if (wx) b.hx[e] = hx[e];
-        if (wy) b.hy[e] = hy[e];
-        miss = miss || (wx && is_unset(hx[e])) || (wy && is_unset(hy[e]));
-      }
-      if ((it & 63) == 63 &&
-          __hip_atomic_load(v.gave_up + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
-        lost = true;
-    }
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      if (edge_i) ui[(par * R::kRows + R::kHalo + ln.cj) * kB + 3 * a + e] = b.hx[e];
-      if (edge_j) uj[(par * R::kRows + R::kHalo + ln.ci) * kB + 3 * a + e] = b.hy[e];
-    }
   };
   int row_i = R::kZero, row_j = R::kZero;
   if (ln.c < g.bx * g.by) {
@@ -239,16 +236,16 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
 #pragma unroll
   for (int e = 0; e < 9; ++e) uk[e] = 0.0;
   // level s: the rows of the next DEPTH levels and the indices of the levels
-  // up to s + 5 in flight (512 threads have registers for one level of rows)
-  constexpr int DEPTH = NT < 512 ? 2 : 1, ND = DEPTH + 1;
+  // up to s + 5 in flight (512 threads, and 256 beside the exchange, have
+  // registers for one level of rows)
+  constexpr int DEPTH = NT < (HALO ? 256 : 512) ? 2 : 1, ND = DEPTH + 1;
   FacRow rows[ND];
   FacSlot slots[6];
 #pragma unroll
   for (int s = 0; s < 5; ++s) slots[s] = slot_at(s);
 #pragma unroll
   for (int s = 0; s < DEPTH; ++s) data(s, slots[s], rows[s]);
-  receive(0, rows[0], 0);
-  level_barrier<NT>();
+  level_barrier<HALO ? 2 * NT : NT>();
   auto step = [&](int s, int qq) __attribute__((always_inline)) {
     const int par = qq & 1;
     double Ui[9], Uj[9];   // column by column
@@ -303,13 +300,6 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
       uk[3 + e] = quad_lane<1>(U[2][e]);
       uk[6 + e] = quad_lane<2>(U[2][e]);
     }
-    if (HALO) {
-#pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        col_store<kCoherent>(U[0][e], rdx, put_x + s * sx + 8 * e);
-        col_store<kCoherent>(U[1][e], rdy, put_y + s * sy + 8 * e);
-      }
-    }
     if (live && ln.eq < 3) {
 #pragma unroll
       for (int e = 0; e < 3; ++e) {
@@ -319,8 +309,7 @@ __global__ __launch_bounds__(NT) void k_cols_pivots(ColView<T> v, FacIn f) {
         if (sizeof(T) != sizeof(double)) ((T*)f.dinv)[at] = (T)di;
       }
     }
-    receive(s + 1, rows[(qq + 1) % ND], par ^ 1);
-    level_barrier<NT>();
+    level_barrier<HALO ? 2 * NT : NT>();
   };
   for (int s = 0;; s += 6) {
 #pragma unroll
@@ -414,7 +403,8 @@ __device__ __forceinline__ bool cols_begin(Lds<T>* nb, const int32_t* skip, cons
                                            int* word, int& state) {
   int w = 0;
   if (threadIdx.x == 0) w = MODE != kry::kFuseNone ? f.sc->state : skip ? *skip : 0;
-  for (int e = threadIdx.x; e < 8 * ColRows<NT, HALO>::kRows; e += NT) nb[e] = (T)0;
+  for (int e = threadIdx.x; e < 8 * ColRows<NT, HALO>::kRows; e += NT + (HALO ? kExchange : 0))
+    nb[e] = (T)0;
   if (threadIdx.x == 0) *word = w;
   __syncthreads();
   state = *word;
@@ -484,9 +474,12 @@ __global__ __launch_bounds__(NT) void k_cols_apply(ColView<T> v, const double* r
 // One sweep of the tiles of a whole lattice.  Backward workgroups take the
 // tiles in descending order, so that they too wait on lower indices only.
 template <typename T, int NT, int DEPTH, bool FWD, int MODE>
-__global__ __launch_bounds__(NT) void k_cols_tiles(ColView<T> v, const double* r, double* x,
-                                                    const int32_t* skip, kry::Fused f) {
-  __shared__ double red[NT / 64];
+__global__ __launch_bounds__(NT + kExchange) void k_cols_tiles(ColView<T> v, const double* r,
+                                                                double* x, const int32_t* skip,
+                                                                kry::Fused f) {
+  typedef ColRows<NT, true> R;
+  constexpr int kAll = NT + kExchange;
+  __shared__ double red[kAll / 64];
   __shared__ int word;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   Lds<T>* nb = (Lds<T>*)reinterpret_cast<T*>(smem);
@@ -498,19 +491,29 @@ __global__ __launch_bounds__(NT) void k_cols_tiles(ColView<T> v, const double* r
   BlockRhs q{r, f, 0.0, 0.0, 0.0};
   double ss = 0.0;
   const int box = FWD ? (int)blockIdx.x : v.g.boxes() - 1 - (int)blockIdx.x;
-  if (!col_sweep<T, NT, DEPTH, FWD, M, true>(
-          v, box, q, nb, (Lds<T>*)nullptr, x, ss,
-          [&](BlockRhs& qq) { return cols_gate<NT, M>(f, state, red, qq); }))
-    return;
+  // (every wavefront of the workgroup takes the same decision, and the same
+  // number of barriers)
+  auto gate = [&](BlockRhs& qq) { return cols_gate<kAll, M>(f, state, red, qq); };
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  if (wave < NT / 64) {
+    if (!col_sweep<T, NT, DEPTH, FWD, M, true>(v, box, q, nb, (Lds<T>*)nullptr, x, ss, gate))
+      return;
+  } else {
+    if (!gate(q)) return;
+    if (wave == NT / 64)
+      tile_send<T, FWD, R>(v, box, nb);
+    else
+      tile_receive<T, FWD, R>(v, box, nb);
+  }
   if (FWD && MODE == kry::kFuseS) {
-    const double tot = block_sum<NT>(ss, red);
+    const double tot = block_sum<kAll>(ss, red);
     if (threadIdx.x == 0) f.part_out[box] = tot;
   }
   // the other sweep's exchange arrays of this tile, and its give-up word
   constexpr int o = FWD ? 1 : 0;
   const size_t nx = (size_t)3 * v.g.bz * v.g.by, ny = (size_t)3 * v.g.bz * v.g.bx;
-  mark(v.ex[o] + box * nx, nx, threadIdx.x, NT);
-  mark(v.ey[o] + box * ny, ny, threadIdx.x, NT);
+  mark(v.ex[o] + box * nx, nx, threadIdx.x, kAll);
+  mark(v.ey[o] + box * ny, ny, threadIdx.x, kAll);
   if (blockIdx.x == 0 && threadIdx.x == 0) v.gave_up[o] = 0;
 }
 
@@ -570,7 +573,7 @@ size_t factor_lds(const ColGrid& g) {
 bool fits(const ColGrid& g) {
   // (LDS for FP64, so that both precisions take the same boxes; the
   // records' and vectors' byte offsets stay below 2^31)
-  return (long)g.bx * g.by * 4 <= kMaxColThreads && apply_lds<double>(g) <= kMaxColLds &&
+  return (long)g.bx * g.by * 4 <= kMaxColThreads && (!g.halo || 3 * (g.bx + g.by) <= 64) && apply_lds<double>(g) <= kMaxColLds &&
          factor_lds(g) <= kMaxColLds && (size_t)g.L * g.C * 288 < ((size_t)1 << 30) &&
          (!g.halo || (g.bx + g.by <= kHaloRows && g.nbz == 1)) && g.n < (1 << 26) &&
          // at most twice as many slots as cells of the lattice, or few of them
@@ -595,7 +598,7 @@ bool grid_of(const opm_problem* pb, ColGrid& g) {
   // the whole system: one box of at most 128 columns (300 cells: an
   // application 28 -> 24 us, and the updates of BiCGStab fused into it, 8
   // launches per iteration -> 5), else tiles of 8x8 columns (500k cells: an
-  // application 1120 us by planes -> 463 us; factored 1900 -> 870 us)
+  // application 1120 us by planes -> 392 us; factored 1900 -> 766 us)
   if ((long)pb->nx * pb->ny <= 128) {
     g = make_grid(pb, pb->nx, pb->ny, pb->nz, false);
     if (fits(g)) return true;
@@ -674,7 +677,7 @@ int factor_impl(const opm_problem* pb, const ColGrid& g, const double* J, void* 
   do {                                                                                       \
     if (g.halo) {                                                                            \
       hipLaunchKernelGGL((k_cols_pivots<T, (NT < 512 ? NT : 256), true>), dim3(g.boxes()),   \
-                         dim3(NT), lds, s, v, f);                                            \
+                         dim3(NT + kExchange), lds, s, v, f);                                \
     } else {                                                                                 \
       OPM_TRY(allow_lds(k_cols_pivots<T, NT, false>, slot + SL));                            \
       hipLaunchKernelGGL((k_cols_pivots<T, NT, false>), dim3(g.boxes()), dim3(NT), lds, s, v, \
@@ -703,10 +706,12 @@ int apply_impl(const opm_problem* pb, const ColGrid& g, void* ilu, const double*
 #define OPM_COLS(NT, D, SL)                                                                  \
   do {                                                                                       \
     if (g.halo) {                                                                            \
-      hipLaunchKernelGGL((k_cols_tiles<T, (NT < 512 ? NT : 256), 3, true, MODE>),            \
-                         dim3(g.boxes()), dim3(NT), lds, s, v, r, x, skip, f);               \
-      hipLaunchKernelGGL((k_cols_tiles<T, (NT < 512 ? NT : 256), 3, false, kry::kFuseNone>), \
-                         dim3(g.boxes()), dim3(NT), lds, s, v, r, x, skip2, f);              \
+      /* (forward FP64: with three levels in flight the fused forms spill) */                \
+      constexpr int NTT = NT < 512 ? NT : 256, DF = sizeof(T) == 8 ? 2 : 3;                  \
+      hipLaunchKernelGGL((k_cols_tiles<T, NTT, DF, true, MODE>), dim3(g.boxes()),            \
+                         dim3(NT + kExchange), lds, s, v, r, x, skip, f);                    \
+      hipLaunchKernelGGL((k_cols_tiles<T, NTT, 3, false, kry::kFuseNone>), dim3(g.boxes()),  \
+                         dim3(NT + kExchange), lds, s, v, r, x, skip2, f);                   \
     } else {                                                                                 \
       OPM_TRY(allow_lds(k_cols_apply<T, NT, D, MODE>, slot + SL));                           \
       hipLaunchKernelGGL((k_cols_apply<T, NT, D, MODE>), dim3(g.boxes()), dim3(NT), lds, s,  \

@@ -16,18 +16,18 @@
 // SIMD pays for each instruction of a level.  With rows found by position (the
 // sweeps of ilu0.hip) most of a level is index arithmetic and nine LDS reads per
 // lane; here it is one LDS write, four reads, 12 fused multiply-adds and the
-// loads of a later level (about 65 instructions, 0.12-0.16 us per level of a
+// loads of a later level (about 55 instructions, 0.11-0.14 us per level of a
 // 4x4 box, against 0.24 us).  One application, both sweeps, by HIP events:
-// 9000 cells in 4x4x15 boxes 10.6 -> 8.9 us FP64, 10.1 -> 7.4 us FP32; 500k
-// cells in 4x4x50 boxes 56.8 -> 54.7 us (bound by bandwidth: 63 values per row
-// instead of 72), FP32 33.8 -> 27.1 us.  The dynamic LDS must be declared
+// 9000 cells in 4x4x10 boxes 10.6 -> 6.7 us FP64, 10.1 -> 5.8 us FP32; 500k
+// cells in 4x4x50 boxes 56.8 -> 48.3 us (bound by bandwidth: 63 values per row
+// instead of 72), FP32 33.8 -> 24.4 us.  The dynamic LDS must be declared
 // 16-byte aligned: behind a static 4-byte word its 8-byte reads were misaligned
 // and split (8x8x60 cells, FP64: 131 against 43 us).
 //
 // Storage: slot (box, l, c) for every level and column, also where the column
-// has no cell (ahead of its first and past its last level, inactive cells,
-// columns past the box): those have zero records and the index 0, and their
-// value is zero.  Record of (slot, equation): forward the three scaled lower
+// has no cell: the index is 0 there and the value zero.  Inactive cells have
+// zero records; ahead of a column's first and past its last level, and for
+// columns past the box, no record is written or read.  Record of (slot, equation): forward the three scaled lower
 // blocks' rows (k, j, i) and the row of D^{-1}, 12 values in 16-byte chunks;
 // backward the scaled upper blocks' rows (i, j, k), 9 values, the last one in
 // an array of its own.  A level of a box is one contiguous piece.
@@ -36,9 +36,9 @@
 // a tile's western and southern columns need the values of the eastern and
 // northern columns of its neighbours.  Those go through exchange arrays that
 // hold a marker (a signalling NaN, which no arithmetic returns) until they are
-// written through to the device's coherence point.  A tile loads them with the
-// records of their level, several levels ahead, and re-reads those that still
-// held the marker (bounded; a wait that gives up takes NaN, so that the solve
+// written through to the device's coherence point.  Two wavefronts of a tile's
+// own store and load them (tile_send, tile_receive), the loads two levels ahead
+// and again while a value still holds the marker (bounded; a wait that gives up takes NaN, so that the solve
 // returns NaN instead of hanging).  Workgroups are dispatched in index order
 // and wait only on lower indices.  The forward launch refills the exchange
 // arrays of the backward one with the marker and the other way round.
@@ -95,8 +95,6 @@ template <typename T>
 using Lds = __attribute__((address_space(3))) T;
 // Word 3 of a raw buffer resource on gfx9 (32-bit data format, no swizzle).
 constexpr int kBufferWord3 = 0x00020000;
-// sc1: through to (from) the device's coherence point
-constexpr int kCoherent = 16;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t col_rsrc(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0,
@@ -104,21 +102,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t col_rsrc(const void* p, size_t
                                            kBufferWord3);
 }
 
-template <typename T, int AUX = 0>
+template <typename T>
 __device__ __forceinline__ T col_load(__amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
   if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, AUX));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
   else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, AUX));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
 }
-template <int AUX = 0>
 __device__ __forceinline__ void col_store(double x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
   typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), r, off, soff, AUX);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), r, off, soff, 0);
 }
-template <int AUX = 0>
 __device__ __forceinline__ void col_store(float x, __amdgpu_buffer_rsrc_t r, int off, int soff = 0) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, off, soff, AUX);
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, off, soff, 0);
 }
 
 // the marker of a value not yet written (signalling NaNs: arithmetic
@@ -148,47 +144,6 @@ __device__ __forceinline__ float coherent_reread(const float* p) {
   asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
   return __builtin_bit_cast(float, b);
 }
-// All the values of a poll in one round trip.
-__device__ __forceinline__ void coherent_poll(const double* p0, const double* p1,
-                                                const double* p2, const double* p3,
-                                                const double* p4, const double* p5, double& v0,
-                                                double& v1, double& v2, double& v3, double& v4,
-                                                double& v5) {
-  unsigned long long b0, b1, b2, b3, b4, b5;
-  asm volatile(
-      "global_load_dwordx2 %0, %6, off sc1\n\tglobal_load_dwordx2 %1, %7, off sc1\n\t"
-      "global_load_dwordx2 %2, %8, off sc1\n\tglobal_load_dwordx2 %3, %9, off sc1\n\t"
-      "global_load_dwordx2 %4, %10, off sc1\n\tglobal_load_dwordx2 %5, %11, off sc1\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3), "=&v"(b4), "=&v"(b5)
-      : "v"(p0), "v"(p1), "v"(p2), "v"(p3), "v"(p4), "v"(p5));
-  v0 = __builtin_bit_cast(double, b0);
-  v1 = __builtin_bit_cast(double, b1);
-  v2 = __builtin_bit_cast(double, b2);
-  v3 = __builtin_bit_cast(double, b3);
-  v4 = __builtin_bit_cast(double, b4);
-  v5 = __builtin_bit_cast(double, b5);
-}
-__device__ __forceinline__ void coherent_poll(const float* p0, const float* p1, const float* p2,
-                                                const float* p3, const float* p4, const float* p5,
-                                                float& v0, float& v1, float& v2, float& v3,
-                                                float& v4, float& v5) {
-  unsigned b0, b1, b2, b3, b4, b5;
-  asm volatile(
-      "global_load_dword %0, %6, off sc1\n\tglobal_load_dword %1, %7, off sc1\n\t"
-      "global_load_dword %2, %8, off sc1\n\tglobal_load_dword %3, %9, off sc1\n\t"
-      "global_load_dword %4, %10, off sc1\n\tglobal_load_dword %5, %11, off sc1\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3), "=&v"(b4), "=&v"(b5)
-      : "v"(p0), "v"(p1), "v"(p2), "v"(p3), "v"(p4), "v"(p5));
-  v0 = __builtin_bit_cast(float, b0);
-  v1 = __builtin_bit_cast(float, b1);
-  v2 = __builtin_bit_cast(float, b2);
-  v3 = __builtin_bit_cast(float, b3);
-  v4 = __builtin_bit_cast(float, b4);
-  v5 = __builtin_bit_cast(float, b5);
-}
-
 // Value of lane K of the lane's quad (DPP quad permutation: a VALU move, no
 // LDS round trip).
 template <int K>
@@ -276,8 +231,128 @@ struct ColJob {
   T d[3];       // forward: row of D^{-1}
   T z;          // backward, HALO: the forward result
   double u[3];  // forward: the vector values the right-hand side is made of
-  T hx, hy;     // HALO: this lane's value of the neighbouring tiles
 };
+
+// The exchange of a tile with its neighbours, by two wavefronts beside those
+// that compute: at most 24 values towards x and 24 towards y per level, one per
+// lane.  The sender stores a level's values of the edge columns as soon as the
+// level is done; the receiver asks for the neighbours' values two levels ahead
+// and has them in the LDS rows of a level before that level starts.  They meet
+// the others at the barrier of each level, and a level of those is then that of
+// a box on its own: with the exchange in the computing wavefronts (its loads,
+// tests and stores in every lane) a level of 256 threads took 0.5 us, where a
+// box's takes 0.28 us.  30 x 30 x 10 cells: application 114 -> 69 us, 100 x 100 x
+// 50: 441 -> 391 us (FP32 factors 328 -> 252 us).  Levels ahead: every one adds to
+// the distance between neighbouring tiles, and none leaves a round trip (0.6 to
+// 1 us) on every level; 8, 4, 3, 2, 1 of them: 81, 74.5, 69.7, 69.3, 78 us.
+constexpr int kExchange = 128;   // threads of the two wavefronts
+template <typename T>
+struct TileEdge {
+  T* base;
+  int off, step, size;   // of level l: off + l step, if in [0, size)
+  int row, a;            // LDS row of a level, equation
+  bool x;                // towards x (else y)
+  __device__ __forceinline__ bool has(int l) const {
+    return (unsigned)(off + l * step) < (unsigned)size;
+  }
+};
+// W values per cell (of a sweep 3, of the factorisation 9; the lane's W / 3 are
+// consecutive, its first one is here), exchanged through x and y
+template <typename T, int W, bool FWD, bool SEND, typename R>
+__device__ __forceinline__ TileEdge<T> tile_edge(const ColGrid& g, T* ex, T* ey, int box) {
+  const int lane = threadIdx.x & 63, I = box % g.nbx, Jt = box / g.nbx % g.nby;
+  const bool x = lane < 3 * g.by;
+  const int k = x ? lane : lane - 3 * g.by, p = k / 3, a = k - 3 * p;
+  constexpr bool up = FWD == SEND;   // the edge towards higher columns
+  const int at = x ? (up ? g.bx - 1 : 0) : (up ? g.by - 1 : 0);
+  const int ci = x ? at : p, cj = x ? p : at, per = x ? g.by : g.bx;
+  const bool on = (x || k < 3 * g.bx) &&
+                  (x ? (up ? I + 1 < g.nbx : I > 0) : (up ? Jt + 1 < g.nby : Jt > 0));
+  TileEdge<T> e;
+  e.step = W * per;
+  e.size = g.bz * e.step;
+  const int other = (up ? 1 : -1) * (x ? 1 : g.nbx);
+  T* const all = x ? ex : ey;
+  e.base = all + (on ? (size_t)(box + (SEND ? 0 : other)) * e.size : 0);
+  e.off = (p - (ci + cj) * per) * W + a * (W / 3);
+  e.row = SEND ? cj * g.bx + ci : R::kHalo + (W == 3 ? (x ? cj : g.by + ci) : p);
+  e.a = a;
+  e.x = x;
+  if (!on) e.size = 0;
+  return e;
+}
+
+template <typename T, bool FWD, typename R>
+__device__ __forceinline__ void tile_send(const ColView<T>& v, int box, const Lds<T>* nb) {
+  const TileEdge<T> e =
+      tile_edge<T, 3, FWD, true, R>(v.g, v.ex[FWD ? 0 : 1], v.ey[FWD ? 0 : 1], box);
+  const int L = v.g.L;
+  __syncthreads();
+  for (int s = 0; s < L; ++s) {
+    __syncthreads();   // level s is done: its values are in the rows the next one reads
+    const int l = FWD ? s : L - 1 - s;
+    if (e.has(l))
+      __hip_atomic_store(e.base + e.off + l * e.step, (T)nb[((s + 1) & 1) * 4 * R::kRows + 4 * e.row + e.a],
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// A value not yet written holds the marker: the receiver polls for it (with the
+// levels behind it, in the same round trip), at most v.spin times.
+template <typename T, bool FWD, typename R>
+__device__ __forceinline__ void tile_receive(const ColView<T>& v, int box, Lds<T>* nb) {
+  const TileEdge<T> e =
+      tile_edge<T, 3, FWD, false, R>(v.g, v.ex[FWD ? 0 : 1], v.ey[FWD ? 0 : 1], box);
+  const int L = v.g.L;
+  constexpr int D = 2;
+  auto level = [&](int s) { return FWD ? min(s, L - 1) : L - 1 - min(s, L - 1); };
+  auto load = [&](int s) {   // (a lane without a value there: the array's first, not used)
+    const int l = level(s);
+    return __hip_atomic_load(e.has(l) ? e.base + e.off + l * e.step : e.base, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  };
+  T h[D];
+#pragma unroll
+  for (int u = 0; u < D; ++u) h[u] = load(u);
+  bool lost = false;
+  auto get = [&](int s, int slot) __attribute__((always_inline)) {
+    const bool want = s < L && e.has(level(s));
+    bool miss = want && (is_unset(h[slot]) || v.spin == 0);
+    for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
+      if (it >= v.spin || lost) {
+        lost = true;
+        if (miss) h[slot] = (T)__builtin_nan("");
+        __hip_atomic_store(v.gave_up + (FWD ? 0 : 1), 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        break;
+      }
+#pragma unroll
+      for (int u = 0; u < D; ++u) h[(slot + u) % D] = load(s + u);
+      miss = want && is_unset(h[slot]);
+      if ((it & 63) == 63 && __hip_atomic_load(v.gave_up + (FWD ? 0 : 1), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) != 0)
+        lost = true;
+    }
+    if (want) nb[(s & 1) * 4 * R::kRows + 4 * e.row + e.a] = h[slot];
+    h[slot] = load(s + D);
+  };
+  get(0, 0);
+  __syncthreads();
+  int s = 1;   // level s is received while level s - 1 is computed
+  for (; s + D - 1 <= L; s += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      get(s + u, (1 + u) % D);
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u) {
+    if (s + u > L) return;
+    get(s + u, (1 + u) % D);
+    __syncthreads();
+  }
+}
 
 // One sweep of box `box` by the workgroup of NT threads.
 //   nb: LDS rows (col_rows_bytes), all zero on entry to the forward sweep
@@ -328,31 +403,6 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     row_j = !edge_j ? (FWD ? ln.c - g.bx : ln.c + g.bx)
                     : HALO ? R::kHalo + g.by + ln.ci : R::kZero;
   }
-  // exchange with the neighbouring tiles: where this lane's column reads and
-  // writes at level l: base + l * stride
-  const int I = box % g.nbx, Jt = (box / g.nbx) % g.nby;
-  const int sx = 3 * ts * g.by, sy = 3 * ts * g.bx;
-  const int kx = HALO ? ((-ln.ci - ln.cj) * g.by + ln.cj) * 3 * ts + a * ts : 0;
-  const int ky = HALO ? ((-ln.ci - ln.cj) * g.bx + ln.ci) * 3 * ts + a * ts : 0;
-  const int szx = g.bz * sx, szy = g.bz * sy;
-  const bool from_x = HALO && ln.in_box && edge_i && (FWD ? I > 0 : I + 1 < g.nbx);
-  const bool from_y = HALO && ln.in_box && edge_j && (FWD ? Jt > 0 : Jt + 1 < g.nby);
-  const bool to_x = HALO && ln.in_box && (FWD ? ln.ci == g.bx - 1 && I + 1 < g.nbx
-                                              : ln.ci == 0 && I > 0);
-  const bool to_y = HALO && ln.in_box && (FWD ? ln.cj == g.by - 1 && Jt + 1 < g.nby
-                                              : ln.cj == 0 && Jt > 0);
-  // (a lane without such a value: past the end of the array at every level)
-  const int get_x = from_x ? kx : kOut, get_y = from_y ? ky : kOut;
-  const int put_x = to_x ? kx : kOut, put_y = to_y ? ky : kOut;
-  const T* srcx = HALO ? v.ex[FWD ? 0 : 1] + (size_t)(box + (FWD ? -1 : 1)) * (szx / ts) : nullptr;
-  const T* srcy = HALO ? v.ey[FWD ? 0 : 1] + (size_t)(box + (FWD ? -1 : 1) * g.nbx) * (szy / ts)
-                       : nullptr;
-  const __amdgpu_buffer_rsrc_t rsx = col_rsrc(srcx, HALO ? szx : 0), rsy = col_rsrc(srcy, HALO ? szy : 0);
-  const __amdgpu_buffer_rsrc_t rdx =
-      col_rsrc(HALO ? v.ex[FWD ? 0 : 1] + (size_t)box * (szx / ts) : nullptr, HALO ? szx : 0);
-  const __amdgpu_buffer_rsrc_t rdy =
-      col_rsrc(HALO ? v.ey[FWD ? 0 : 1] + (size_t)box * (szy / ts) : nullptr, HALO ? szy : 0);
-
   auto level = [&](int s) {   // of step s (past the last one: the last one)
     const int sc = min(s, L - 1);
     return FWD ? sc : L - 1 - sc;
@@ -413,75 +463,13 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     } else if (HALO) {
       j.z = col_load<T>(rz, at ? vz : kOut, l * C * 3 * ts);
     }
-    if (HALO) {
-      j.hx = col_load<T, kCoherent>(rsx, get_x + l * sx);
-      j.hy = col_load<T, kCoherent>(rsy, get_y + l * sy);
-    }
     next_idx();
     // keep every load of the stage here, ahead of the computation of the
     // current level, and the arithmetic on them after this point
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  // HALO: the exchanged values of step s, re-read while they hold the marker
-  // (with those of the steps behind it, which the same wait makes ready too),
-  // then in LDS for the step
   ColJob<T> jobs[ND];
-  bool lost = false;   // a wait of this wavefront gave up
-  auto in_range = [](int off, int size) { return (unsigned)off < (unsigned)size; };
-  auto receive = [&](int s, int slot, int par) __attribute__((always_inline)) {
-    if (!HALO) return;
-    const int l = level(s);
-    const int ox = get_x + l * sx, oy = get_y + l * sy;
-    const bool wait_x = in_range(ox, szx), wait_y = in_range(oy, szy);
-    T hx = jobs[slot].hx, hy = jobs[slot].hy;
-    bool miss = (wait_x && is_unset(hx)) || (wait_y && is_unset(hy));
-    if (v.spin == 0 && (wait_x || wait_y)) miss = true;
-    if (__builtin_amdgcn_ballot_w64(miss) != 0) {
-      // a poll reads the values of this step and of the loaded ones behind it
-      // (a lane or step without one: the array's first value, not used)
-      static_assert(DEPTH == 3, "the values of a poll");
-      const T *px[DEPTH], *py[DEPTH];
-      bool wx[DEPTH], wy[DEPTH];
-#pragma unroll
-      for (int u = 0; u < DEPTH; ++u) {
-        const int lu = level(s + u), ux = get_x + lu * sx, uy = get_y + lu * sy;
-        wx[u] = in_range(ux, szx);
-        wy[u] = in_range(uy, szy);
-        px[u] = wx[u] ? srcx + ux / ts : v.ex[FWD ? 0 : 1];
-        py[u] = wy[u] ? srcy + uy / ts : v.ey[FWD ? 0 : 1];
-      }
-      for (unsigned it = 0; __builtin_amdgcn_ballot_w64(miss) != 0; ++it) {
-        if (it >= v.spin || lost) {
-          lost = true;
-          if (miss) {
-            hx = (T)__builtin_nan("");
-            hy = (T)__builtin_nan("");
-          }
-          __hip_atomic_store(v.gave_up + (FWD ? 0 : 1), 1, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-          break;
-        }
-        T x0, x1, x2, y0, y1, y2;
-        coherent_poll(px[0], py[0], px[1], py[1], px[2], py[2], x0, y0, x1, y1, x2, y2);
-        if (wx[0]) hx = x0;
-        if (wy[0]) hy = y0;
-        ColJob<T>&j1 = jobs[(slot + 1) % ND], &j2 = jobs[(slot + 2) % ND];
-        if (wx[1]) j1.hx = x1;
-        if (wy[1]) j1.hy = y1;
-        if (wx[2]) j2.hx = x2;
-        if (wy[2]) j2.hy = y2;
-        miss = (wx[0] && is_unset(hx)) || (wy[0] && is_unset(hy));
-        if ((it & 63) == 63 && __hip_atomic_load(v.gave_up + (FWD ? 0 : 1), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT) != 0)
-          lost = true;
-      }
-    }
-    Lds<T>* h = nb + par * 4 * R::kRows + 4 * R::kHalo + ln.eq;
-    if (ln.in_box && edge_i) h[4 * ln.cj] = hx;
-    if (ln.in_box && edge_j) h[4 * (g.by + ln.ci)] = hy;
-  };
-
   int idx[P];
   // prologue: the data of steps 0 .. DEPTH-1, their indices and the ND after
 #pragma unroll
@@ -492,8 +480,7 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
   // iteration's scalars (their loads overlap those of the sweep)
   if (!gate(q)) return false;
   T out = (T)0;
-  receive(0, 0, 0);
-  level_barrier<NT>();
+  level_barrier<HALO ? 2 * NT : NT>();
   // step s reads the rows of parity s % 2 and writes the others
   auto step = [&](int s, int qq) __attribute__((always_inline)) {
     const Lds<T>* rd = nb + (qq & 1) * 4 * R::kRows;
@@ -530,8 +517,6 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     nb[((qq & 1) ^ 1) * 4 * R::kRows + 4 * ln.c + ln.eq] = out;
     const int off = ix + vcell;
     if (HALO) {
-      col_store<kCoherent>(out, rdx, put_x + l * sx);
-      col_store<kCoherent>(out, rdy, put_y + l * sy);
       if (FWD) col_store(out, rz, ix != 0 ? vz : kOut, l * C * 3 * ts);
     } else if (FWD) {
       *zp = out;
@@ -543,8 +528,7 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
       col_store(u, col_rsrc(q.f.s, vec_bytes), off);
       ss += ix != 0 ? u * u : 0.0;
     }
-    receive(s + 1, (qq + 1) % ND, (qq & 1) ^ 1);
-    level_barrier<NT>();
+    level_barrier<HALO ? 2 * NT : NT>();
   };
   // (the last levels apart: an exit inside the loop meets its back edge in the
   // compiled code, which then waits there as for the loads of the shortest way)
