@@ -63,7 +63,7 @@ constexpr unsigned kNoBlock = 0xffffff00u;
 template <typename T>
 __global__ __launch_bounds__(256) void k_cols_slots(ColView<T> v, FacIn f) {
   const ColGrid& g = v.g;
-  const size_t slot = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const unsigned slot = blockIdx.x * 256u + threadIdx.x;
   if (blockIdx.x == 0)   // the padding of the inverse pivots
     for (int e = threadIdx.x; e < 9 * (f.ns - g.n); e += 256) {
       const size_t at = (size_t)(e / (f.ns - g.n)) * f.ns + g.n + e % (f.ns - g.n);
@@ -71,17 +71,14 @@ __global__ __launch_bounds__(256) void k_cols_slots(ColView<T> v, FacIn f) {
       if (sizeof(T) != sizeof(double)) ((T*)f.dinv)[at] = (T)0;
     }
   if (slot >= g.slots()) return;
-  const int c = (int)(slot % g.C), s = (int)(slot / g.C % g.L), box = (int)(slot / g.C / g.L);
+  const int row = (int)(slot / (unsigned)g.C), c = (int)(slot - (unsigned)row * (unsigned)g.C);
+  const int box = row / g.L, s = row - box * g.L;
   const int cj = c / g.bx, ci = c - cj * g.bx, kk = s - ci - cj;
   const int gi = box % g.nbx * g.bx + ci, gj = box / g.nbx % g.nby * g.by + cj;
   const int k = box / (g.nbx * g.nby) * g.bz + kk;
   FacSlot rec{{kNoBlock, kNoBlock, kNoBlock}, kNoBlock, {kNoBlock, kNoBlock, kNoBlock}, 0};
   int cell = -1;
-  if (c >= g.bx * g.by || kk < 0 || kk >= g.bz) {   // (no record is read there)
-    v.idx[slot] = 0;
-    return;
-  }
-  if (gi < g.nx && gj < g.ny && k < g.nz) {
+  if (c < g.bx * g.by && gi < g.nx && gj < g.ny && kk >= 0 && kk < g.bz && k < g.nz) {
     const int sxy = g.nx * g.ny;
     const int32_t* b = f.box_cell + gi + g.nx * gj + (size_t)sxy * k;
     cell = b[0];
@@ -330,8 +327,6 @@ __global__ __launch_bounds__(256) void k_cols_records(ColView<T> v, FacIn f) {
   const size_t slot = (size_t)blockIdx.x * 64 + threadIdx.x / 4;
   const int a = (int)(threadIdx.x & 3u);
   if (slot >= g.slots() || a == 3) return;
-  const int col = (int)(slot % g.C), kk = (int)(slot / g.C % g.L) - col % g.bx - col / g.bx;
-  if (col >= g.bx * g.by || kk < 0 || kk >= g.bz) return;   // (never read)
   const FacSlot r = v.fac[slot];
   const bool live = r.diag != kNoBlock;
   double di[3];
@@ -577,6 +572,7 @@ bool fits(const ColGrid& g) {
          factor_lds(g) <= kMaxColLds && (size_t)g.L * g.C * 288 < ((size_t)1 << 30) &&
          (!g.halo || (g.bx + g.by <= kHaloRows && g.nbz == 1)) && g.n < (1 << 26) &&
          // at most twice as many slots as cells of the lattice, or few of them
+         g.slots() < ((size_t)1 << 31) &&   // (32-bit slot numbers)
          (g.slots() <= 2 * (size_t)g.nx * g.ny * g.nz || g.slots() <= 65536);
 }
 

@@ -25,10 +25,9 @@
 // and split (8x8x60 cells, FP64: 131 against 43 us).
 //
 // Storage: slot (box, l, c) for every level and column, also where the column
-// has no cell: the index is 0 there and the value zero.  Inactive cells have
-// zero records; ahead of a column's first and past its last level, and for
-// columns past the box, no record is written or read.  Record of (slot, equation): forward the three scaled lower
-// blocks' rows (k, j, i) and the row of D^{-1}, 12 values in 16-byte chunks;
+// has no cell: the index is 0 there, the records and the value are zero
+// (records ahead of a column's first and past its last level are not read).
+// Record of (slot, equation): forward the three scaled lower blocks' rows (k, j, i) and the row of D^{-1}, 12 values in 16-byte chunks;
 // backward the scaled upper blocks' rows (i, j, k), 9 values, the last one in
 // an array of its own.  A level of a box is one contiguous piece.
 //
@@ -38,8 +37,8 @@
 // hold a marker (a signalling NaN, which no arithmetic returns) until they are
 // written through to the device's coherence point.  Two wavefronts of a tile's
 // own store and load them (tile_send, tile_receive), the loads two levels ahead
-// and again while a value still holds the marker (bounded; a wait that gives up takes NaN, so that the solve
-// returns NaN instead of hanging).  Workgroups are dispatched in index order
+// and again while a value still holds the marker (bounded; a wait that gives up
+// takes NaN, so that the solve returns NaN instead of hanging).  Workgroups are dispatched in index order
 // and wait only on lower indices.  The forward launch refills the exchange
 // arrays of the backward one with the marker and the other way round.
 #pragma once
