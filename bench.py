@@ -42,26 +42,22 @@ METRIC = "cell-Newton-iterations/s (assembly+ILU0-BiCGStab) & % HBM roofline vs 
 
 
 def sweep_bytes_per_cell(precision: int) -> float:
-    """Algorithmic bytes of one preconditioner application (forward plus
-    backward sweep) per cell: three lower and three upper off-diagonal blocks
-    read once, D^{-1} read in both sweeps, the right-hand side read, the
-    result written by the forward sweep and updated by the backward sweep,
-    plus the level-order index tables (perm twice, lower and upper positions)."""
+    """Algorithmic bytes of one application of the ILU(0) of a whole lattice
+    per cell: the two sweep records (36 and 27 values: three scaled lower blocks
+    and D^{-1}, three scaled upper blocks), the 4-byte index in both sweeps, the
+    right-hand side read, the forward result written and read, the result
+    written."""
     w = 8 if precision == 0 else 4
-    blocks = (27 + 27) * w + 2 * 9 * w
-    vectors = 24 + 24 + 24 + 24
-    index = 4 * 2 + 12 + 12
-    return blocks + vectors + index
+    return (36 + 27) * w + 2 * 4 + 2 * 3 * w + 24 + 24
 
 
 def block_sweep_bytes_per_cell(precision: int) -> float:
     """Algorithmic bytes of one block-ILU0 preconditioner application per
-    cell: the three lower and three upper off-diagonal blocks and D^{-1}
-    (read in both sweeps) of the sweep records, the two 16-byte neighbour
-    index records, the right-hand side read and the result written (the
-    intermediate vector stays in LDS)."""
+    cell: the two sweep records (36 and 27 values), the 4-byte index in both
+    sweeps, the right-hand side read and the result written (the intermediate
+    vector stays in LDS)."""
     w = 8 if precision == 0 else 4
-    return (27 + 27 + 2 * 9) * w + 2 * 16 + 24 + 24
+    return (36 + 27) * w + 2 * 4 + 24 + 24
 
 
 def spmv_bytes_per_cell(nnzb: int, n: int) -> float:
@@ -79,28 +75,20 @@ def assemble_bytes(n: int, nnzb: int, nf: int) -> float:
 
 
 def factor_bytes_per_cell(precision: int) -> float:
-    """Algorithmic bytes of the ILU(0) factorisation per cell: the block row
-    of J read once (7 FP64 blocks and their column indices), the level-order
-    copies of the off-diagonal blocks and the inverse pivot written (27 + 27
-    + 9 values, plus the FP64 pivot copy in mixed precision), and the three
-    lower and three transposed blocks plus the neighbours' inverse pivots
-    read again by the pivot recursion."""
+    """Algorithmic bytes of the ILU(0) factorisation by columns per cell: the
+    32-byte row record written and read twice (recursion, records), the seven
+    blocks of the row read and D^{-1} written (plus its FP32 copy) by the
+    recursion, the six off-diagonal blocks and D^{-1} read and the two sweep
+    records written, and the index."""
     w = 8 if precision == 0 else 4
-    pack = 7 * (72 + 4) + (27 + 27 + 9) * w + (72 if precision else 0)
-    recurse = (27 + 27) * w + 3 * 9 * 8 + 9 * 8
-    return pack + recurse
+    recurse = 7 * 72 + 72 + (36 if precision else 0)
+    records = 6 * 72 + 72 + (36 + 27) * w
+    return 3 * 32 + 4 + recurse + records
 
 
 def block_factor_bytes_per_cell(precision: int) -> float:
-    """Algorithmic bytes of the block-ILU0 factorisation per cell: the pivot
-    recursion reads the diagonal, the three lower and the three transposed
-    blocks of the row and writes D^{-1} (plus its FP32 copy); the record
-    pass reads the six off-diagonal blocks and D^{-1} and writes the two
-    sweep records and index records."""
-    w = 8 if precision == 0 else 4
-    recurse = 7 * 72 + 72 + (36 if precision else 0)
-    records = 6 * 72 + 9 * w + 2 * 36 * w + 2 * 16
-    return recurse + records
+    """As factor_bytes_per_cell: the same three kernels."""
+    return factor_bytes_per_cell(precision)
 
 
 def gmres_cycle_bytes(n: int, nnzb: int, m: int, apply_bytes: float) -> float:
@@ -620,25 +608,24 @@ def bench_kernels(args):
                  spmv_bytes_per_cell(g.nnzb, n) * n, "k_spmv"),
         "ilu0_apply_fp64": (lambda: L.opm_ilu0_apply(pbp, sp(ilu[0]), 0, sp(R), sp(x), st),
                             sweep_bytes_per_cell(0) * n,
-                            "k_plane_reset + k_sweep_planes forward and backward (FP64)"),
+                            "k_cols_tiles forward and backward (FP64)"),
         "ilu0_apply_fp32": (lambda: L.opm_ilu0_apply(pbp, sp(ilu[1]), 1, sp(R), sp(x), st),
                             sweep_bytes_per_cell(1) * n,
-                            "k_plane_reset + k_sweep_planes forward and backward (FP32)"),
+                            "k_cols_tiles forward and backward (FP32)"),
         "assemble": (lambda: L.opm_assemble(pbp, sp(yk), sp(acc0), dt, sp(Rb), sp(Jb), sp(norms), st),
                      assemble_bytes(n, g.nnzb, g.nf), "k_assemble_tiled + k_norms_final"),
         "ilu0_factor_fp64": (lambda: L.opm_ilu0_factor(pbp, sp(J), sp(ilu_tmp[0]), 0, sp(status), st),
                              factor_bytes_per_cell(0) * n,
-                             "k_pack + k_plane_init + k_plane_fill + k_plane_factor_reset + "
-                             "k_factor_planes + k_pack_records (FP64)"),
+                             "k_cols_reset + k_cols_slots + k_cols_pivots + k_cols_records (FP64)"),
         "block_apply_fp64": (lambda: L.opm_ilu0_apply(pbb, sp(bilu[0]), 0, sp(R), sp(x), st),
                              block_sweep_bytes_per_cell(0) * n,
-                             f"k_apply_blocks (FP64, {gb.pb.n_sub} subdomains of {blk})"),
+                             f"k_cols_apply (FP64, {gb.pb.n_sub} subdomains of {blk})"),
         "block_apply_fp32": (lambda: L.opm_ilu0_apply(pbb, sp(bilu[1]), 1, sp(R), sp(x), st),
                              block_sweep_bytes_per_cell(1) * n,
-                             f"k_apply_blocks (FP32, {gb.pb.n_sub} subdomains of {blk})"),
+                             f"k_cols_apply (FP32, {gb.pb.n_sub} subdomains of {blk})"),
         "block_factor_fp64": (lambda: L.opm_ilu0_factor(pbb, sp(Jb_), sp(ilu_tmp[0]), 0, sp(status), st),
                               block_factor_bytes_per_cell(0) * n,
-                              "k_factor_blocks + k_pack_block_records (FP64)"),
+                              "k_cols_slots + k_cols_pivots + k_cols_records (FP64)"),
     }
     # assembly with live oil on the same grid: a seeded state, half of the
     # cells with free gas (x = s_g), half undersaturated (x = r_go < r_s(p))
@@ -670,7 +657,7 @@ def bench_kernels(args):
         lambda: L.opm_gmres(pbb, sp(Jb_), sp(bilu[0]), 0, sp(R), sp(xg), 0.0, m, m, sp(gwork),
                             ctypes.byref(grep), st),
         gmres_cycle_bytes(n, g.nnzb, m, block_sweep_bytes_per_cell(0) * n),
-        f"one GMRes({m}) cycle: {m} x (k_apply_blocks + k_gm_spmv + k_gm_dots + k_gm_cgs1 + "
+        f"one GMRes({m}) cycle: {m} x (k_cols_apply + k_gm_spmv + k_gm_dots + k_gm_cgs1 + "
         "k_gm_cgs2 + k_gm_rotate) + start and finish kernels (FP64 block ILU0)")
     # CPR-AMG on the same system (FP64 block ILU0 as its second stage)
     cpr_k, cpr_st = gb.cpr_setup(Jb_)
@@ -678,13 +665,14 @@ def bench_kernels(args):
     kern["cpr_setup"] = (
         lambda: L.opm_cpr_setup(pbb, sp(Jb_), sp(cpr_k), sp(cpr_st), st),
         cpr_setup_bytes(lv, n, g.nnzb),
-        f"k_cpr_weights + {len(lv) - 1} x (k_cpr_galerkin + k_cpr_diag) + k_cpr_inverse")
+        f"k_cpr_weights + {len(lv) - 1} x (k_cpr_galerkin + k_cpr_diag) + k_cpr_inverse + "
+        "k_cpr_tail")
     kern["cpr_apply"] = (
         lambda: L.opm_cpr_apply(pbb, sp(Jb_), sp(bilu[0]), 0, sp(cpr_k), sp(R), sp(x), st),
         cpr_apply_bytes(lv, n, g.nnzb, block_sweep_bytes_per_cell(0) * n),
         f"V(1,1) cycle over {len(lv)} levels ({'/'.join(str(a) for a, _ in lv)} unknowns: "
-        f"{len(lv) - 1} x k_cpr_down + k_cpr_coarse + {len(lv) - 1} x k_cpr_up) + k_cpr_r2 + "
-        "k_apply_blocks (FP64) + k_cpr_add")
+        "per level of more than 2048 k_cpr_rhs + k_cpr_res and k_cpr_up, k_cpr_dense for the "
+        "others) + k_cpr_r2 + k_cols_apply (FP64) + k_cpr_add")
     # a whole linear solve (BiCGStab to 1e-6) with either preconditioner: the
     # iterations CPR saves against its dearer application
     kwork = torch.empty(L.opm_krylov_bytes(pbb), dtype=torch.uint8, device=g.dev)
@@ -991,13 +979,13 @@ def main():
     if blocks is not None:
         apply_class = "block_apply"
         apply = {"seconds": t_apply, "bytes": block_sweep_bytes_per_cell(args.precision) * n,
-                 "kernel": f"block-ILU0 forward+backward sweeps (k_apply_blocks, one 64-thread "
-                           f"workgroup per subdomain, {g.pb.n_sub} subdomains)"}
+                 "kernel": f"block-ILU0 forward+backward sweeps (k_cols_apply, one workgroup per "
+                           f"subdomain, {g.pb.n_sub} subdomains)"}
     else:
         apply_class = "ilu0_apply"
         apply = {"seconds": t_apply, "bytes": sweep_bytes_per_cell(args.precision) * n,
-                 "kernel": "ilu0 forward+backward sweeps (k_gather_rhs + k_apply_ring2, "
-                           "one workgroup of 512 threads)"}
+                 "kernel": "ilu0 forward+backward sweeps (k_cols_tiles, one workgroup per tile "
+                           "of 8x8 columns)"}
     kernels = {
         apply_class: apply,
         "spmv": {"seconds": t_spmv, "bytes": spmv_b, "kernel": "k_spmv"},
