@@ -444,7 +444,7 @@ __device__ __forceinline__ int xcd_box(int boxes) {
 template <typename T, int NT, int DEPTH, int MODE>
 __global__ __launch_bounds__(NT) void k_cols_apply(ColView<T> v, const double* r, double* x,
                                                     const int32_t* skip, kry::Fused f) {
-  __shared__ double red[NT / 64];
+  __shared__ double red[2 * NT / 64];
   __shared__ int word;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   Lds<T>* nb = (Lds<T>*)reinterpret_cast<T*>(smem);
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(NT + kExchange) void k_cols_tiles(ColView<T> v, con
                                                                 kry::Fused f) {
   typedef ColRows<NT, true> R;
   constexpr int kAll = NT + kExchange;
-  __shared__ double red[kAll / 64];
+  __shared__ double red[2 * kAll / 64];
   __shared__ int word;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   Lds<T>* nb = (Lds<T>*)reinterpret_cast<T*>(smem);

@@ -61,6 +61,29 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return s;
 }
 
+// Both sums at once, each in the order of block_sum (one after the other costs
+// the exchanges' and the barriers' latency twice); sh: 2 NT / kWave values.
+template <int NT>
+__device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    const double oa = __shfl_down(a, off, kWave), ob = __shfl_down(b, off, kWave);
+    a += oa;
+    b += ob;
+  }
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  __syncthreads();
+  if (lane == 0) {
+    sh[2 * w] = a;
+    sh[2 * w + 1] = b;
+  }
+  __syncthreads();
+  a = b = 0.0;
+  for (int k = 0; k < NT / kWave; ++k) {
+    a += sh[2 * k];
+    b += sh[2 * k + 1];
+  }
+}
+
 // max that propagates NaN (fmax would drop it and hide a non-finite residual)
 __device__ __forceinline__ double nan_max(double a, double b) {
   return (a != a || a > b) ? a : b;

@@ -734,7 +734,7 @@ __global__ __launch_bounds__(NT) void k_apply_blocks(IluView<T> v, const int32_t
                                                       int nlev, int max_sub, const double* r,
                                                       double* x, const int32_t* skip,
                                                       kry::Fused f) {
-  __shared__ double red[NT / 64];
+  __shared__ double red[2 * NT / 64];
   __shared__ int word;
   // the skip flag or the iteration's state word (read once for the
   // workgroup) go out together with the level bounds

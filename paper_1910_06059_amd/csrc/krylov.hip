@@ -74,6 +74,16 @@ __device__ __forceinline__ void store_partial(double v, double* part, double* sh
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
+template <int NT>
+__device__ __forceinline__ void store_partials(double a, double* part_a, double b, double* part_b,
+                                               double* sh) {
+  block_sum2<NT>(a, b, sh);
+  if (threadIdx.x == 0) {
+    part_a[blockIdx.x] = a;
+    part_b[blockIdx.x] = b;
+  }
+}
+
 // Keeps a value's computation (and the loads it waits for) ahead of the
 // branches that follow.
 __device__ __forceinline__ void keep_value(double v) { asm volatile("" ::"v"(v)); }
@@ -136,7 +146,7 @@ __global__ __launch_bounds__(kBlock) void k_init2(Work w, int G, double rtol, in
 // Start of an iteration: convergence / cap / breakdown tests on the
 // residual of the previous iteration, then p = r + beta (p - omega v).
 __global__ __launch_bounds__(kBlock) void k_begin(int N, Work w, int G) {
-  __shared__ double sh[kBlock / kWave];
+  __shared__ double sh[2 * kBlock / kWave];
   __shared__ int word;
   Scalars& s = *w.sc;
   const int state = kry::read_state(w.sc, &word);
@@ -209,7 +219,7 @@ template <bool CHECK, int NT>
 __global__ __launch_bounds__(NT) void k_spmv_t(int n, const int32_t* row_ptr,
                                                     const int32_t* col, const double* J, Work w,
                                                     int nss, WellCorr wc) {
-  __shared__ double sh[NT / kWave];
+  __shared__ double sh[2 * NT / kWave];
   __shared__ int word;
   // the state word (read once for the workgroup) and the partials of
   // <s, s> go out first, the first group's products are formed while they
@@ -247,14 +257,13 @@ __global__ __launch_bounds__(NT) void k_spmv_t(int n, const int32_t* row_ptr,
       tt += yv * yv;
     }
   }
-  store_partial<NT>(ts, w.part_ts, sh);
-  store_partial<NT>(tt, w.part_tt, sh);
+  store_partials<NT>(ts, w.part_ts, tt, w.part_tt, sh);
 }
 
 // omega = <t,s>/<t,t>; x += alpha p^ + omega s^; r = s - omega t; partials of
 // <r, r> and <r^, r>.  On a half-step exit only x += alpha p^.
 __global__ __launch_bounds__(kBlock) void k_x(int N, double* x, Work w, int G) {
-  __shared__ double sh[kBlock / kWave];
+  __shared__ double sh[2 * kBlock / kWave];
   Scalars& sc = *w.sc;
   const int state = sc.state;
   const double alpha = sc.alpha;
@@ -281,8 +290,9 @@ __global__ __launch_bounds__(kBlock) void k_x(int N, double* x, Work w, int G) {
     return;
   }
   if (state != kRunning) return;
-  const double ts = block_sum<kBlock>(kry::partials_share<kBlock>(w.part_ts, G, pts), sh);
-  const double tt = block_sum<kBlock>(kry::partials_share<kBlock>(w.part_tt, G, ptt), sh);
+  double ts = kry::partials_share<kBlock>(w.part_ts, G, pts);
+  double tt = kry::partials_share<kBlock>(w.part_tt, G, ptt);
+  block_sum2<kBlock>(ts, tt, sh);
   if (tt == 0.0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       sc.status = OPM_EBREAKDOWN;
@@ -306,8 +316,7 @@ __global__ __launch_bounds__(kBlock) void k_x(int N, double* x, Work w, int G) {
     rr += r * r;
     rhr += w.rh[k] * r;
   }
-  store_partial(rr, w.part_rr, sh);
-  store_partial(rhr, w.part_rhr, sh);
+  store_partials<kBlock>(rr, w.part_rr, rhr, w.part_rhr, sh);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     sc.omega = omega;
     sc.rho0 = rho;

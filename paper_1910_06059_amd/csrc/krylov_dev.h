@@ -107,8 +107,8 @@ __device__ __forceinline__ bool begin_iteration(Scalars& s, int state, const dou
   const int its = s.its, maxit = s.maxit;
   const double tol = s.tol, om_prev = s.omega, rho0 = s.rho0, alpha = s.alpha;
   const double f_rr = partial_first(part_rr, G), f_rhr = partial_first(part_rhr, G);
-  const double rr = block_sum<NT>(partials_share<NT>(part_rr, G, f_rr), sh);
-  const double rho = block_sum<NT>(partials_share<NT>(part_rhr, G, f_rhr), sh);
+  double rr = partials_share<NT>(part_rr, G, f_rr), rho = partials_share<NT>(part_rhr, G, f_rhr);
+  block_sum2<NT>(rr, rho, sh);
   const double rnorm = sqrt(rr);
   int verdict = kRunning, status = OPM_OK;
   if (rnorm <= tol) {
