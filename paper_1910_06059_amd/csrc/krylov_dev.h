@@ -89,25 +89,56 @@ __device__ __forceinline__ double partials_share(const double* part, int G, doub
   return v;
 }
 
-// Start of an iteration: the convergence / iteration-cap / breakdown tests
-// on the residual of the previous iteration.  Returns true if the iteration
-// runs, with beta and omega of p = r + beta (p - omega v).  `state` is the
-// state word as read once for the whole workgroup.
+// All of a thread's partials of a sum of 1 <= G <= kMaxGrid, in registers: loaded
+// at the start of a kernel, ahead of the loads that its sums must not wait for
+// (loads complete in order).  share(): as partials_share.
 template <int NT>
-__device__ __forceinline__ bool begin_iteration(Scalars& s, int state, const double* part_rr,
-                                                const double* part_rhr, int G, double* sh,
-                                                double& beta, double& om) {
+struct Shares {
+  static constexpr int N = (kMaxGrid + NT - 1) / NT;
+  double p[N];
+  __device__ __forceinline__ void load(const double* part, int G) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) p[u] = part[min((int)threadIdx.x + u * NT, G - 1)];
+  }
+  __device__ __forceinline__ double share(int G) const {
+    double v = 0.0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) v += (int)threadIdx.x + u * NT < G ? p[u] : 0.0;
+    return v;
+  }
+};
+
+// What the tests at the start of an iteration and alpha need of the scalars
+// (none of it is written by the kernels that read it here).
+struct IterScalars {
+  int its, maxit;
+  double tol, omega, rho0, alpha, rho;
+  __device__ __forceinline__ void load(const Scalars& s) {
+    its = s.its;
+    maxit = s.maxit;
+    tol = s.tol;
+    omega = s.omega;
+    rho0 = s.rho0;
+    alpha = s.alpha;
+    rho = s.rho;
+  }
+};
+
+// Start of an iteration: the convergence / iteration-cap / breakdown tests
+// on the residual of the previous iteration, from this thread's shares of
+// <r, r> and <r^, r>.  Returns true if the iteration runs, with beta and omega
+// of p = r + beta (p - omega v).  `state` is the state word as read once for the
+// whole workgroup.
+template <int NT>
+__device__ __forceinline__ bool begin_iteration_share(Scalars& s, int state,
+                                                      const IterScalars& c, double rr, double rho,
+                                                      double* sh, double& beta, double& om) {
   if (state != kRunning) {
     if (state == kHalfPending && blockIdx.x == 0 && threadIdx.x == 0) s.state = kDone;
     return false;
   }
-  // the iteration's scalars (not written by this kernel) and both first
-  // partials go out before either sum waits (no load moves above the sums'
-  // barriers)
-  const int its = s.its, maxit = s.maxit;
-  const double tol = s.tol, om_prev = s.omega, rho0 = s.rho0, alpha = s.alpha;
-  const double f_rr = partial_first(part_rr, G), f_rhr = partial_first(part_rhr, G);
-  double rr = partials_share<NT>(part_rr, G, f_rr), rho = partials_share<NT>(part_rhr, G, f_rhr);
+  const int its = c.its, maxit = c.maxit;
+  const double tol = c.tol, om_prev = c.omega, rho0 = c.rho0, alpha = c.alpha;
   block_sum2<NT>(rr, rho, sh);
   const double rnorm = sqrt(rr);
   int verdict = kRunning, status = OPM_OK;
@@ -137,14 +168,30 @@ __device__ __forceinline__ bool begin_iteration(Scalars& s, int state, const dou
   return true;
 }
 
-// alpha = rho / <r^, v> (breakdown on a zero denominator).  Returns true if
-// the iteration goes on.
+// The same with the shares formed here (the scalars and both first partials go
+// out before either sum waits: no load moves above the sums' barriers).
 template <int NT>
-__device__ __forceinline__ bool alpha_step(Scalars& sc, int state, const double* part_rv, int G,
-                                           double* sh, double& alpha) {
+__device__ __forceinline__ bool begin_iteration(Scalars& s, int state, const double* part_rr,
+                                                const double* part_rhr, int G, double* sh,
+                                                double& beta, double& om) {
+  IterScalars c{};
+  double rr = 0.0, rho = 0.0;
+  if (state == kRunning) {
+    c.load(s);
+    const double f_rr = partial_first(part_rr, G), f_rhr = partial_first(part_rhr, G);
+    rr = partials_share<NT>(part_rr, G, f_rr);
+    rho = partials_share<NT>(part_rhr, G, f_rhr);
+  }
+  return begin_iteration_share<NT>(s, state, c, rr, rho, sh, beta, om);
+}
+
+// alpha = rho / <r^, v> (breakdown on a zero denominator), from this thread's
+// share of <r^, v>.  Returns true if the iteration goes on.
+template <int NT>
+__device__ __forceinline__ bool alpha_step_share(Scalars& sc, int state, double rho, double share,
+                                                 double* sh, double& alpha) {
   if (state != kRunning) return false;
-  const double rho = sc.rho;   // (read before the sum's barriers)
-  const double rv = sum_partials<NT>(part_rv, G, sh);
+  const double rv = block_sum<NT>(share, sh);
   if (rv == 0.0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       sc.status = OPM_EBREAKDOWN;
@@ -155,6 +202,14 @@ __device__ __forceinline__ bool alpha_step(Scalars& sc, int state, const double*
   alpha = rho / rv;
   if (blockIdx.x == 0 && threadIdx.x == 0) sc.alpha = alpha;
   return true;
+}
+template <int NT>
+__device__ __forceinline__ bool alpha_step(Scalars& sc, int state, const double* part_rv, int G,
+                                           double* sh, double& alpha) {
+  if (state != kRunning) return false;
+  const double rho = sc.rho;   // (read before the sum's barriers)
+  return alpha_step_share<NT>(sc, state, rho,
+                              partials_share<NT>(part_rv, G, partial_first(part_rv, G)), sh, alpha);
 }
 
 // Half-step exit test ||s|| <= tol on the threads' shares of the partials
