@@ -329,9 +329,15 @@ __global__ __launch_bounds__(256) void k_cols_records(ColView<T> v, FacIn f) {
   if (slot >= g.slots() || a == 3) return;
   const FacSlot r = v.fac[slot];
   const bool live = r.diag != kNoBlock;
+  // (a wait of the recursion gave up: the pivots that went on from zeros are no
+  // factors of this matrix, and every solve with them returns NaN)
+  const bool lost = g.halo && v.gave_up[2] != 0;
   double di[3];
 #pragma unroll
-  for (int e = 0; e < 3; ++e) di[e] = live ? f.dinv64[(size_t)(3 * a + e) * f.ns + r.pos] : 0.0;
+  for (int e = 0; e < 3; ++e)
+    di[e] = !live  ? 0.0
+            : lost ? __builtin_nan("")
+                   : f.dinv64[(size_t)(3 * a + e) * f.ns + r.pos];
   const __amdgpu_buffer_rsrc_t rj = col_rsrc(f.J, (size_t)f.nnzb * 72);
   auto scaled = [&](unsigned o, T* S) {
     double A[9];
