@@ -329,6 +329,9 @@ __global__ __launch_bounds__(256) void k_cols_records(ColView<T> v, FacIn f) {
   if (slot >= g.slots() || a == 3) return;
   const FacSlot r = v.fac[slot];
   const bool live = r.diag != kNoBlock;
+  // (sixteen slots without a cell: nobody reads their records, and they are whole
+  // cache lines; single ones are written, 110 -> 131 us at 500,000 cells otherwise)
+  if (__builtin_amdgcn_ballot_w64(live) == 0) return;
   // (a wait of the recursion gave up: the pivots that went on from zeros are no
   // factors of this matrix, and every solve with them returns NaN)
   const bool lost = g.halo && v.gave_up[2] != 0;
@@ -555,13 +558,14 @@ int allow_lds(K kernel, int slot) {
   return OPM_OK;
 }
 
-int waves_of(const ColGrid& g) { return g.C / kColsPerWave; }
-// threads of a box's workgroup: a power of two of wavefronts
-int threads_of(const ColGrid& g) {
+// threads for a level of that many rows, and of a box's workgroup: a power of
+// two of wavefronts
+int threads_of_rows(int rows) {
   int nt = 64;
-  while (nt < 64 * waves_of(g)) nt *= 2;
+  while (nt / 64 * kColsPerWave < rows) nt *= 2;
   return nt;
 }
+int threads_of(const ColGrid& g) { return threads_of_rows(g.C); }
 
 ColGrid make_grid(const opm_problem* pb, int bx, int by, int bz, bool halo) {
   ColGrid g;
@@ -597,9 +601,7 @@ bool fits(const ColGrid& g) {
   return (long)g.bx * g.by * 4 <= kMaxColThreads && (!g.halo || 3 * (g.bx + g.by) <= 64) && apply_lds<double>(g) <= kMaxColLds &&
          factor_lds(g) <= kMaxColLds && (size_t)g.L * g.C * 288 < ((size_t)1 << 30) &&
          (!g.halo || (g.bx + g.by <= kHaloRows && g.nbz == 1)) && g.n < (1 << 26) &&
-         // at most twice as many slots as cells of the lattice, or few of them
-         g.slots() < ((size_t)1 << 31) &&   // (32-bit slot numbers)
-         (g.slots() <= 2 * (size_t)g.nx * g.ny * g.nz || g.slots() <= 65536);
+         g.slots() < ((size_t)1 << 31);   // (32-bit slot numbers)
 }
 
 bool lattice(const opm_problem* pb) {
@@ -608,14 +610,54 @@ bool lattice(const opm_problem* pb) {
          (size_t)pb->nnzb * 72 < 0xfffffe00u;   // (byte offsets into the Jacobian)
 }
 
+// The storage has a slot for every level and column of a box, with a cell or
+// without: 604 bytes each (FP64, tiles; FP32 340), the position lists 1170 (670)
+// per cell.  How many slots there may be, by what was measured:
+constexpr size_t kFewSlots = (size_t)1 << 20;   // 0.6 GB
+
+// The whole system by columns was faster at every share of active cells: the
+// other shapes walk its levels one after another in one workgroup or by launches
+// (an iteration of BiCGStab, 100 x 100 x 50 all active / 40 % / 15 % / 4 %: 1133 / 802 /
+// 574 / 555 us against 2479 / 4569 / 2265 / 1003; 50 x 50 x 12, 2.7 slots per cell, 318
+// against 960; 200 x 200 x 5, 3.8 slots per cell, 1244 against 5701).  32 slots per
+// cell, the sparsest of these, keep the storage in proportion.
+bool worth_whole(const ColGrid& g) { return g.slots() <= std::max(32 * (size_t)g.n, kFewSlots); }
+
+// Subdomains: the position lists serve them with one workgroup each, too.
+bool worth_blocks(const opm_problem* pb, const ColGrid& g, int precision) {
+  // A level costs a barrier over the workgroup, so columns do not pay where the
+  // widest level would need half their wavefronts: an iteration with 8 x 8 x 3
+  // boxes (22 rows) 43 us against 36, 11 x 11 x 3 (31 rows) 74 against 47, 8 x 8 x 30 at
+  // 12 % active (30 rows) 80 against 69; at 15 % (37 rows) 81 against 85.  Two
+  // wavefronts against one: equal within 5 %.
+  const int nt = threads_of(g);
+  if (nt > 128 && threads_of_rows(pb->max_width) < nt) return false;
+  // What is left in the 256 MB last-level cache between two sweeps (J and the
+  // records, about 1 kB per cell, and the vectors) is bound by its levels, and
+  // columns have the cheaper ones: 125,000 of 500,000 places active, 4.5 slots
+  // per cell, 103 us against 114; 120 x 100 x 10 in 2 x 2 x 10, 4.8 slots per cell, 103
+  // against 103.
+  if (g.n <= (1 << 17) && g.slots() <= kFewSlots) return true;
+  // Larger systems are bound by bytes, of which a place without a cell beside
+  // one with a cell costs its share of a cache line: 100 x 100 x 50 in 4 x 4 columns, 70 %
+  // active (1.6 slots per cell) 242 us against 243 and 250 against 259, 60 % (1.9)
+  // 218 against 214, 40 % (2.8) 153 against 140; 8 x 8 columns, 70 % (2.0) 270
+  // against 270 and 278 against 294, 40 % (3.5) 184 against 153; full ones, 3 x 3 x 50
+  // (2.0) 334 against 331 with the factorisation 345 against 445, 8 x 8 x 10 (2.6)
+  // 370 against 362, 4 x 4 x 4 (2.6) 371 against 333.  FP32 factors take half of
+  // these: 40 % active 106 against 126 and 128 against 140; 4 x 4 x 4 292 against 278.
+  return g.slots() <= 2 * (size_t)g.nx * g.ny * g.nz &&
+         g.slots() <= (precision == OPM_PREC_MIXED ? 4 : 2) * (size_t)g.n;
+}
+
 // The boxes of a problem's preconditioner; false: not by columns.
-bool grid_of(const opm_problem* pb, ColGrid& g) {
+bool grid_of(const opm_problem* pb, int precision, ColGrid& g) {
   if (!lattice(pb)) return false;
   if (pb->n_sub > 1) {
     const int bx = pb->ilu_box & 1023, by = (pb->ilu_box >> 10) & 1023, bz = (pb->ilu_box >> 20) & 1023;
     if (bx <= 0 || by <= 0 || bz <= 0) return false;
     g = make_grid(pb, bx, by, bz, false);
-    return fits(g);
+    return fits(g) && worth_blocks(pb, g, precision);
   }
   // the whole system: one box of at most 128 columns (300 cells: an
   // application 28 -> 24 us, and the updates of BiCGStab fused into it, 8
@@ -623,10 +665,10 @@ bool grid_of(const opm_problem* pb, ColGrid& g) {
   // application 1120 us by planes -> 392 us; factored 1900 -> 766 us)
   if ((long)pb->nx * pb->ny <= 128) {
     g = make_grid(pb, pb->nx, pb->ny, pb->nz, false);
-    if (fits(g)) return true;
+    if (fits(g) && worth_whole(g)) return true;
   }
   g = make_grid(pb, 8, 8, pb->nz, true);
-  return fits(g);
+  return fits(g) && worth_whole(g);
 }
 
 template <typename T>
@@ -754,20 +796,20 @@ int apply_impl(const opm_problem* pb, const ColGrid& g, void* ilu, const double*
 }  // namespace
 
 // The preconditioner of pb is factored and applied by columns.
-bool cols_capable(const opm_problem* pb) {
+bool cols_capable(const opm_problem* pb, int precision) {
   ColGrid g;
-  return grid_of(pb, g);
+  return grid_of(pb, precision, g);
 }
 
 // Workgroups of a sweep (the partial sums of a fused one).
-int cols_boxes(const opm_problem* pb) {
+int cols_boxes(const opm_problem* pb, int precision) {
   ColGrid g;
-  return grid_of(pb, g) ? g.boxes() : 0;
+  return grid_of(pb, precision, g) ? g.boxes() : 0;
 }
 
 size_t cols_bytes(const opm_problem* pb, int precision) {
   ColGrid g;
-  if (!grid_of(pb, g)) return 0;
+  if (!grid_of(pb, precision, g)) return 0;
   return precision == OPM_PREC_MIXED ? pivot_bytes<float>(pb) + view_bytes_of<float>(g)
                                      : pivot_bytes<double>(pb) + view_bytes_of<double>(g);
 }
@@ -775,7 +817,7 @@ size_t cols_bytes(const opm_problem* pb, int precision) {
 int cols_factor(const opm_problem* pb, const double* J, void* ilu, int precision,
                 int32_t* status, hipStream_t s) {
   ColGrid g;
-  if (!grid_of(pb, g)) return OPM_EINVAL;
+  if (!grid_of(pb, precision, g)) return OPM_EINVAL;
   return precision == OPM_PREC_MIXED ? factor_impl<float>(pb, g, J, ilu, status, s)
                                      : factor_impl<double>(pb, g, J, ilu, status, s);
 }
@@ -785,7 +827,7 @@ int cols_factor(const opm_problem* pb, const double* J, void* ilu, int precision
 int cols_apply(const opm_problem* pb, void* ilu, int precision, int mode, const double* r,
                double* x, const int32_t* skip, const kry::Fused& f, hipStream_t s) {
   ColGrid g;
-  if (!grid_of(pb, g)) return OPM_EINVAL;
+  if (!grid_of(pb, precision, g)) return OPM_EINVAL;
   if (precision == OPM_PREC_MIXED) {
     switch (mode) {
       case kry::kFuseBegin: return apply_impl<float, kry::kFuseBegin>(pb, g, ilu, r, x, skip, f, s);

@@ -38,8 +38,8 @@
 
 namespace opm {
 
-bool cols_capable(const opm_problem* pb);
-int cols_boxes(const opm_problem* pb);
+bool cols_capable(const opm_problem* pb, int precision);
+int cols_boxes(const opm_problem* pb, int precision);
 size_t cols_bytes(const opm_problem* pb, int precision);
 int cols_factor(const opm_problem* pb, const double* J, void* ilu, int precision,
                 int32_t* status, hipStream_t s);
@@ -1557,7 +1557,7 @@ int g_block_depth = 0;
 // subdomain's vector fits in LDS; modes 0 and 1 also serve it (same
 // factors and sweeps, level by level over the whole system).
 int sweep_mode(const opm_problem* pb, int precision) {
-  if (g_sweep_mode == -1 && cols_capable(pb)) return 3;
+  if (g_sweep_mode == -1 && cols_capable(pb, precision)) return 3;
   if (g_sweep_mode == 0 || g_sweep_mode == 1) {
     if (g_sweep_mode == 0 && pb->max_level > kMaxWindowRows) return 1;
     return g_sweep_mode;
@@ -1581,7 +1581,7 @@ int ilu_factor(const opm_problem* pb, const double* J, void* ilu, int precision,
 // Workgroups of a fused solve (its partial sums of <s, s>); 0: not fused.
 int ilu_fused_groups(const opm_problem* pb, int precision) {
   const int mode = sweep_mode(pb, precision);
-  const int g = mode == 3 ? cols_boxes(pb) : mode == 2 ? pb->n_sub : 0;
+  const int g = mode == 3 ? cols_boxes(pb, precision) : mode == 2 ? pb->n_sub : 0;
   return g <= kry::kMaxGrid ? g : 0;
 }
 
