@@ -63,3 +63,26 @@ def test_storage_in_proportion_to_cells(dims, blk, share):
     whole system at most 32."""
     got, n = _bytes(dims, blk, None if share == 1.0 else _some(dims, share))
     assert got <= max(1400 * n if blk else 32 * 640 * n, 640 << 20), (got / n, n)
+
+
+@pytest.mark.parametrize("box", [
+    -1, 0x7fffffff, 1 << 30 | 4 | 4 << 10 | 15 << 20, 4 | 4 << 10, 25 | 4 << 10 | 15 << 20,
+    2 | 2 << 10 | 15 << 20, 4 | 4 << 10 | 14 << 20, 5 | 4 << 10 | 15 << 20, 8 | 2 << 10 | 15 << 20,
+    0x00cdcdcd])
+def test_box_of_another_topology_is_not_taken(box):
+    """A box that the counts of the topology contradict (a field that was never
+    set): by position, as without a box."""
+    dims, blk = (24, 25, 15), (4, 4, 15)
+    n, nf, host, topo, b = opm.build_topology(*dims, np.ones(dims[::-1], bool), blk)
+    there = host["row_ptr"].ctypes.data
+    pb = opm.Problem(n_cells=n, n_faces=nf, nnzb=n + 2 * nf, n_levels=topo.n_levels,
+                     max_level=topo.max_level, sweep_span=topo.sweep_span, row_ptr=there,
+                     iperm=there, lo_blk=there, up_blk=there, n_sub=b.n_sub, max_sub=b.max_sub,
+                     max_width=b.max_width, nx=24, ny=25, nz=15, box_cell=there, cell_box=there)
+    size = opm.lib().opm_ilu0_bytes
+    plain = size(pb, opm.PREC_FP64)
+    pb.ilu_box = 4 | 4 << 10 | 15 << 20
+    # (63 doubles, an index and a 32-byte record for each of 42 x 21 x 16 slots)
+    assert size(pb, opm.PREC_FP64) >= 42 * 21 * 16 * (63 * 8 + 36)
+    pb.ilu_box = box
+    assert size(pb, opm.PREC_FP64) == plain

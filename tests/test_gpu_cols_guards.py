@@ -48,3 +48,49 @@ def test_tile_factorisation_gives_up_with_nan(opm, precision):
     assert torch.isnan(g.ilu0_apply(ilu, R, precision)).all()
     _factor(opm, g, J, ilu, None, precision)
     assert torch.equal(g.ilu0_apply(ilu, R, precision), ref)
+
+
+def _blocks(opm, dims, blk):
+    case = cases.box_case(*dims, seed=3)
+    g = opm.GpuModel(case, ilu_blocks=blk, amg=False)
+    y = g.state(cases.random_state(case, 5))
+    R, J, _ = g.assemble(y, g.accumulation(g.state(cases.random_state(case, 6))), DAY)
+    return g, R, J
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_box_that_was_never_set(opm, precision):
+    """A box that the topology's counts contradict: factors and solution by
+    position, bitwise those of the right box."""
+    g, R, J = _blocks(opm, (24, 25, 15), (4, 4, 15))
+    ilu, _ = g.ilu0_factor(J, precision)
+    ref = g.ilu0_apply(ilu, R, precision)
+    for box in (-1, 0x7fffffff, 2 | 2 << 10 | 15 << 20, 0x00cdcdcd):
+        g.pb.ilu_box = box
+        ilu, status = g.ilu0_factor(J, precision)
+        assert int(status.item()) == 0
+        assert torch.equal(g.ilu0_apply(ilu, R, precision), ref), hex(box)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_transposed_box_is_refused(opm, precision):
+    """A box with the counts of the topology's own but other subdomains:
+    OPM_EINVAL where a status is given, and no finite solution; the Newton step
+    returns OPM_EINVAL.  With the right box everything is as before."""
+    g, R, J = _blocks(opm, (12, 12, 6), (2, 6, 6))
+    right = g.pb.ilu_box
+    ilu, status = g.ilu0_factor(J, precision)
+    assert int(status.item()) == 0
+    ref = g.ilu0_apply(ilu, R, precision)
+    g.pb.ilu_box = 6 | 2 << 10 | 6 << 20
+    ilu, status = g.ilu0_factor(J, precision)
+    assert int(status.item()) == opm.EINVAL
+    _factor(opm, g, J, ilu, None, precision)
+    x = g.ilu0_apply(ilu, R, precision)
+    assert torch.isnan(x).any() and not torch.isfinite(x.sum())
+    y = g.initial_state()
+    with pytest.raises(opm.OpmError):
+        g.newton_step(y, g.initial_state(), DAY, opm.default_opts(g.case, precision=precision))
+    g.pb.ilu_box = right
+    ilu, status = g.ilu0_factor(J, precision)
+    assert int(status.item()) == 0 and torch.equal(g.ilu0_apply(ilu, R, precision), ref)
