@@ -64,28 +64,36 @@ struct LdsPlan {
   size_t red, sweep, fac, total;
 };
 
-inline size_t window_bytes(size_t tsize, int max_level) { return tsize * 2 * 3 * (size_t)max_level; }
+__host__ __device__ inline size_t window_bytes(size_t tsize, int max_level) { return tsize * 2 * 3 * (size_t)max_level; }
 inline size_t ring_bytes(size_t tsize, const opm_problem& pb) {
   return tsize * 3 * (size_t)ilu::ring_rows(pb.sweep_span, pb.max_level);
 }
 
 // The sweep storage of k_ensemble_mw: the window (the cell marks of its row
-// list share its place, where they take no more than kMaxMarks), then two
-// level bounds per level.
+// list share its place), then two level bounds per level.  Where both do not fit
+// beside the window the marks go first (the list is then by level), then the
+// bounds (the sweeps then read them from memory): a shape whose window fits is
+// never refused, and with 128 threads two workgroups fit a compute unit if their
+// windows do.  The kernel tells by the size which of them it has.
 constexpr size_t kMaxMarks = 64 * 1024;
-size_t mw_sweep_bytes(const opm_problem* members, int n, size_t tsize, int width) {
+inline size_t red_bytes(int threads) { return sizeof(double) * 2 * (threads / kWave); }
+size_t mw_sweep_bytes(const opm_problem* members, int n, size_t tsize, int width, int threads) {
   size_t marks = 0, levels = 0;
   for (int m = 0; m < n; ++m) {
     marks = std::max(marks, sizeof(unsigned) * (((size_t)members[m].n_cells + 31) / 32));
     levels = std::max(levels, (size_t)members[m].n_levels);
   }
-  return al256(std::max(al256(window_bytes(tsize, width)), marks <= kMaxMarks ? marks : 0) +
-               2 * sizeof(int) * levels);
+  const size_t win = al256(window_bytes(tsize, width)), fixed = al256(red_bytes(threads));
+  const size_t room = threads == 128 && fixed + win <= kEnsLds / 2 ? kEnsLds / 2 : kEnsLds;
+  const size_t bounds = 2 * sizeof(int) * levels;
+  const size_t all = al256(std::max(win, marks <= kMaxMarks ? marks : 0) + bounds);
+  if (fixed + all <= room) return all;
+  return fixed + al256(win + bounds) <= room ? al256(win + bounds) : win;
 }
 
 LdsPlan lds_plan(size_t tsize, int threads, size_t sweep_bytes, int max_level, bool fac_window) {
   LdsPlan p;
-  p.red = sizeof(double) * 2 * (threads / kWave);
+  p.red = red_bytes(threads);
   p.sweep = al256(sweep_bytes);
   p.fac = fac_window ? sizeof(double) * 2 * 9 * (size_t)max_level : 0;
   p.total = al256(p.red) + p.sweep + p.fac;
@@ -761,7 +769,7 @@ __device__ __forceinline__ void mw_sweep(const Topo& t, IluView<T> v, const doub
 template <typename T, int NT>
 __device__ __forceinline__ void mw_apply(const Topo& t, IluView<T> v, const double* r, double* x,
                                          T* win, const int* lvl) {
-  if (t.max_level > NT) {   // levels wider than the workgroup
+  if (t.max_level > NT || !lvl) {   // levels wider than the workgroup, no room for their bounds
     ilu::apply_levels_wg<T, NT>(t, v, r, x, win);
     return;
   }
@@ -1026,12 +1034,15 @@ __global__ __launch_bounds__(NT) void k_ensemble_mw(const EnsMember* tab, const 
   tp.max_level = W.width;
   Grp G{W.w, W.g, part + (size_t)2 * kPartStride * (blockIdx.x - W.w), sync + W.m, spin, 0};
   IluView<T> iv = ilu::view<T>(&M.pb, M.ilu);
-  // the level bounds lie behind the sweep window
-  const size_t lvl_bytes = 2 * sizeof(int) * (size_t)tp.nlev;
+  // the level bounds lie behind the sweep window, where there is room for them
+  size_t lvl_bytes = 2 * sizeof(int) * (size_t)tp.nlev;
+  if ((window_bytes(sizeof(T), W.width) + 255) / 256 * 256 + lvl_bytes > sweep_bytes) lvl_bytes = 0;
   const Rows rows = list_rows<NT>(tp, M.pb.n_cells, M.rows, reinterpret_cast<unsigned*>(swin),
                                   sweep_bytes - lvl_bytes);
-  int* lvl = reinterpret_cast<int*>(reinterpret_cast<char*>(swin) + sweep_bytes - lvl_bytes);
-  for (int l = threadIdx.x; l < tp.nlev; l += NT) {
+  int* lvl = lvl_bytes != 0
+                 ? reinterpret_cast<int*>(reinterpret_cast<char*>(swin) + sweep_bytes - lvl_bytes)
+                 : nullptr;
+  for (int l = threadIdx.x; lvl && l < tp.nlev; l += NT) {
     lvl[2 * l] = ilu::lvl_begin(tp, l);
     lvl[2 * l + 1] = ilu::lvl_end(tp, l);
   }
@@ -1422,7 +1433,7 @@ int opm_ensemble_configure(const opm_problem* members, int32_t n_members, int pr
     int width = 0;
     for (const EnsWg& e : wt) width = std::max(width, e.width);
     const size_t ts = precision == OPM_PREC_MIXED ? sizeof(float) : sizeof(double);
-    c.sweep_bytes = (int32_t)mw_sweep_bytes(members, n_members, ts, width);
+    c.sweep_bytes = (int32_t)mw_sweep_bytes(members, n_members, ts, width, c.threads);
     if (lds_plan(ts, c.threads, (size_t)c.sweep_bytes, width, false).total > kEnsLds)
       return OPM_EINVAL;
   } else if (!plan_members(members, n_members, precision, c, &ring, &max_level)) {
