@@ -1288,16 +1288,31 @@ int build_wg_table(const opm_problem* members, int n, int budget, std::vector<En
         p.rows[sd] += p.slp[l * ns1 + sd + 1] - p.slp[l * ns1 + sd];
     p.first = {0, pb.n_sub};
   }
-  // the fewest workgroups that make the largest range smaller: the largest
-  // sums of neighbouring subdomains below it are the candidates
-  auto smaller = [](const Plan& p) {
-    long best = 0;
-    for (size_t s = 0; s < p.rows.size(); ++s) {
-      long acc = 0;
-      for (size_t e = s; e < p.rows.size() && acc + p.rows[e] < p.largest; ++e) acc += p.rows[e];
+  // the fewest workgroups that make the largest range smaller: those that the
+  // largest sum of neighbouring subdomains below it takes, their largest range
+  // then as small as that many can have it
+  auto smaller = [](const Plan& p) -> std::vector<int> {
+    const std::vector<long>& rows = p.rows;
+    long best = 0, acc = 0;
+    for (size_t s = 0, e = 0; s < rows.size(); ++s) {   // subdomains s .. e - 1
+      if (e < s) e = s;
+      while (e < rows.size() && acc + rows[e] < p.largest) acc += rows[e++];
       best = std::max(best, acc);
+      if (e > s) acc -= rows[s];
     }
-    return best > 0 ? split_ranges(p.rows, best) : std::vector<int>{};
+    std::vector<int> f = best > 0 ? split_ranges(rows, best) : std::vector<int>{};
+    long lo = 0;   // too small for that many
+    while (!f.empty() && best - lo > 1) {
+      const long mid = lo + (best - lo) / 2;
+      std::vector<int> g = split_ranges(rows, mid);
+      if (g.empty() || g.size() > f.size()) {
+        lo = mid;
+      } else {
+        best = mid;
+        f.swap(g);
+      }
+    }
+    return f;
   };
   std::vector<char> done(n, 0);
   for (;;) {
