@@ -128,20 +128,6 @@ __device__ __forceinline__ bool is_unset(float v) {
   return __builtin_bit_cast(unsigned, v) == 0x7FA5A5A5u;
 }
 
-// The re-read of a value found not yet written (the slow path): the load and
-// its wait in one block, so that the compiler counts no load of this loop
-// among those in flight (a counted load here would make it wait for every
-// prefetch issued since, at the next use of any of them).
-__device__ __forceinline__ double coherent_reread(const double* p) {
-  unsigned long long b;
-  asm volatile("global_load_dwordx2 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
-  return __builtin_bit_cast(double, b);
-}
-__device__ __forceinline__ float coherent_reread(const float* p) {
-  unsigned b;
-  asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
-  return __builtin_bit_cast(float, b);
-}
 // Value of lane K of the lane's quad (DPP quad permutation: a VALU move, no
 // LDS round trip).
 template <int K>

@@ -682,9 +682,10 @@ __device__ __forceinline__ void spmv_rows(const Rows& r, const opm_problem& pb, 
 
 // x = (LU)^{-1} r for the workgroup's rows: the sweeps of wg_sweep with the
 // level bounds in LDS (`lvl`, two per level; so a level's loads wait for no
-// other load), one (FP32: two) levels of rows in flight (jobs in turn, every load
-// clamped and in straight-line code), and every neighbour value from the LDS
-// window (a row's neighbours lie on the level just finished).
+// other load), the next level's rows in flight while one is computed (two jobs in
+// turn, every load clamped and in straight-line code; a third job spilled), and
+// every neighbour value from the LDS window (a row's neighbours lie on the level
+// just finished).
 template <typename T, bool FWD>
 __device__ __forceinline__ void mw_row(const ilu::SweepJob<T>& j, IluView<T> v, double* x, T* win,
                                        int L, int par, int prev0, int p0, int pos) {
@@ -709,7 +710,6 @@ __device__ __forceinline__ void mw_row(const ilu::SweepJob<T>& j, IluView<T> v, 
 template <typename T, int NT, bool FWD>
 __device__ __forceinline__ void mw_sweep(const Topo& t, IluView<T> v, const double* r, double* x,
                                          T* win, const int* lvl) {
-  constexpr int ND = 2;
   const int L = t.max_level, tid = threadIdx.x;
   auto level = [&](int k) {
     const int kc = min(k, t.nlev - 1);
@@ -720,7 +720,7 @@ __device__ __forceinline__ void mw_sweep(const Topo& t, IluView<T> v, const doub
     return max(min(lvl[2 * l] + tid, lvl[2 * l + 1] - 1), 0);
   };
   auto cell_of = [&](int k) { return t.perm[position(k)]; };
-  // the row of level k, its cell loaded ND steps ago (older than any load that
+  // the row of level k, its cell loaded two steps ago (older than any load that
   // a level waits for)
   auto fetch = [&](int k, int& cell, ilu::SweepJob<T>& j) __attribute__((always_inline)) {
     const unsigned ns = (unsigned)v.ns, up = (unsigned)position(k);
@@ -737,31 +737,24 @@ __device__ __forceinline__ void mw_sweep(const Topo& t, IluView<T> v, const doub
     if (FWD)
 #pragma unroll
       for (unsigned e = 0; e < 9; ++e) j.D[e] = v.dinv[e * ns + up];
-    cell = cell_of(k + ND);
+    cell = cell_of(k + 2);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
   int prev0 = 0;
-  // level k from `own`, the level ND - 1 behind it into `last`
-  auto step = [&](int k, int par, const ilu::SweepJob<T>& own, ilu::SweepJob<T>& last, int& cell)
+  // level k from `own`, the next one into `next`
+  auto step = [&](int k, int par, const ilu::SweepJob<T>& own, ilu::SweepJob<T>& next, int& cell)
       __attribute__((always_inline)) {
     const int l = level(k), p0 = lvl[2 * l], p1 = lvl[2 * l + 1];
-    fetch(k + ND - 1, cell, last);
+    fetch(k + 1, cell, next);
     if (p0 + tid < p1) mw_row<T, FWD>(own, v, x, win, L, par, prev0, p0, p0 + tid);
     __syncthreads();
     prev0 = p0;
     return k + 1 < t.nlev;
   };
-  ilu::SweepJob<T> a, b, c;
-  int ca = cell_of(0), cb = cell_of(1), cc = ND == 3 ? cell_of(2) : 0;
+  ilu::SweepJob<T> a, b;
+  int ca = cell_of(0), cb = cell_of(1);
   fetch(0, ca, a);
-  if (ND == 3) {
-    fetch(1, cb, b);
-    for (int k = 0;; k += 6)
-      if (!step(k, 0, a, c, cc) || !step(k + 1, 1, b, a, ca) || !step(k + 2, 0, c, b, cb) ||
-          !step(k + 3, 1, a, c, cc) || !step(k + 4, 0, b, a, ca) || !step(k + 5, 1, c, b, cb))
-        return;
-  }
   for (int k = 0;; k += 2)
     if (!step(k, 0, a, b, cb) || !step(k + 1, 1, b, a, ca)) return;
 }

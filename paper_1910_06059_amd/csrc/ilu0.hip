@@ -984,6 +984,21 @@ __device__ __forceinline__ void coherent_store(float* p, float x) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The re-read of a value found not yet written (the slow path): the load and
+// its wait in one block, so that the compiler counts no load of this loop
+// among those in flight (a counted load here would make it wait for every
+// prefetch issued since, at the next use of any of them).
+__device__ __forceinline__ double coherent_reread(const double* p) {
+  unsigned long long b;
+  asm volatile("global_load_dwordx2 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
+  return __builtin_bit_cast(double, b);
+}
+__device__ __forceinline__ float coherent_reread(const float* p) {
+  unsigned b;
+  asm volatile("global_load_dword %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=v"(b) : "v"(p));
+  return __builtin_bit_cast(float, b);
+}
+
 // A row of a plane step: its sweep data, and the value of its off-plane
 // neighbour (loaded with the data; re-read at use while it holds the marker).
 template <typename T>
