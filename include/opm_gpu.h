@@ -379,17 +379,21 @@ typedef struct opm_problem {
    * bx | by << 10 | bz << 20 (each axis at most 1023 cells, the bx, by, bz
    * given to opm_topology_build_blocks, at most the lattice's).  With it, or
    * without a block topology, the ILU(0) is factored and swept by lattice
-   * columns, one workgroup per subdomain or per tile of the whole system;
-   * otherwise by the position lists below.  Both give the same factors and
-   * solutions. */
+   * columns, one workgroup per subdomain or per tile of the whole system,
+   * where the share of active cells and the shape of the boxes suit that;
+   * otherwise by the position lists.  Both give the same factors and
+   * solutions.  A box that the counts of the topology (n_sub, max_sub,
+   * n_levels) contradict is ignored; one with the right counts but other
+   * subdomains is found by the factorisation (OPM_EINVAL in its status). */
   int32_t nx, ny, nz, ilu_box;
   const int32_t* box_cell;
   /* cell_box [n_cells] (device): the box index of each active cell (the
-   * inverse of box_cell).  With both maps, the ILU(0) sweeps of a system
-   * too large for one workgroup run plane by plane in one launch each: one
-   * workgroup per z-plane walks the plane's diagonals i + j, and a row waits
-   * only for the value of its neighbour in the plane below (forward) or
-   * above (backward).  NULL: one launch per level. */
+   * inverse of box_cell).  Both maps are needed for the ILU(0) by columns
+   * (see ilu_box).  Where a system too large for one workgroup does not go by
+   * columns, its sweeps run plane by plane in one launch each with both maps
+   * (a workgroup per z-plane walks the plane's diagonals i + j, and a row waits
+   * only for the value of its neighbour in the plane below or above), and in
+   * one launch per level without. */
   const int32_t* cell_box;
 } opm_problem;
 
@@ -446,11 +450,13 @@ size_t opm_ilu0_bytes(const opm_problem* pb, int precision);
 /* Block ILU(0) of J (sec. 2.3.1) into ilu (device, opm_ilu0_bytes): the
  * inverse pivot blocks D_i^{-1} with D_i = A_ii - sum_{k<i} A_ik D_k^{-1} A_ki
  * (exact ILU(0) for a pattern without triangles, which the 7-point TPFA
- * stencil is) and level-ordered copies of the off-diagonal blocks, in FP64 or
+ * stencil is) and copies of the off-diagonal blocks scaled by them, in FP64 or
  * FP32.  status (device int, may be NULL) receives OPM_ESINGULAR on a zero or
- * non-finite pivot, and OPM_EHIP if the plane-pipelined factorisation of a
- * lattice system (OPM_OPT_PLANE_SWEEP) gave up waiting for a neighbouring
- * plane (OPM_OPT_PLANE_SPIN). */
+ * non-finite pivot, OPM_EHIP if the factorisation of a whole lattice gave up
+ * waiting for a neighbouring tile or plane (OPM_OPT_PLANE_SPIN), and
+ * OPM_EINVAL if ilu_box is not the topology's box; after the last two a solve
+ * with the factors returns NaN, with or without a status.  The factors are
+ * applied with the OPM_OPT_SWEEP_MODE that they were made with. */
 int opm_ilu0_factor(const opm_problem* pb, const double* J, void* ilu, int precision,
                     int32_t* status, void* stream);
 
@@ -813,7 +819,8 @@ int opm_advance_guess(const opm_problem* pb, double* y, const double* y_nm1, dou
  * opm_ensemble_configure); wgs: 0 one workgroup per member, else (in) the
  * workgroups of the launch (at least n_members, at most 2048, ring 0):
  * members built with a block-ILU0 topology (opm_topology_build_blocks) get
- * workgroups in proportion to their rows, at most one per subdomain, each
+ * workgroups where their ranges are the largest (none where one more would
+ * not make a member's largest range smaller), at most one per subdomain, each
  * owning a contiguous range of the member's subdomains (its rows in
  * assembly, vector operations and SpMV, its subdomains in the factorisation
  * and sweeps), the member's workgroups meeting at device-memory barriers
@@ -864,17 +871,22 @@ int opm_ensemble_autotune(const opm_problem* members, int32_t n_members, int pre
  * option or value.
  *   OPM_OPT_SWEEP_MODE: ILU(0) factor/sweep launch shape: -1 automatic,
  *     0 one workgroup walks all levels, 1 one launch per level, 2 (block
- *     ILU0 topologies; else automatic) one workgroup per subdomain, also
- *     for a single subdomain.  Automatic picks 2 for a block ILU0 topology
- *     of two or more subdomains whose subdomain vector fits in LDS.
+ *     ILU0 topologies; else automatic) one workgroup per subdomain by
+ *     position lists, also for a single subdomain.  Automatic takes a lattice
+ *     by columns (opm_problem.ilu_box, cell_box), which no value forces; else
+ *     2 for a block ILU0 topology of two or more subdomains whose subdomain
+ *     vector fits in LDS; else 0 or 1 by size.  Set before the factorisation:
+ *     its factors are applied with the same mode.
  *   OPM_OPT_KRYLOV_CHUNK: BiCGStab iterations enqueued between reads of the
  *     convergence state (0 automatic, else >= 1).
- *   OPM_OPT_SWEEP_KERNEL: the one-workgroup LDS-ring sweep: 0 automatic,
+ *   OPM_OPT_SWEEP_KERNEL: the one-workgroup LDS-ring sweep (mode 0; without
+ *     effect on a lattice that goes by columns): 0 automatic,
  *     1 right-hand side gathered inside the sweep, 2-6 right-hand side
  *     gathered into level order first and branch-free prefetch with 512,
  *     256 or 128 threads (2, 3, 4) or with wavefronts that have no row in a
  *     level skipping their loads (5: 512, 6: 256 threads).
- *   OPM_OPT_BLOCK_DEPTH: block-ILU0 sweeps, levels whose data is loaded
+ *   OPM_OPT_BLOCK_DEPTH: block-ILU0 sweeps by position lists (mode 2; without
+ *     effect on a lattice that goes by columns), levels whose data is loaded
  *     while a level is computed: 0 automatic (2 for the sweeps fused with
  *     BiCGStab, and for the others on a system of 256 or more subdomains;
  *     else 1), 1 or 2.
@@ -886,13 +898,16 @@ int opm_ensemble_autotune(const opm_problem* members, int32_t n_members, int pre
  *     allows it (box_cell set, dead oil, fixed-source wells), 0 always the
  *     row-per-lane assembly.
  *   OPM_OPT_PLANE_SWEEP: factorisation and sweeps of the ILU(0) of a large
- *     system (sweep mode 1): 1 (default) plane-pipelined where box_cell and
+ *     system (mode 1; without effect on a lattice that goes by columns):
+ *     1 (default) plane-pipelined where box_cell and
  *     cell_box are set (one workgroup per z-plane), 0 one launch per level.
- *   OPM_OPT_PLANE_SPIN: re-reads a plane sweep makes of a value of the
- *     neighbouring plane that is not yet written before it gives up
+ *   OPM_OPT_PLANE_SPIN: re-reads that a factorisation or sweep of a whole
+ *     lattice makes of a value of a neighbouring tile (by columns) or plane
+ *     that is not yet written before it gives up
  *     (default 262144; 0 gives up at once, to exercise the failure path): a
  *     sweep that gives up returns NaN, so the Krylov solver reports
- *     non-finite values instead of hanging.
+ *     non-finite values instead of hanging; a factorisation reports OPM_EHIP
+ *     and leaves factors that solve to NaN.
  *   OPM_OPT_ENSEMBLE_SPIN: polls a member barrier of an ensemble launch
  *     with several workgroups per member makes before it gives up (default
  *     4194304; 0 gives up at once, to exercise the failure path): the

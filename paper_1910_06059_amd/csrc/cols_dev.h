@@ -18,7 +18,7 @@
 // lane; here it is one LDS write, four reads, 12 fused multiply-adds and the
 // loads of a later level (about 55 instructions, 0.11-0.14 us per level of a
 // 4x4 box, against 0.24 us).  One application, both sweeps, by HIP events:
-// 9000 cells in 4x4x10 boxes 10.6 -> 6.7 us FP64, 10.1 -> 5.8 us FP32; 500k
+// 9000 cells in 4x4x15 boxes 10.6 -> 6.7 us FP64, 10.1 -> 5.8 us FP32; 500k
 // cells in 4x4x50 boxes 56.8 -> 48.3 us (bound by bandwidth: 63 values per row
 // instead of 72), FP32 33.8 -> 24.4 us.  The dynamic LDS must be declared
 // 16-byte aligned: behind a static 4-byte word its 8-byte reads were misaligned
@@ -174,12 +174,10 @@ struct BlockRhs {
 struct ColLane {
   int c, eq, ci, cj;
   int lag;       // level of the column's first cell (far past the last level: no column)
-  bool in_box;   // a column of the box, eq < 3
   __device__ __forceinline__ explicit ColLane(const ColGrid& g) {
     const int tid = (int)threadIdx.x;
     c = tid >> 2;
     eq = tid & 3;
-    in_box = c < g.bx * g.by && eq < 3;
     cj = c / g.bx;
     ci = c - cj * g.bx;
     lag = c < g.bx * g.by ? ci + cj : 1 << 29;
