@@ -408,11 +408,12 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
   Lds<T>* zp = HALO ? nullptr
                     : zl + (stored ? ((FWD ? 0 : L - 1) * C + ln.c) * 3 + a : L * C * 3);
   const int zstep = HALO || !stored ? 0 : FWD ? C * 3 : -C * 3;
-  auto data = [&](int s, int ix, ColJob<T>& j, auto next_idx) __attribute__((always_inline)) {
+  auto data = [&](int s, bool at, int ix, ColJob<T>& j, auto next_idx)
+      __attribute__((always_inline)) {
     const int l = level(s), so = FWD ? so_rec : last_rec - so_rec;   // (l: HALO)
-    const bool at = ix != 0;
     const int vr = at ? vrec : kOut;
     so_rec = min(so_rec + rb, last_rec);
+    next_idx();
     // 8 or 12 values in whole chunks (backward: the ninth follows them)
 #pragma unroll
     for (int c = 0; c < (FWD ? 12 : 8) / kV; ++c) {
@@ -445,7 +446,6 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     } else if (HALO) {
       j.z = col_load<T>(rz, at ? vz : kOut, l * C * 3 * ts);
     }
-    next_idx();
     // keep every load of the stage here, ahead of the computation of the
     // current level, and the arithmetic on them after this point
     asm volatile("" ::: "memory");
@@ -454,10 +454,12 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
   ColJob<T> jobs[ND];
   int idx[P];
   // prologue: the data of steps 0 .. DEPTH-1, their indices and the ND after
+  // (records by the column's range, so that they do not wait for the indices: a
+  // round trip per sweep; what an inactive cell's place holds is not used)
 #pragma unroll
   for (int s = 0; s < DEPTH + ND; ++s) idx[s] = load_idx();
 #pragma unroll
-  for (int s = 0; s < DEPTH; ++s) data(s, idx[s], jobs[s], []() {});
+  for (int s = 0; s < DEPTH; ++s) data(s, ln.at(level(s), g.bz), idx[s], jobs[s], []() {});
   // with the first levels' loads in flight: the decisions that need the
   // iteration's scalars (their loads overlap those of the sweep)
   if (!gate(q)) return false;
@@ -471,7 +473,8 @@ __device__ __forceinline__ bool col_sweep(const ColView<T>& v, int box, BlockRhs
     const T xi0 = wi[0], xi1 = wi[1], xi2 = wi[2];
     const T xj0 = wj[0], xj1 = wj[1], xj2 = wj[2];
     __builtin_amdgcn_sched_barrier(0);
-    data(s + DEPTH, idx[(qq + DEPTH) % P], jobs[(qq + DEPTH) % ND],
+    const int next = idx[(qq + DEPTH) % P];
+    data(s + DEPTH, next != 0, next, jobs[(qq + DEPTH) % ND],
          [&]() { idx[(qq + DEPTH + ND) % P] = load_idx(); });
     const ColJob<T>& j = jobs[qq % ND];
     const int ix = idx[qq];
