@@ -41,10 +41,10 @@ inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 //    slots at once (it reads the matrix a second time: cheaper than its stores
 //    and its products in the chain).
 // Factorisation with its records, by HIP events, against the recursion by
-// position and a packing pass: 9000 cells 40.2 -> 25.7 us, 500k cells
-// (4x4x50 boxes) 304 -> 201 us FP64.  Whole lattices, the exchange in the
+// position and a packing pass: 9000 cells 40.2 -> 27.7 us, 500k cells
+// (4x4x50 boxes) 304 -> 207 us FP64.  Whole lattices, the exchange in the
 // computing wavefronts -> beside them: 30 x 30 x 10 165 -> 109 us, 100 x 100 x 50
-// 875 -> 766 us.
+// 875 -> 745 us.
 struct FacIn {
   const double* J;
   const int32_t* row_ptr;
@@ -709,7 +709,7 @@ bool grid_of(const opm_problem* pb, int precision, ColGrid& g) {
   // the whole system: one box of at most 128 columns (300 cells: an
   // application 28 -> 24 us, and the updates of BiCGStab fused into it, 8
   // launches per iteration -> 5), else tiles of 8x8 columns (500k cells: an
-  // application 1120 us by planes -> 392 us; factored 1900 -> 766 us)
+  // application 1120 us by planes -> 386 us; factored 1900 -> 745 us)
   if ((long)pb->nx * pb->ny <= 128) {
     g = make_grid(pb, pb->nx, pb->ny, pb->nz, false);
     if (fits(g) && worth_whole(g)) return true;
