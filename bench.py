@@ -110,8 +110,9 @@ def gmres_cycle_bytes(n: int, nnzb: int, m: int, apply_bytes: float) -> float:
 
 
 def cpr_apply_bytes(levels, n: int, nnzb: int, apply_bytes: float) -> float:
-    """Bytes of one CPR application as designed (one kernel per level down
-    and up): down at level 0 the CSR values, columns and row pointers, the
+    """Bytes of one CPR application, each level's arrays once on the way down
+    and once up (what the cycle cannot do without; the levels of at most 2048
+    unknowns run as one dense product of 8 n^2 bytes instead): down at level 0 the CSR values, columns and row pointers, the
     diagonal, the weights and r read, b_0 and the residual written; down at
     level l the CSR, the diagonal, the child lists and the finer residual
     read, b_l and the residual written; the coarsest level's child lists,
